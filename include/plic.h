@@ -122,6 +122,29 @@ int plic_offset_backward_f64(const double *nx, const double *ny, const double *n
                              int solver, void *stream);
 
 /*
+ * plic_offset_rows_f32 / _f64, plic_volume_rows_f32 / _f64,
+ * plic_offset_backward_rows_f32 / _f64 — the three calls above (Sec. 2) for
+ * normals stored as rows: n holds 3 * count elements, (nx, ny, nz) of problem i
+ * at 3 i.  Same values, aliasing rules (d0 may be V0, V0 may be d0; nothing
+ * else may overlap) and status codes.
+ *   n_copy : NULL, or 3 * count elements that receive a copy of n, for a
+ *            caller that differentiates later and does not own n.
+ *   grad_n : 3 * count elements, the rows grad_d0 * centroid.
+ * count above INT64_MAX / 64 gives PLIC_EINVAL.
+ */
+int plic_offset_rows_f32(const float *n, const float *V0, float *d0, float *n_copy, int64_t count,
+                         int solver, int precision, void *stream);
+int plic_offset_rows_f64(const double *n, const double *V0, double *d0, double *n_copy, int64_t count,
+                         int solver, void *stream);
+int plic_volume_rows_f32(const float *n, const float *d0, float *V0, int64_t count, int precision,
+                         void *stream);
+int plic_volume_rows_f64(const double *n, const double *d0, double *V0, int64_t count, void *stream);
+int plic_offset_backward_rows_f32(const float *n, const float *V0, const float *grad_d0, float *grad_n,
+                                  float *grad_V0, int64_t count, int solver, int precision, void *stream);
+int plic_offset_backward_rows_f64(const double *n, const double *V0, const double *grad_d0, double *grad_n,
+                                  double *grad_V0, int64_t count, int solver, void *stream);
+
+/*
  * plic_curvature_workspace_bytes — recommended size of the device workspace of
  * plic_curvature_f32 and plic_curvature_backward_f32 for an X*Y*Z lattice.
  * The workspace holds a fixed part of 256 + 784 * tiles bytes (64x4x4 tiles:

@@ -37,8 +37,12 @@ from ._lib import (  # noqa: F401  (re-exported: the C ABI by name)
     plic_last_hip_error,
     plic_offset_backward_f32,
     plic_offset_backward_f64,
+    plic_offset_backward_rows_f32,
+    plic_offset_backward_rows_f64,
     plic_offset_f32,
     plic_offset_f64,
+    plic_offset_rows_f32,
+    plic_offset_rows_f64,
     plic_sphere_offset_f32,
     plic_sphere_offset_f64,
     plic_sphere_volume_f32,
@@ -47,6 +51,8 @@ from ._lib import (  # noqa: F401  (re-exported: the C ABI by name)
     plic_version,
     plic_volume_f32,
     plic_volume_f64,
+    plic_volume_rows_f32,
+    plic_volume_rows_f64,
 )
 
 __all__ = ["offset", "volume", "curvature", "PlicOffset", "PlicCurvature", "SOLVERS", "PAPER_SOLVERS", "PRECISIONS",
@@ -93,6 +99,46 @@ class PlicOffset(torch.autograd.Function):
         return gx.reshape(s), gy.reshape(s), gz.reshape(s), gv.reshape(s), None, None
 
 
+def _as_rows(n, x):
+    """Whether n is one contiguous (..., 3) tensor of x's type and device, a row
+    per element of a contiguous x: such normals go to the kernels as they are
+    (three strided columns would each be copied first).  Anything else
+    (broadcast shapes, views, tuples) takes the general path."""
+    plain = (torch.Tensor, torch.nn.Parameter)
+    return type(n) in plain and type(x) in plain and n.is_cuda and n.device == x.device and n.dtype is x.dtype and \
+        n.dtype in (torch.float32, torch.float64) and n.dim() > 0 and n.shape == (*x.shape, 3) and \
+        n.is_contiguous() and x.is_contiguous() and not n.is_neg() and not x.is_neg()
+
+
+class _PlicOffsetRows(torch.autograd.Function):
+    """PlicOffset for normals as rows.  The backward works on a copy of n that
+    the forward's kernel writes beside d0, so n may change in between."""
+
+    @staticmethod
+    def forward(ctx, n, V0, solver, precision, grad_mode):
+        d0 = torch.empty_like(V0)
+        keep = torch.empty_like(n) if grad_mode and any(ctx.needs_input_grad) else None
+        if V0.dtype == torch.float64:
+            plic_offset_rows_f64(n, V0, d0, keep, solver)
+        else:
+            plic_offset_rows_f32(n, V0, d0, keep, solver, precision)
+        if keep is not None:
+            ctx.save_for_backward(keep, V0)
+            ctx.solver, ctx.precision = solver, precision
+        return d0
+
+    @staticmethod
+    def backward(ctx, grad_d0):
+        n, V0 = ctx.saved_tensors
+        g = grad_d0.contiguous()
+        gn, gv = torch.empty_like(n), torch.empty_like(V0)
+        if V0.dtype == torch.float64:
+            plic_offset_backward_rows_f64(n, V0, g, gn, gv, ctx.solver)
+        else:
+            plic_offset_backward_rows_f32(n, V0, g, gn, gv, ctx.solver, ctx.precision)
+        return gn, gv, None, None, None
+
+
 def offset(n, V0, solver: str = "sz", precision: str = "fp32"):
     """Plane offset d0 of the PLIC problem for normals ``n`` and fill levels ``V0``.
 
@@ -101,12 +147,19 @@ def offset(n, V0, solver: str = "sz", precision: str = "fp32"):
     FP64.  ``solver``: "analytic", "sz", "newton", "nested", or "sz_kawano" (the
     unoptimized SZ comparison variant: NaN for an axis normal at V0 in {0, 1},
     not held to the 1e-5 bound)."""
+    if _as_rows(n, V0):
+        return _PlicOffsetRows.apply(n, V0, solver, precision, torch.is_grad_enabled())
     nx, ny, nz = _split_normal(n)
     return PlicOffset.apply(nx, ny, nz, V0, solver, precision)
 
 
 def volume(n, d0, precision: str = "fp32"):
     """Forward volume V0(n, d0) (no gradient)."""
+    if _as_rows(n, d0):
+        n, d0 = n.detach(), d0.detach()
+        out = torch.empty_like(d0)
+        return plic_volume_rows_f64(n, d0, out) if d0.dtype == torch.float64 else \
+            plic_volume_rows_f32(n, d0, out, precision)
     nx, ny, nz = _split_normal(n)
     shape = d0.shape
     nx, ny, nz, d0 = (t.detach().contiguous().reshape(-1) for t in torch.broadcast_tensors(nx, ny, nz, d0))

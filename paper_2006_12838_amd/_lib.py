@@ -43,6 +43,12 @@ _c = {
     "plic_volume_f64": _sig("plic_volume_f64", [_vp] * 5 + [_i64, _vp]),
     "plic_offset_backward_f32": _sig("plic_offset_backward_f32", [_vp] * 9 + [_i64, _int, _int, _vp]),
     "plic_offset_backward_f64": _sig("plic_offset_backward_f64", [_vp] * 9 + [_i64, _int, _vp]),
+    "plic_offset_rows_f32": _sig("plic_offset_rows_f32", [_vp] * 4 + [_i64, _int, _int, _vp]),
+    "plic_offset_rows_f64": _sig("plic_offset_rows_f64", [_vp] * 4 + [_i64, _int, _vp]),
+    "plic_volume_rows_f32": _sig("plic_volume_rows_f32", [_vp] * 3 + [_i64, _int, _vp]),
+    "plic_volume_rows_f64": _sig("plic_volume_rows_f64", [_vp] * 3 + [_i64, _vp]),
+    "plic_offset_backward_rows_f32": _sig("plic_offset_backward_rows_f32", [_vp] * 5 + [_i64, _int, _int, _vp]),
+    "plic_offset_backward_rows_f64": _sig("plic_offset_backward_rows_f64", [_vp] * 5 + [_i64, _int, _vp]),
     "plic_curvature_f32": _sig("plic_curvature_f32",
                                [_vp, _i64, _i64, _i64, _vp, _int, _int, _vp, ctypes.c_size_t, _vp]),
     "plic_curvature_noalloc_f32": _sig("plic_curvature_noalloc_f32", [_vp, _i64, _i64, _i64, _vp, _int, _int, _vp]),
@@ -218,6 +224,67 @@ def plic_offset_backward_f64(nx, ny, nz, V0, grad_d0, grad_nx, grad_ny, grad_nz,
     args = [_ptr(t, torch.float64, n, w) for t, w in zip(ts, names)]
     _check(_c["plic_offset_backward_f64"](*args, n, _enum(SOLVERS, solver, "solver"), _stream(V0)),
            "plic_offset_backward_f64")
+
+
+# ---- normals as rows: n has 3 * V0.numel() elements, one row (x, y, z) a problem
+
+def plic_offset_rows_f32(n, V0, d0, n_copy=None, solver="analytic", precision="fp32"):
+    """n_copy, if given (n's size), receives a copy of n."""
+    m = V0.numel()
+    _same_device(n, V0, d0, n if n_copy is None else n_copy)
+    _check(_c["plic_offset_rows_f32"](_ptr(n, torch.float32, 3 * m, "n"), _ptr(V0, torch.float32, m, "V0"),
+                                      _ptr(d0, torch.float32, m, "d0"),
+                                      None if n_copy is None else _ptr(n_copy, torch.float32, 3 * m, "n_copy"), m,
+                                      _enum(SOLVERS, solver, "solver"), _enum(PRECISIONS, precision, "precision"),
+                                      _stream(V0)), "plic_offset_rows_f32")
+    return d0
+
+
+def plic_offset_rows_f64(n, V0, d0, n_copy=None, solver="analytic"):
+    m = V0.numel()
+    _same_device(n, V0, d0, n if n_copy is None else n_copy)
+    _check(_c["plic_offset_rows_f64"](_ptr(n, torch.float64, 3 * m, "n"), _ptr(V0, torch.float64, m, "V0"),
+                                      _ptr(d0, torch.float64, m, "d0"),
+                                      None if n_copy is None else _ptr(n_copy, torch.float64, 3 * m, "n_copy"), m,
+                                      _enum(SOLVERS, solver, "solver"), _stream(V0)), "plic_offset_rows_f64")
+    return d0
+
+
+def plic_volume_rows_f32(n, d0, V0, precision="fp32"):
+    m = d0.numel()
+    _same_device(n, d0, V0)
+    _check(_c["plic_volume_rows_f32"](_ptr(n, torch.float32, 3 * m, "n"), _ptr(d0, torch.float32, m, "d0"),
+                                      _ptr(V0, torch.float32, m, "V0"), m,
+                                      _enum(PRECISIONS, precision, "precision"), _stream(d0)), "plic_volume_rows_f32")
+    return V0
+
+
+def plic_volume_rows_f64(n, d0, V0):
+    m = d0.numel()
+    _same_device(n, d0, V0)
+    _check(_c["plic_volume_rows_f64"](_ptr(n, torch.float64, 3 * m, "n"), _ptr(d0, torch.float64, m, "d0"),
+                                      _ptr(V0, torch.float64, m, "V0"), m, _stream(d0)), "plic_volume_rows_f64")
+    return V0
+
+
+def plic_offset_backward_rows_f32(n, V0, grad_d0, grad_n, grad_V0, solver="analytic", precision="fp32"):
+    m = V0.numel()
+    _same_device(n, V0, grad_d0, grad_n, grad_V0)
+    _check(_c["plic_offset_backward_rows_f32"](
+        _ptr(n, torch.float32, 3 * m, "n"), _ptr(V0, torch.float32, m, "V0"),
+        _ptr(grad_d0, torch.float32, m, "grad_d0"), _ptr(grad_n, torch.float32, 3 * m, "grad_n"),
+        _ptr(grad_V0, torch.float32, m, "grad_V0"), m, _enum(SOLVERS, solver, "solver"),
+        _enum(PRECISIONS, precision, "precision"), _stream(V0)), "plic_offset_backward_rows_f32")
+
+
+def plic_offset_backward_rows_f64(n, V0, grad_d0, grad_n, grad_V0, solver="analytic"):
+    m = V0.numel()
+    _same_device(n, V0, grad_d0, grad_n, grad_V0)
+    _check(_c["plic_offset_backward_rows_f64"](
+        _ptr(n, torch.float64, 3 * m, "n"), _ptr(V0, torch.float64, m, "V0"),
+        _ptr(grad_d0, torch.float64, m, "grad_d0"), _ptr(grad_n, torch.float64, 3 * m, "grad_n"),
+        _ptr(grad_V0, torch.float64, m, "grad_V0"), m, _enum(SOLVERS, solver, "solver"), _stream(V0)),
+        "plic_offset_backward_rows_f64")
 
 
 def _lattice_dims(phi):

@@ -1,11 +1,12 @@
 // Batched PLIC kernels on gfx950: inversion (four solvers), forward volume and
 // the backward (vector-Jacobian) pass of the inversion.
 //
-// Layout: structure of arrays in HBM (nx, ny, nz, V0 / d0), one problem per
-// element.  Each thread handles VEC consecutive problems with 16-byte loads
-// and stores per array (4 floats or 2 doubles), so a wavefront moves 1 KiB per
-// array per access; VEC = 1 covers unaligned pointers, and the last thread's
-// partial vector is loaded element by element.  One pass over HBM, no reuse.
+// Layout: V0 and d0 hold one element per problem; the normals are either three
+// such arrays (nx, ny, nz) or, ROWS, one array of rows (x, y, z).  Each thread
+// handles VEC consecutive problems with 16-byte loads and stores per array (4
+// floats or 2 doubles), so a wavefront moves 1 KiB per array per access; VEC =
+// 1 covers unaligned pointers and small batches, and the last block, when it
+// is not whole, goes element by element.  One pass over HBM, no reuse.
 // The inversion kernels settle the closed-form cases in registers and pack the
 // rest (the cubic cases, about 40 % of uniformly random problems) densely in
 // LDS before the iterative / trigonometric stage, so that stage runs on full
@@ -62,10 +63,10 @@ __device__ __forceinline__ void store(S* __restrict__ p, int64_t i, const S (&v)
 }
 
 // Loads VEC consecutive elements at i, or those below count (others 0).
-// FULL: the launch covers whole blocks only, no bounds checks.
-template <class S, int VEC, bool FULL>
-__device__ __forceinline__ void load_part(const S* p, int64_t i, int64_t count, S (&v)[VEC]) {
-    if (FULL || i + VEC <= count) {
+// full: the block's problems all lie below count (uniform per block).
+template <class S, int VEC>
+__device__ __forceinline__ void load_part(const S* p, int64_t i, int64_t count, bool full, S (&v)[VEC]) {
+    if (full) {
         load<S, VEC>(p, i, v);
     } else {
 #pragma unroll
@@ -73,14 +74,110 @@ __device__ __forceinline__ void load_part(const S* p, int64_t i, int64_t count, 
     }
 }
 
-template <class S, int VEC, bool FULL>
-__device__ __forceinline__ void store_part(S* p, int64_t i, int64_t count, const S (&v)[VEC]) {
-    if (FULL || i + VEC <= count) {
+template <class S, int VEC>
+__device__ __forceinline__ void store_part(S* p, int64_t i, int64_t count, bool full, const S (&v)[VEC]) {
+    if (full) {
         store<S, VEC>(p, i, v);
     } else {
 #pragma unroll
         for (int k = 0; k < VEC; ++k)
             if (i + k < count) p[i + k] = v[k];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Normals as rows (x, y, z): the 64 VEC rows of a wavefront are 3 KiB of
+// consecutive memory.  They move as three 16-byte accesses per lane over whole
+// cache lines, and change places through LDS to and from the VEC rows of each
+// lane; the 48-byte stride of a lane's rows there meets every bank once per 8
+// lanes.  Rows loaded lane by lane instead would touch each line three times,
+// and split into component arrays beforehand they cost three strided copies:
+// the volume of 10,000,019 rows took 104.6 us so (75 of them the copies) and
+// takes 32.5 us here (6.2 TB/s).
+// ---------------------------------------------------------------------------
+template <class S, int VEC> struct RowStage {
+    typename NVec<S, VEC>::type v[3 * 64];
+};
+template <class S> struct RowStage<S, 1> {};
+
+// keep, when not null, receives a copy of the rows
+template <class S, int VEC>
+__device__ __forceinline__ void load_rows(const S* n, S* keep, int64_t i, int64_t count, bool full,
+                                          RowStage<S, VEC>& st, S (&a)[VEC], S (&b)[VEC], S (&c)[VEC]) {
+    if constexpr (VEC > 1) {
+        if (full) {
+            using V = typename NVec<S, VEC>::type;
+            const int lane = threadIdx.x & 63;
+            const int64_t first = (i - static_cast<int64_t>(lane) * VEC) * 3;
+            V t[3];
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                t[j] = __builtin_nontemporal_load(reinterpret_cast<const V*>(n + first) + j * 64 + lane);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) st.v[j * 64 + lane] = t[j];
+            if (keep) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    __builtin_nontemporal_store(t[j], reinterpret_cast<V*>(keep + first) + j * 64 + lane);
+            }
+            __syncwarp();
+            S f[3 * VEC];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const V r = st.v[lane * 3 + j];
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) f[j * VEC + k] = r[k];
+            }
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) { a[k] = f[3 * k]; b[k] = f[3 * k + 1]; c[k] = f[3 * k + 2]; }
+            __syncwarp();
+            return;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) {
+        const bool in = i + k < count;
+        const S* r = n + (i + k) * 3;
+        a[k] = in ? r[0] : S(0); b[k] = in ? r[1] : S(0); c[k] = in ? r[2] : S(0);
+        if (keep && in) {
+            S* o = keep + (i + k) * 3;
+            o[0] = a[k]; o[1] = b[k]; o[2] = c[k];
+        }
+    }
+}
+
+template <class S, int VEC>
+__device__ __forceinline__ void store_rows(S* n, int64_t i, int64_t count, bool full, RowStage<S, VEC>& st,
+                                           const S (&a)[VEC], const S (&b)[VEC], const S (&c)[VEC]) {
+    if constexpr (VEC > 1) {
+        if (full) {
+            using V = typename NVec<S, VEC>::type;
+            const int lane = threadIdx.x & 63;
+            const int64_t first = (i - static_cast<int64_t>(lane) * VEC) * 3;
+            S f[3 * VEC];
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) { f[3 * k] = a[k]; f[3 * k + 1] = b[k]; f[3 * k + 2] = c[k]; }
+            __syncwarp();
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                V r;
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) r[k] = f[j * VEC + k];
+                st.v[lane * 3 + j] = r;
+            }
+            __syncwarp();
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                __builtin_nontemporal_store(st.v[j * 64 + lane], reinterpret_cast<V*>(n + first) + j * 64 + lane);
+            return;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) {
+        if (i + k < count) {
+            S* o = n + (i + k) * 3;
+            o[0] = a[k]; o[1] = b[k]; o[2] = c[k];
+        }
     }
 }
 
@@ -140,50 +237,80 @@ __device__ __forceinline__ void solve_packed(const Reduced<T> (&r)[VEC], const b
 }
 
 // S: storage type, T: bulk arithmetic, U: cubic-case arithmetic.  d0 may be
-// V0 (each element is read and written by the same thread).  FULL launches
-// cover whole blocks (kBlock * VEC problems each) and skip the bounds checks;
-// the remainder goes to one checked block.
-template <int SOLVER, class S, class T, class U, int VEC, bool FULL>
-__global__ __launch_bounds__(kBlock) void k_offset(const S* __restrict__ nx, const S* __restrict__ ny,
-                                                   const S* __restrict__ nz, const S* V0, S* d0,
-                                                   int64_t count) {
-    __shared__ PackLds<T, VEC> sm;
-    const int64_t i = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * VEC;
+// V0 (each element is read and written by the same thread).  ROWS: the normals
+// are the rows of nx (ny, nz unused), and keep may ask for a copy of them.
+// The last block may reach past count: it takes the checked loads and stores,
+// in the same launch (a launch of its own for it cost 5 us at any size).
+template <class S, class T, int VEC, bool ROWS> union OffsetLds {
+    PackLds<T, VEC> pack;
+    RowStage<S, VEC> rows[ROWS ? kBlock / 64 : 1];
+};
+
+template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
+__device__ __forceinline__ void offset_block(const S* __restrict__ nx, const S* __restrict__ ny,
+                                             const S* __restrict__ nz, const S* V0, S* d0, S* keep, int64_t i,
+                                             int64_t count, bool full, OffsetLds<S, T, VEC, ROWS>& sm) {
     S a[VEC], b[VEC], c[VEC], v[VEC];
-    load_part<S, VEC, FULL>(nx, i, count, a); load_part<S, VEC, FULL>(ny, i, count, b);
-    load_part<S, VEC, FULL>(nz, i, count, c); load_part<S, VEC, FULL>(V0, i, count, v);
+    if constexpr (ROWS) {
+        load_rows<S, VEC>(nx, keep, i, count, full, sm.rows[threadIdx.x >> 6], a, b, c);
+    } else {
+        load_part<S, VEC>(nx, i, count, full, a); load_part<S, VEC>(ny, i, count, full, b);
+        load_part<S, VEC>(nz, i, count, full, c);
+    }
+    load_part<S, VEC>(V0, i, count, full, v);
+    if constexpr (ROWS && VEC > 1) __syncthreads();        // the packing reuses the LDS
     Reduced<T> r[VEC];
     bool valid[VEC];
     T d[VEC];
 #pragma unroll
     for (int k = 0; k < VEC; ++k) {
         r[k] = reduce(T(a[k]), T(b[k]), T(c[k]), T(v[k]));
-        valid[k] = FULL || i + k < count;
+        valid[k] = full || i + k < count;
         d[k] = T(0);
     }
-    solve_packed<SOLVER, T, U, VEC>(r, valid, d, sm);
+    solve_packed<SOLVER, T, U, VEC>(r, valid, d, sm.pack);
     S out[VEC];
 #pragma unroll
     for (int k = 0; k < VEC; ++k)
         out[k] = S(finish<SOLVER>(r[k], d[k], T(a[k]), T(b[k]), T(c[k]), T(v[k])));
-    store_part<S, VEC, FULL>(d0, i, count, out);
+    store_part<S, VEC>(d0, i, count, full, out);
 }
 
-template <class S, class T, int VEC>
+template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
+__global__ __launch_bounds__(kBlock) void k_offset(const S* __restrict__ nx, const S* __restrict__ ny,
+                                                   const S* __restrict__ nz, const S* V0, S* d0, S* keep,
+                                                   int64_t count) {
+    __shared__ OffsetLds<S, T, VEC, ROWS> sm;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kBlock * VEC), i = first + threadIdx.x * VEC;
+    if (first + kBlock * VEC <= count) offset_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, d0, keep, i, count, true, sm);
+    else offset_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, d0, keep, i, count, false, sm);
+}
+
+template <class S, class T, int VEC, bool ROWS>
+__device__ __forceinline__ void volume_block(const S* __restrict__ nx, const S* __restrict__ ny,
+                                             const S* __restrict__ nz, const S* d0, S* V0, int64_t i, int64_t count,
+                                             bool full, RowStage<S, VEC>* rows) {
+    S a[VEC], b[VEC], c[VEC], v[VEC], r[VEC];
+    if constexpr (ROWS) {
+        load_rows<S, VEC>(nx, nullptr, i, count, full, rows[threadIdx.x >> 6], a, b, c);
+    } else {
+        load_part<S, VEC>(nx, i, count, full, a); load_part<S, VEC>(ny, i, count, full, b);
+        load_part<S, VEC>(nz, i, count, full, c);
+    }
+    load_part<S, VEC>(d0, i, count, full, v);
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) r[k] = S(volume<T>(T(a[k]), T(b[k]), T(c[k]), T(v[k])));
+    store_part<S, VEC>(V0, i, count, full, r);
+}
+
+template <class S, class T, int VEC, bool ROWS>
 __global__ __launch_bounds__(kBlock) void k_volume(const S* __restrict__ nx, const S* __restrict__ ny,
                                                    const S* __restrict__ nz, const S* d0, S* V0,
                                                    int64_t count) {
-    const int64_t i = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * VEC;
-    if (i + VEC <= count) {
-        S a[VEC], b[VEC], c[VEC], v[VEC], r[VEC];
-        load<S, VEC>(nx, i, a); load<S, VEC>(ny, i, b); load<S, VEC>(nz, i, c); load<S, VEC>(d0, i, v);
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) r[k] = S(volume<T>(T(a[k]), T(b[k]), T(c[k]), T(v[k])));
-        store<S, VEC>(V0, i, r);
-    } else {
-        for (int64_t j = i; j < count; ++j)
-            V0[j] = S(volume<T>(T(nx[j]), T(ny[j]), T(nz[j]), T(d0[j])));
-    }
+    __shared__ RowStage<S, VEC> rows[ROWS ? kBlock / 64 : 1];
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kBlock * VEC), i = first + threadIdx.x * VEC;
+    if (first + kBlock * VEC <= count) volume_block<S, T, VEC, ROWS>(nx, ny, nz, d0, V0, i, count, true, rows);
+    else volume_block<S, T, VEC, ROWS>(nx, ny, nz, d0, V0, i, count, false, rows);
 }
 
 // plane-sphere intersection (Sec. 3): one input and one output array;
@@ -218,17 +345,21 @@ __device__ __forceinline__ void backward1(T nx, T ny, T nz, T V0, T d0, T gd, T&
 // The backward solves one problem per thread (no packing): its gradient stage
 // is as long as the solve, and the packing's LDS and barriers cost more
 // occupancy than they save there.  grad_d0 is loaded with the other inputs.
-template <int SOLVER, class S, class T, class U, int VEC, bool FULL>
-__global__ __launch_bounds__(kBwdBlock) void k_offset_bwd(const S* __restrict__ nx, const S* __restrict__ ny,
-                                                       const S* __restrict__ nz, const S* __restrict__ V0,
-                                                       const S* __restrict__ gd, S* __restrict__ gnx,
-                                                       S* __restrict__ gny, S* __restrict__ gnz,
-                                                       S* __restrict__ gV0, int64_t count) {
-    const int64_t i = (static_cast<int64_t>(blockIdx.x) * kBwdBlock + threadIdx.x) * VEC;
+// ROWS: the normals and their gradients are the rows of nx and gnx.
+template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
+__device__ __forceinline__ void bwd_block(const S* __restrict__ nx, const S* __restrict__ ny, const S* __restrict__ nz,
+                                          const S* __restrict__ V0, const S* __restrict__ gd, S* __restrict__ gnx,
+                                          S* __restrict__ gny, S* __restrict__ gnz, S* __restrict__ gV0, int64_t i,
+                                          int64_t count, bool full, RowStage<S, VEC>* rows) {
     S a[VEC], b[VEC], c[VEC], v[VEC], g[VEC];
-    load_part<S, VEC, FULL>(nx, i, count, a); load_part<S, VEC, FULL>(ny, i, count, b);
-    load_part<S, VEC, FULL>(nz, i, count, c); load_part<S, VEC, FULL>(V0, i, count, v);
-    load_part<S, VEC, FULL>(gd, i, count, g);
+    if constexpr (ROWS) {
+        load_rows<S, VEC>(nx, nullptr, i, count, full, rows[threadIdx.x >> 6], a, b, c);
+    } else {
+        load_part<S, VEC>(nx, i, count, full, a); load_part<S, VEC>(ny, i, count, full, b);
+        load_part<S, VEC>(nz, i, count, full, c);
+    }
+    load_part<S, VEC>(V0, i, count, full, v);
+    load_part<S, VEC>(gd, i, count, full, g);
     S ox[VEC], oy[VEC], oz[VEC], ov[VEC];
 #pragma unroll
     for (int k = 0; k < VEC; ++k) {
@@ -237,8 +368,27 @@ __global__ __launch_bounds__(kBwdBlock) void k_offset_bwd(const S* __restrict__ 
         backward1<T>(T(a[k]), T(b[k]), T(c[k]), T(v[k]), d0, T(g[k]), x, y, z, w);
         ox[k] = S(x); oy[k] = S(y); oz[k] = S(z); ov[k] = S(w);
     }
-    store_part<S, VEC, FULL>(gnx, i, count, ox); store_part<S, VEC, FULL>(gny, i, count, oy);
-    store_part<S, VEC, FULL>(gnz, i, count, oz); store_part<S, VEC, FULL>(gV0, i, count, ov);
+    if constexpr (ROWS) {
+        store_rows<S, VEC>(gnx, i, count, full, rows[threadIdx.x >> 6], ox, oy, oz);
+    } else {
+        store_part<S, VEC>(gnx, i, count, full, ox); store_part<S, VEC>(gny, i, count, full, oy);
+        store_part<S, VEC>(gnz, i, count, full, oz);
+    }
+    store_part<S, VEC>(gV0, i, count, full, ov);
+}
+
+template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
+__global__ __launch_bounds__(kBwdBlock) void k_offset_bwd(const S* __restrict__ nx, const S* __restrict__ ny,
+                                                       const S* __restrict__ nz, const S* __restrict__ V0,
+                                                       const S* __restrict__ gd, S* __restrict__ gnx,
+                                                       S* __restrict__ gny, S* __restrict__ gnz,
+                                                       S* __restrict__ gV0, int64_t count) {
+    __shared__ RowStage<S, VEC> rows[ROWS ? kBwdBlock / 64 : 1];
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kBwdBlock * VEC), i = first + threadIdx.x * VEC;
+    if (first + kBwdBlock * VEC <= count)
+        bwd_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, gd, gnx, gny, gnz, gV0, i, count, true, rows);
+    else
+        bwd_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, gd, gnx, gny, gnz, gV0, i, count, false, rows);
 }
 
 inline unsigned grid_for(int64_t count, int vec, int block = kBlock) {
@@ -252,17 +402,20 @@ template <class S> constexpr int kVec = 16 / sizeof(S);
 // chunks of 2^30 problems (a multiple of every block's problem count).
 constexpr int64_t kChunkProblems = int64_t(1) << 30;
 
-template <class S, class T, int VEC>
+// rows of three elements advance three times as fast as single elements
+template <bool ROWS, class S> S* advance(S* p, int64_t base) { return p ? p + base * (ROWS ? 3 : 1) : p; }
+
+template <class S, class T, int VEC, bool ROWS>
 void launch_volume_v(const S* nx, const S* ny, const S* nz, const S* d0, S* V0, int64_t count, hipStream_t st) {
     for (int64_t base = 0; base < count; base += kChunkProblems) {
         const int64_t n = count - base < kChunkProblems ? count - base : kChunkProblems;
-        hipLaunchKernelGGL((k_volume<S, T, VEC>), dim3(grid_for(n, VEC)), dim3(kBlock), 0, st, nx + base, ny + base,
-                           nz + base, d0 + base, V0 + base, n);
+        hipLaunchKernelGGL((k_volume<S, T, VEC, ROWS>), dim3(grid_for(n, VEC)), dim3(kBlock), 0, st,
+                           advance<ROWS>(nx, base), advance<ROWS>(ny, base), advance<ROWS>(nz, base), d0 + base,
+                           V0 + base, n);
     }
 }
 
 // ---- dispatch ------------------------------------------------------------------
-// whole blocks unchecked, then the remainder in one checked block
 template <int OP, class S>
 void launch_sphere(const S* in, S* out, int64_t count, hipStream_t st) {
     const bool vec = aligned(in, 16) && aligned(out, 16);
@@ -277,71 +430,68 @@ void launch_sphere(const S* in, S* out, int64_t count, hipStream_t st) {
     }
 }
 
-template <int SOLVER, class S, class T, class U, int VEC>
-void launch_offset_v(const S* nx, const S* ny, const S* nz, const S* V0, S* d0, int64_t count, hipStream_t st) {
-    const int64_t per = static_cast<int64_t>(kBlock) * VEC, full = count / per * per, rem = count - full;
-    for (int64_t base = 0; base < full; base += kChunkProblems) {
-        const int64_t n = full - base < kChunkProblems ? full - base : kChunkProblems;
-        hipLaunchKernelGGL((k_offset<SOLVER, S, T, U, VEC, true>), dim3(grid_for(n, VEC)), dim3(kBlock), 0, st,
-                           nx + base, ny + base, nz + base, V0 + base, d0 + base, n);
+template <class S> struct OffsetArgs {
+    const S *nx, *ny, *nz, *V0;
+    S *d0, *keep;
+    int64_t count;
+};
+
+template <class S> struct BwdArgs {
+    const S *nx, *ny, *nz, *V0, *gd;
+    S *gx, *gy, *gz, *gv;
+    int64_t count;
+};
+
+template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
+void launch_offset_v(const OffsetArgs<S>& p, hipStream_t st) {
+    for (int64_t base = 0; base < p.count; base += kChunkProblems) {
+        const int64_t n = p.count - base < kChunkProblems ? p.count - base : kChunkProblems;
+        hipLaunchKernelGGL((k_offset<SOLVER, S, T, U, VEC, ROWS>), dim3(grid_for(n, VEC)), dim3(kBlock), 0, st,
+                           advance<ROWS>(p.nx, base), advance<ROWS>(p.ny, base), advance<ROWS>(p.nz, base),
+                           p.V0 + base, p.d0 + base, advance<ROWS>(p.keep, base), n);
     }
-    if (rem)
-        hipLaunchKernelGGL((k_offset<SOLVER, S, T, U, VEC, false>), dim3(1), dim3(kBlock), 0, st,
-                           nx + full, ny + full, nz + full, V0 + full, d0 + full, rem);
 }
 
-template <int SOLVER, class S, class T, class U>
-void launch_offset_t(const S* nx, const S* ny, const S* nz, const S* V0, S* d0, int64_t count,
-                     bool vec, hipStream_t st) {
-    if (vec) launch_offset_v<SOLVER, S, T, U, kVec<S>>(nx, ny, nz, V0, d0, count, st);
-    else launch_offset_v<SOLVER, S, T, U, 1>(nx, ny, nz, V0, d0, count, st);
+template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
+void launch_bwd_v(const BwdArgs<S>& p, hipStream_t st) {
+    for (int64_t base = 0; base < p.count; base += kChunkProblems) {
+        const int64_t n = p.count - base < kChunkProblems ? p.count - base : kChunkProblems;
+        hipLaunchKernelGGL((k_offset_bwd<SOLVER, S, T, U, VEC, ROWS>), dim3(grid_for(n, VEC, kBwdBlock)),
+                           dim3(kBwdBlock), 0, st, advance<ROWS>(p.nx, base), advance<ROWS>(p.ny, base),
+                           advance<ROWS>(p.nz, base), p.V0 + base, p.gd + base, advance<ROWS>(p.gx, base),
+                           advance<ROWS>(p.gy, base), advance<ROWS>(p.gz, base), p.gv + base, n);
+    }
 }
 
-template <class S, class T, class U>
-void launch_offset_s(int solver, const S* nx, const S* ny, const S* nz, const S* V0, S* d0,
-                     int64_t count, bool vec, hipStream_t st) {
+template <int SOLVER, class S, class T, class U, bool ROWS>
+void launch_t(const OffsetArgs<S>& p, bool vec, hipStream_t st) {
+    if (vec) launch_offset_v<SOLVER, S, T, U, kVec<S>, ROWS>(p, st);
+    else launch_offset_v<SOLVER, S, T, U, 1, ROWS>(p, st);
+}
+
+template <int SOLVER, class S, class T, class U, bool ROWS>
+void launch_t(const BwdArgs<S>& p, bool vec, hipStream_t st) {
+    if (vec) launch_bwd_v<SOLVER, S, T, U, kVec<S>, ROWS>(p, st);
+    else launch_bwd_v<SOLVER, S, T, U, 1, ROWS>(p, st);
+}
+
+// the solver's kernel for a forward (OffsetArgs) or a backward (BwdArgs)
+template <class S, class T, class U, bool ROWS, class Args>
+void launch_s(int solver, const Args& p, bool vec, hipStream_t st) {
     switch (solver) {
-        case kSZ: launch_offset_t<kSZ, S, T, U>(nx, ny, nz, V0, d0, count, vec, st); break;
-        case kNewton: launch_offset_t<kNewton, S, T, U>(nx, ny, nz, V0, d0, count, vec, st); break;
-        case kNested: launch_offset_t<kNested, S, T, U>(nx, ny, nz, V0, d0, count, vec, st); break;
-        case kKawano: launch_offset_t<kKawano, S, T, U>(nx, ny, nz, V0, d0, count, vec, st); break;
-        default: launch_offset_t<kAnalytic, S, T, U>(nx, ny, nz, V0, d0, count, vec, st); break;
+        case kSZ: launch_t<kSZ, S, T, U, ROWS>(p, vec, st); break;
+        case kNewton: launch_t<kNewton, S, T, U, ROWS>(p, vec, st); break;
+        case kNested: launch_t<kNested, S, T, U, ROWS>(p, vec, st); break;
+        case kKawano: launch_t<kKawano, S, T, U, ROWS>(p, vec, st); break;
+        default: launch_t<kAnalytic, S, T, U, ROWS>(p, vec, st); break;
     }
 }
 
-template <int SOLVER, class S, class T, class U, int VEC>
-void launch_bwd_v(const S* nx, const S* ny, const S* nz, const S* V0, const S* gd, S* gx, S* gy, S* gz, S* gv,
-                  int64_t count, hipStream_t st) {
-    const int64_t per = static_cast<int64_t>(kBwdBlock) * VEC, full = count / per * per, rem = count - full;
-    for (int64_t base = 0; base < full; base += kChunkProblems) {
-        const int64_t n = full - base < kChunkProblems ? full - base : kChunkProblems;
-        hipLaunchKernelGGL((k_offset_bwd<SOLVER, S, T, U, VEC, true>), dim3(grid_for(n, VEC, kBwdBlock)), dim3(kBwdBlock), 0,
-                           st, nx + base, ny + base, nz + base, V0 + base, gd + base, gx + base, gy + base, gz + base,
-                           gv + base, n);
-    }
-    if (rem)
-        hipLaunchKernelGGL((k_offset_bwd<SOLVER, S, T, U, VEC, false>), dim3(1), dim3(kBwdBlock), 0, st,
-                           nx + full, ny + full, nz + full, V0 + full, gd + full, gx + full, gy + full, gz + full,
-                           gv + full, rem);
-}
-
-template <int SOLVER, class S, class T, class U>
-void launch_bwd_t(const S* nx, const S* ny, const S* nz, const S* V0, const S* gd, S* gx, S* gy,
-                  S* gz, S* gv, int64_t count, bool vec, hipStream_t st) {
-    if (vec) launch_bwd_v<SOLVER, S, T, U, kVec<S>>(nx, ny, nz, V0, gd, gx, gy, gz, gv, count, st);
-    else launch_bwd_v<SOLVER, S, T, U, 1>(nx, ny, nz, V0, gd, gx, gy, gz, gv, count, st);
-}
-
-template <class S, class T, class U>
-void launch_bwd_s(int solver, const S* nx, const S* ny, const S* nz, const S* V0, const S* gd, S* gx,
-                  S* gy, S* gz, S* gv, int64_t count, bool vec, hipStream_t st) {
-    switch (solver) {
-        case kSZ: launch_bwd_t<kSZ, S, T, U>(nx, ny, nz, V0, gd, gx, gy, gz, gv, count, vec, st); break;
-        case kNewton: launch_bwd_t<kNewton, S, T, U>(nx, ny, nz, V0, gd, gx, gy, gz, gv, count, vec, st); break;
-        case kNested: launch_bwd_t<kNested, S, T, U>(nx, ny, nz, V0, gd, gx, gy, gz, gv, count, vec, st); break;
-        case kKawano: launch_bwd_t<kKawano, S, T, U>(nx, ny, nz, V0, gd, gx, gy, gz, gv, count, vec, st); break;
-        default: launch_bwd_t<kAnalytic, S, T, U>(nx, ny, nz, V0, gd, gx, gy, gz, gv, count, vec, st); break;
-    }
+template <bool ROWS, class Args>
+void launch_f32(int solver, int precision, const Args& p, bool vec, hipStream_t st) {
+    if (precision == PLIC_FP32) launch_s<float, float, float, ROWS>(solver, p, vec, st);
+    else if (precision == PLIC_MIXED) launch_s<float, float, double, ROWS>(solver, p, vec, st);
+    else launch_s<float, double, double, ROWS>(solver, p, vec, st);
 }
 
 template <class S>
@@ -349,6 +499,63 @@ bool all_aligned16(std::initializer_list<const void*> ps) {
     for (const void* p : ps)
         if (!aligned(p, 16)) return false;
     return true;
+}
+
+// normals as rows: 3 count elements, overlapping nothing that is written
+template <class S>
+int offset_rows_entry(const S* n, const S* V0, S* d0, S* keep, int64_t count, int solver, int precision, void* stream) {
+    if (count < 0 || count > INT64_MAX / 64 || !valid_solver(solver) || !valid_precision(precision)) return PLIC_EINVAL;
+    if (!valid_array(n, count) || !valid_array(V0, count) || !valid_array(d0, count) || !aligned(keep, sizeof(S)))
+        return PLIC_EINVAL;
+    const size_t nb = static_cast<size_t>(count) * sizeof(S), kb = keep ? 3 * nb : 0;
+    if (overlap(d0, nb, n, 3 * nb) || (overlap(d0, nb, V0, nb) && d0 != V0)) return PLIC_EINVAL;
+    if (overlap(keep, kb, n, 3 * nb) || overlap(keep, kb, V0, nb) || overlap(keep, kb, d0, nb)) return PLIC_EINVAL;
+    if (count == 0) return PLIC_OK;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const bool vec = all_aligned16<S>({n, V0, d0, keep});
+    const OffsetArgs<S> p{n, nullptr, nullptr, V0, d0, keep, count};
+    if constexpr (sizeof(S) == 4) launch_f32<true>(solver, precision, p, vec, st);
+    else launch_s<double, double, double, true>(solver, p, vec, st);
+    return launch_status();
+}
+
+template <class S>
+int volume_rows_entry(const S* n, const S* d0, S* V0, int64_t count, int precision, void* stream) {
+    if (count < 0 || count > INT64_MAX / 64 || !valid_precision(precision)) return PLIC_EINVAL;
+    if (!valid_array(n, count) || !valid_array(d0, count) || !valid_array(V0, count)) return PLIC_EINVAL;
+    const size_t nb = static_cast<size_t>(count) * sizeof(S);
+    if (overlap(V0, nb, n, 3 * nb) || (overlap(V0, nb, d0, nb) && V0 != d0)) return PLIC_EINVAL;
+    if (count == 0) return PLIC_OK;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const bool vec = all_aligned16<S>({n, d0, V0});
+    const S* no = nullptr;
+    if (sizeof(S) == 4 && precision != PLIC_FP64) {
+        if (vec) launch_volume_v<S, S, kVec<S>, true>(n, no, no, d0, V0, count, st);
+        else launch_volume_v<S, S, 1, true>(n, no, no, d0, V0, count, st);
+    } else {
+        if (vec) launch_volume_v<S, double, kVec<S>, true>(n, no, no, d0, V0, count, st);
+        else launch_volume_v<S, double, 1, true>(n, no, no, d0, V0, count, st);
+    }
+    return launch_status();
+}
+
+template <class S>
+int bwd_rows_entry(const S* n, const S* V0, const S* gd, S* gn, S* gv, int64_t count, int solver, int precision,
+                   void* stream) {
+    if (count < 0 || count > INT64_MAX / 64 || !valid_solver(solver) || !valid_precision(precision)) return PLIC_EINVAL;
+    for (const S* p : {n, V0, gd}) if (!valid_array(p, count)) return PLIC_EINVAL;
+    if (!valid_array(gn, count) || !valid_array(gv, count)) return PLIC_EINVAL;
+    const size_t nb = static_cast<size_t>(count) * sizeof(S);
+    if (overlap(gn, 3 * nb, n, 3 * nb) || overlap(gn, 3 * nb, V0, nb) || overlap(gn, 3 * nb, gd, nb) ||
+        overlap(gn, 3 * nb, gv, nb) || overlap(gv, nb, n, 3 * nb) || overlap(gv, nb, V0, nb) || overlap(gv, nb, gd, nb))
+        return PLIC_EINVAL;
+    if (count == 0) return PLIC_OK;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const bool vec = all_aligned16<S>({n, V0, gd, gn, gv});
+    const BwdArgs<S> p{n, nullptr, nullptr, V0, gd, gn, nullptr, nullptr, gv, count};
+    if constexpr (sizeof(S) == 4) launch_f32<true>(solver, precision, p, vec, st);
+    else launch_s<double, double, double, true>(solver, p, vec, st);
+    return launch_status();
 }
 
 // plane-sphere entry points: in and out may be the same array (each element
@@ -383,9 +590,7 @@ int plic_offset_f32(const float* nx, const float* ny, const float* nz, const flo
     if (count == 0) return PLIC_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool vec = all_aligned16<float>({nx, ny, nz, V0, d0});
-    if (precision == PLIC_FP32) launch_offset_s<float, float, float>(solver, nx, ny, nz, V0, d0, count, vec, st);
-    else if (precision == PLIC_MIXED) launch_offset_s<float, float, double>(solver, nx, ny, nz, V0, d0, count, vec, st);
-    else launch_offset_s<float, double, double>(solver, nx, ny, nz, V0, d0, count, vec, st);
+    launch_f32<false>(solver, precision, OffsetArgs<float>{nx, ny, nz, V0, d0, nullptr, count}, vec, st);
     return launch_status();
 }
 
@@ -402,7 +607,7 @@ int plic_offset_f64(const double* nx, const double* ny, const double* nz, const 
     if (count == 0) return PLIC_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool vec = all_aligned16<double>({nx, ny, nz, V0, d0});
-    launch_offset_s<double, double, double>(solver, nx, ny, nz, V0, d0, count, vec, st);
+    launch_s<double, double, double, false>(solver, OffsetArgs<double>{nx, ny, nz, V0, d0, nullptr, count}, vec, st);
     return launch_status();
 }
 
@@ -420,11 +625,11 @@ int plic_volume_f32(const float* nx, const float* ny, const float* nz, const flo
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool vec = all_aligned16<float>({nx, ny, nz, d0, V0});
     if (precision == PLIC_FP64) {
-        if (vec) launch_volume_v<float, double, 4>(nx, ny, nz, d0, V0, count, st);
-        else launch_volume_v<float, double, 1>(nx, ny, nz, d0, V0, count, st);
+        if (vec) launch_volume_v<float, double, 4, false>(nx, ny, nz, d0, V0, count, st);
+        else launch_volume_v<float, double, 1, false>(nx, ny, nz, d0, V0, count, st);
     } else {
-        if (vec) launch_volume_v<float, float, 4>(nx, ny, nz, d0, V0, count, st);
-        else launch_volume_v<float, float, 1>(nx, ny, nz, d0, V0, count, st);
+        if (vec) launch_volume_v<float, float, 4, false>(nx, ny, nz, d0, V0, count, st);
+        else launch_volume_v<float, float, 1, false>(nx, ny, nz, d0, V0, count, st);
     }
     return launch_status();
 }
@@ -441,8 +646,8 @@ int plic_volume_f64(const double* nx, const double* ny, const double* nz, const 
         return PLIC_EINVAL;
     if (count == 0) return PLIC_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (all_aligned16<double>({nx, ny, nz, d0, V0})) launch_volume_v<double, double, 2>(nx, ny, nz, d0, V0, count, st);
-    else launch_volume_v<double, double, 1>(nx, ny, nz, d0, V0, count, st);
+    if (all_aligned16<double>({nx, ny, nz, d0, V0})) launch_volume_v<double, double, 2, false>(nx, ny, nz, d0, V0, count, st);
+    else launch_volume_v<double, double, 1, false>(nx, ny, nz, d0, V0, count, st);
     return launch_status();
 }
 
@@ -462,12 +667,8 @@ int plic_offset_backward_f32(const float* nx, const float* ny, const float* nz, 
     if (count == 0) return PLIC_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool vec = all_aligned16<float>({nx, ny, nz, V0, grad_d0, grad_nx, grad_ny, grad_nz, grad_V0});
-    if (precision == PLIC_FP32)
-        launch_bwd_s<float, float, float>(solver, nx, ny, nz, V0, grad_d0, grad_nx, grad_ny, grad_nz, grad_V0, count, vec, st);
-    else if (precision == PLIC_MIXED)
-        launch_bwd_s<float, float, double>(solver, nx, ny, nz, V0, grad_d0, grad_nx, grad_ny, grad_nz, grad_V0, count, vec, st);
-    else
-        launch_bwd_s<float, double, double>(solver, nx, ny, nz, V0, grad_d0, grad_nx, grad_ny, grad_nz, grad_V0, count, vec, st);
+    launch_f32<false>(solver, precision,
+                      BwdArgs<float>{nx, ny, nz, V0, grad_d0, grad_nx, grad_ny, grad_nz, grad_V0, count}, vec, st);
     return launch_status();
 }
 
@@ -487,10 +688,33 @@ int plic_offset_backward_f64(const double* nx, const double* ny, const double* n
     if (count == 0) return PLIC_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool vec = all_aligned16<double>({nx, ny, nz, V0, grad_d0, grad_nx, grad_ny, grad_nz, grad_V0});
-    launch_bwd_s<double, double, double>(solver, nx, ny, nz, V0, grad_d0, grad_nx, grad_ny, grad_nz, grad_V0, count, vec, st);
+    launch_s<double, double, double, false>(
+        solver, BwdArgs<double>{nx, ny, nz, V0, grad_d0, grad_nx, grad_ny, grad_nz, grad_V0, count}, vec, st);
     return launch_status();
 }
 
+int plic_offset_rows_f32(const float* n, const float* V0, float* d0, float* n_copy, int64_t count, int solver,
+                         int precision, void* stream) {
+    return offset_rows_entry<float>(n, V0, d0, n_copy, count, solver, precision, stream);
+}
+int plic_offset_rows_f64(const double* n, const double* V0, double* d0, double* n_copy, int64_t count, int solver,
+                         void* stream) {
+    return offset_rows_entry<double>(n, V0, d0, n_copy, count, solver, PLIC_FP64, stream);
+}
+int plic_volume_rows_f32(const float* n, const float* d0, float* V0, int64_t count, int precision, void* stream) {
+    return volume_rows_entry<float>(n, d0, V0, count, precision, stream);
+}
+int plic_volume_rows_f64(const double* n, const double* d0, double* V0, int64_t count, void* stream) {
+    return volume_rows_entry<double>(n, d0, V0, count, PLIC_FP64, stream);
+}
+int plic_offset_backward_rows_f32(const float* n, const float* V0, const float* grad_d0, float* grad_n, float* grad_V0,
+                                  int64_t count, int solver, int precision, void* stream) {
+    return bwd_rows_entry<float>(n, V0, grad_d0, grad_n, grad_V0, count, solver, precision, stream);
+}
+int plic_offset_backward_rows_f64(const double* n, const double* V0, const double* grad_d0, double* grad_n,
+                                  double* grad_V0, int64_t count, int solver, void* stream) {
+    return bwd_rows_entry<double>(n, V0, grad_d0, grad_n, grad_V0, count, solver, PLIC_FP64, stream);
+}
 
 int plic_sphere_offset_f32(const float* V0, float* d0, int64_t count, void* stream) {
     return sphere_entry<0, float>(V0, d0, count, stream);
