@@ -201,7 +201,7 @@ PMC_DISPATCHES = {
     "offset_sz": ("k_offset<1, float, float, float, 4,",),
     "offset_newton": ("k_offset<2, float, float, float, 4,",),
     "offset_nested": ("k_offset<3, float, float, float, 4,",),
-    "volume": ("k_volume<float, float, 4>",),
+    "volume": ("k_volume<float, float, 4, false>",),
     "offset_backward_sz": ("k_offset_bwd<1, float, float, float, 4,",),
     "curvature_fwd": ("k_curv_scan<true, true>", "k_curv_quads<0, float, double, double, false, 0, false>"),
     "curvature_bwd": ("k_curv_scan<true, false>", "k_curv_quads<0, float, double, double, true, 0, false>",
@@ -430,9 +430,8 @@ def write_trace_profile(trace_csv, out=None):
         "the 192^3 differentiation lattice, the paper-method benchmark `k_isolated`) appear with their own "
         "call counts.",
         "",
-        "Template arguments: `k_offset<solver, storage, bulk, cubic, problems per lane, whole blocks>`, "
-        "`k_curv_items<solver, points, cubic, fit, backward, normal, neighbour normals>`, "
-        "`k_curv_quads<solver, points, cubic, fit, backward, normal, neighbour normals>` (16 lanes per cell), "
+        "Template arguments: `k_offset<solver, storage, bulk, cubic, problems per lane, normals as rows>`, "
+        "`k_curv_quads<solver, points, cubic, fit, backward, normal, neighbour normals>` (4 lanes per cell), "
         "`k_curv_gather_fallback<solver, points, cubic, fit, normal>`, "
         "`k_curv_gather_direct<neighbour normals, normal, writes the zeros>`; solver 0 analytic, 1 optimized SZ, "
         "2 Newton-Raphson, 3 nested intervals, 4 Kawano's SZ; normal 0 Parker-Youngs.",

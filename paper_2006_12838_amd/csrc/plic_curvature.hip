@@ -11,12 +11,11 @@
 //     lists one work item per 8 interface cells of each tile; the backward
 //     also records each tile's interface count;
 //  3. a persistent kernel over the work list in which each interface cell is
-//     computed by a group of 16 lanes: the group finds its cell from the
-//     bitmask, stages its neighbourhood in LDS, and lane j takes slots j and
-//     j + 16 of the 3x3x3 neighbourhood (their PLIC offsets and rows of the
-//     normal equations; slot 26 is the centre).  Sums over the neighbours go
-//     through a small LDS tile and are added in a fixed order, so results are
-//     bitwise reproducible.
+//     computed by a group of 4 lanes: the group finds its cell from the
+//     bitmask, stages its neighbourhood in LDS, and its lanes share out the
+//     interface neighbours (their PLIC offsets and rows of the normal
+//     equations).  Sums over the neighbours are formed in a fixed order, so
+//     results are bitwise reproducible.
 // The backward first assigns contribution rows by a prefix over the tiles'
 // interface counts in tile order and lists the tiles next to the interface;
 // the work items store each interface cell's 27 contributions in its row; a
@@ -51,6 +50,7 @@ constexpr int kCellsPerThread = kTile / kThreads;
 constexpr int kGroup = 32;                    // lanes per interface cell
 constexpr int kGroups = kThreads / kGroup;    // 8 cells in flight per workgroup
 constexpr int kPersistentBlocks = 2048;
+constexpr int kCellBlocks = 4096;             // wavefronts of the cell kernels: 4 per SIMD
 constexpr int kFallbackBlocks = 256;            // one per CU of an MI355X
 
 // fixed auxiliary vector r of Sec. 4.2 (non-collinear with the normal)
@@ -155,73 +155,88 @@ __device__ __forceinline__ void gradient27(const float* __restrict__ s, int c, i
 }
 
 // ---------------------------------------------------------------------------
-// One interface cell on a group of 16 lanes, four cells per wavefront.  The
-// normal, the frame, the fit and kappa are computed once per group (every
-// lane forms the same values), so per cell they cost half of what they would
-// on 32 lanes; lane j owns the points of slots j and j + 16 (slot s < 26:
-// neighbour q(s), the 26 offsets other than the centre; slot 26: the centre),
-// so each lane inverts at most two PLIC problems.  The fit's sums run over
-// the group's lanes in a fixed order (each lane's two points first), so every
-// call gives the same bits.
+// One interface cell on a group of kLanes = 4 lanes, sixteen cells per
+// wavefront.  About ten of a cell's 26 neighbours are interface cells, and only
+// those have a point: the group lists them (the centre among them) by a
+// bitmask, and lane j takes the list's entries j, j + 4, ...  So the lanes that
+// solve a PLIC problem are nearly always full, where one lane per slot of the
+// 3x3x3 leaves six of ten idle; and what is computed once per cell (normal,
+// frame, LDL^T, kappa) is repeated on 4 lanes instead of 16.  The fit's sums
+// run over the entries of each lane in list order and then over the group by
+// two quad permutations, always in the same order, so every call gives the
+// same bits.  Bound by instruction issue and the latency of its chains: with 16
+// lanes per cell, two slots each, a spray of 24 drops (512 x 384 x 384, mixed
+// precision) took 183 us forward and 308 us adjoint, the 256^3 sphere 16.4 us
+// forward; with 4 lanes 96, 158 and 11.8 us.
 // ---------------------------------------------------------------------------
-constexpr int kQuad = 16;                       // lanes per interface cell
-constexpr int kQuads = kThreads / kQuad;        // cells in flight per workgroup
+constexpr int kLanes = 4;                       // lanes per interface cell
+constexpr int kWaveCells = 64 / kLanes;         // cells of a wavefront
+constexpr int kRounds = (27 + kLanes - 1) / kLanes;
+constexpr unsigned kCentre = 1u << 13;
 
-template <class F, int COLS>
-struct alignas(16) QuadLds {
-    F stage[kQuad][COLS];
-    F res[24];                                  // 20 sums, the centre offset at 20
+// scratch of one wavefront: the offsets of each lane's entries by round; with
+// ADJ, the gradients of the points' fill levels by neighbour, and the centre's
+// own derivatives
+template <class T, bool ADJ> struct CellLds {
+    T D[kRounds][64];
+};
+template <class T> struct CellLds<T, true> {
+    T D[kRounds][64];
+    T pb[kWaveCells][27];
+    T cen[kWaveCells][4];
 };
 
-// sum over the group's 16 lanes of each of the NV entries of row, through a
-// [16][COLS] staging tile (lane k sums column k of each pass in lane order)
-template <class F, int NV, int COLS>
-__device__ __forceinline__ void quad_colsum(QuadLds<F, COLS>& L, int j, const F (&row)[NV], F (&sum)[NV]) {
-#pragma unroll
-    for (int c0 = 0; c0 < NV; c0 += COLS) {
-#pragma unroll
-        for (int k = 0; k < COLS; ++k)
-            if (c0 + k < NV) L.stage[j][k] = row[c0 + k];
-        __syncwarp();
-        if (j < COLS && c0 + j < NV) {
-            F acc = F(0);
-#pragma unroll
-            for (int l = 0; l < kQuad; ++l) acc += L.stage[l][j];
-            L.res[c0 + j] = acc;
-        }
-        __syncwarp();
-    }
-#pragma unroll
-    for (int k = 0; k < NV; ++k) sum[k] = L.res[k];
-    __syncwarp();
+template <int CTRL> __device__ __forceinline__ float quad_move(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL> __device__ __forceinline__ double quad_move(double x) {
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xF, 0xF, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL> __device__ __forceinline__ unsigned quad_move(unsigned x) {
+    return static_cast<unsigned>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), CTRL, 0xF, 0xF, true));
+}
+constexpr int kSwap1 = 0xB1, kSwap2 = 0x4E;     // quad_perm [1,0,3,2] and [2,3,0,1]
+
+// sum over the 4 lanes of the group, the same bits on each
+template <class F> __device__ __forceinline__ F group_sum(F x) {
+    x += quad_move<kSwap1>(x);
+    return x + quad_move<kSwap2>(x);
 }
 
-// this lane's point of slot q (x, y in the frame, z along n), zero when q is
-// not an interface neighbour
+// the list's entries of lane j (the first is the lowest set bit), and the next
+__device__ __forceinline__ unsigned first_entries(unsigned list, int j) {
+#pragma unroll
+    for (int i = 0; i < kLanes - 1; ++i) list = i < j ? list & (list - 1u) : list;
+    return list;
+}
+__device__ __forceinline__ unsigned next_entries(unsigned list) {
+#pragma unroll
+    for (int i = 0; i < kLanes; ++i) list &= list - 1u;
+    return list;
+}
+
+// neighbour q's point (x, y in the frame, z along n), centre normal
 template <class T, class F>
-__device__ __forceinline__ void quad_point(int q, bool iface, T D, T D0, T bx0, T bx1, T bx2, T by0, T by1, T by2,
+__device__ __forceinline__ void cell_point(int q, T D, T D0, T bx0, T bx1, T bx2, T by0, T by1, T by2,
                                            T n0, T n1, T n2, F& x, F& y, F& z) {
-    x = F(0); y = F(0); z = F(0);
-    if (iface) {
-        const T ex = T(q_dx(q)), ey = T(q_dy(q)), ez = T(q_dz(q));
-        x = F(ex * bx0 + ey * bx1 + ez * bx2);
-        y = F(ex * by0 + ey * by1 + ez * by2);
-        z = F(ex * n0 + ey * n1 + ez * n2 + (D - D0));
-    }
+    const T ex = T(q_dx(q)), ey = T(q_dy(q)), ez = T(q_dz(q));
+    x = F(ex * bx0 + ey * bx1 + ez * bx2);
+    y = F(ex * by0 + ey * by1 + ez * by2);
+    z = F(ex * n0 + ey * n1 + ez * n2 + (D - D0));
 }
 
-// neighbour-normal variant: the normal of slot q's plane, the neighbour's own
-// -h / |h| (h its 3^3 fill-level gradient) when it is an interface cell whose
-// 3^3 lies in the lattice and h does not vanish, else the centre normal that m
-// holds on entry (the rule of the oracle's variant)
+// neighbour-normal variant: the normal of interface neighbour q's plane, its
+// own -h / |h| (h its 3^3 fill-level gradient) when its 3^3 lies in the lattice
+// and h does not vanish, else the centre normal that m holds on entry (the rule
+// of the oracle's variant)
 template <int NRM, class T>
-__device__ __forceinline__ void own_normal(const float* __restrict__ s, int c, int sy, int sz, int q, bool iface,
-                                           int gx0, int gy0, int gz0, int X, int Y, int Z, T (&m)[3], bool& own,
-                                           T& ih_out) {
+__device__ __forceinline__ void own_normal(const float* __restrict__ s, int c, int sy, int sz, int q, int gx0,
+                                           int gy0, int gz0, int X, int Y, int Z, T (&m)[3], bool& own, T& ih_out) {
     const int dx = q_dx(q), dy = q_dy(q), dz = q_dz(q);
     const int ax = gx0 + dx, ay = gy0 + dy, az = gz0 + dz;
     const bool inside = ax >= 1 && ay >= 1 && az >= 1 && ax <= X - 2 && ay <= Y - 2 && az <= Z - 2;
-    if (iface && inside) {
+    if (inside) {
         T hx, hy, hz;
         gradient27<NRM, T>(s, c + dz * sz + dy * sy + dx, sy, sz, hx, hy, hz);
         const T h2 = hx * hx + hy * hy + hz * hz;
@@ -234,57 +249,55 @@ __device__ __forceinline__ void own_normal(const float* __restrict__ s, int c, i
     }
 }
 
-// neighbour-normal variant: slot q's point, the foot of its own plane
-// e + D m - D0 n, in the frame (zero when q is not an interface neighbour)
+// neighbour-normal variant: neighbour q's point, the foot of its own plane
+// e + D m - D0 n, in the frame
 template <class T, class F>
-__device__ __forceinline__ void quad_point_own(int q, bool iface, T D, T D0, const T (&m)[3], T bx0, T bx1, T bx2,
+__device__ __forceinline__ void cell_point_own(int q, T D, T D0, const T (&m)[3], T bx0, T bx1, T bx2,
                                                T by0, T by1, T by2, T n0, T n1, T n2, F& x, F& y, F& z) {
-    x = F(0); y = F(0); z = F(0);
-    if (iface) {
-        const T P0 = T(q_dx(q)) + D * m[0] - D0 * n0, P1 = T(q_dy(q)) + D * m[1] - D0 * n1,
-                P2 = T(q_dz(q)) + D * m[2] - D0 * n2;
-        x = F(P0 * bx0 + P1 * bx1 + P2 * bx2);
-        y = F(P0 * by0 + P1 * by1 + P2 * by2);
-        z = F(P0 * n0 + P1 * n1 + P2 * n2);
-    }
+    const T P0 = T(q_dx(q)) + D * m[0] - D0 * n0, P1 = T(q_dy(q)) + D * m[1] - D0 * n1,
+            P2 = T(q_dz(q)) + D * m[2] - D0 * n2;
+    x = F(P0 * bx0 + P1 * bx1 + P2 * bx2);
+    y = F(P0 * by0 + P1 * by1 + P2 * by2);
+    z = F(P0 * n0 + P1 * n1 + P2 * n2);
 }
 
-// s: LDS fill levels, c: centre index, sy/sz: LDS strides, j: lane in the
-// group (0..15), lane: lane in the wavefront.  Every lane of the group must
-// call it; returns kappa (same bits on every lane).  With ADJ, also writes
-// out[q] = gk * d kappa / d phi_q (q = 0..26) from the lane that owns q, with
-// the interface mask, the PLIC cases and the active fit parameters held
-// fixed.  With NBR (neighbour normals: each interface neighbour's point from
-// its own normal m = -h / |h|; gx0.. and X.. locate the cell in the lattice),
-// out[q] holds the derivative with every m held fixed, and the owner of slot t
-// also writes out[27 + 3t .. 29 + 3t] = gk * d kappa / d h of its neighbour
-// (zero where the neighbour keeps the centre normal); spreading that over the
-// neighbour's 3^3 is left to the gathers.
-template <int SOLVER, class T, class U, class F, bool ADJ, int NRM, int COLS, bool NBR = false>
-__device__ __forceinline__ float quad_cell(const float* __restrict__ s, int c, int sy, int sz, int j, int lane,
-                                           float gk, float* __restrict__ out, QuadLds<F, COLS>& L, int gx0 = 0,
+// s: LDS fill levels, c: centre index, sy/sz: LDS strides, lane: lane in the
+// wavefront.  Every lane of the group must call it; returns kappa (same bits
+// on every lane).  With ADJ, also writes out[q * ostride] = gk * d kappa /
+// d phi_q (q = 0..26), with the interface mask, the PLIC cases and the active
+// fit parameters held fixed.  With NBR (neighbour normals: each interface
+// neighbour's point from its own normal m = -h / |h|; gx0.. and X.. locate the
+// cell in the lattice), out holds the derivative with every m held fixed, and
+// outh[3t .. 3t+2] = gk * d kappa / d h of neighbour slot t (the 26 offsets
+// other than the centre; zero where the neighbour keeps the centre normal);
+// spreading that over the neighbour's 3^3 is left to the gathers.
+template <int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR = false>
+__device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, int sy, int sz, int lane,
+                                           float gk, float* __restrict__ out, unsigned ostride,
+                                           float* __restrict__ outh, CellLds<T, ADJ>& L, int gx0 = 0,
                                            int gy0 = 0, int gz0 = 0, int X = 0, int Y = 0, int Z = 0) {
     using mt = M<T>;
+    const int j = lane % kLanes, cell = lane / kLanes;
     T gx, gy, gz;
     gradient27<NRM, T>(s, c, sy, sz, gx, gy, gz);
-    const int qa = j < 13 ? j : j + 1;          // slot j: a neighbour
-    const int sb = j + kQuad;                   // slot j + 16: a neighbour below 26, the centre at 26
-    const bool nbb = sb < 26, centre = sb == 26;
-    const int qb = nbb ? sb + 1 : 13;
-    const float pa = s[c + q_dz(qa) * sz + q_dy(qa) * sy + q_dx(qa)];
-    const float pb = (nbb || centre) ? s[c + q_dz(qb) * sz + q_dy(qb) * sy + q_dx(qb)] : 0.0f;
-    const bool ia = is_iface(pa), ib = nbb && is_iface(pb);
-    const int g0 = lane & 48;                   // this group's lanes in the wave
-    const int npts = __popcll((__ballot(ia) >> g0) & 0xFFFFull) + __popcll((__ballot(ib) >> g0) & 0xFFFFull);
+    auto at = [&](int q) { return c + q_dz(q) * sz + q_dy(q) * sy + q_dx(q); };
+    // interface mask of the 27 cells, 7 tests per lane
+    unsigned mask = 0u;
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+        const int q = j + k * kLanes;
+        if (q < 27 && is_iface(s[at(q < 27 ? q : 0)])) mask |= 1u << q;
+    }
+    mask |= quad_move<kSwap1>(mask);
+    mask |= quad_move<kSwap2>(mask);
+    mask &= ~kCentre;
+    const unsigned list = mask | kCentre;
     const T gn2 = gx * gx + gy * gy + gz * gz;
     if (!(gn2 >= T(1e-24))) {                   // no usable normal: kappa = 0 (uniform per group)
         if constexpr (ADJ) {
-            out[qa] = 0.0f;
-            if (nbb || centre) out[qb] = 0.0f;
-            if constexpr (NBR) {
-                out[27 + 3 * j] = out[28 + 3 * j] = out[29 + 3 * j] = 0.0f;
-                if (nbb) out[27 + 3 * sb] = out[28 + 3 * sb] = out[29 + 3 * sb] = 0.0f;
-            }
+            for (int q = j; q < 27; q += kLanes) out[static_cast<unsigned>(q) * ostride] = 0.0f;
+            if constexpr (NBR)
+                for (int t = j; t < 78; t += kLanes) outh[t] = 0.0f;
         }
         return 0.0f;
     }
@@ -302,68 +315,64 @@ __device__ __forceinline__ float quad_cell(const float* __restrict__ s, int c, i
     const T iun = mt::rcp(mt::sqrt(un2));
     const T by0 = u0 * iun, by1 = u1 * iun, by2 = u2 * iun;
     const T bx0 = by1 * n2 - by2 * n1, bx1 = by2 * n0 - by0 * n2, bx2 = by0 * n1 - by1 * n0;
-    // PLIC offsets of the two slots with the centre normal (neighbour normals:
+    // PLIC offsets of the entries with the centre normal (neighbour normals:
     // each interface neighbour with its own)
-    T Da = T(0), Db = T(0), D0;
-    F xa, ya, za, xb, yb, zb;
-    T ma[3] = {n0, n1, n2}, mb[3] = {n0, n1, n2};     // neighbour normals: each slot's plane normal
-    bool owna = false, ownb = false;                  // the slot's point uses its own normal
-    T iha = T(0), ihb = T(0);                         // 1 / |h| of that normal's gradient
-    if constexpr (NBR) {
-        own_normal<NRM, T>(s, c, sy, sz, qa, ia, gx0, gy0, gz0, X, Y, Z, ma, owna, iha);
-        own_normal<NRM, T>(s, c, sy, sz, qb, ib, gx0, gy0, gz0, X, Y, Z, mb, ownb, ihb);
-        if (ia) Da = offset<SOLVER, T, U>(ma[0], ma[1], ma[2], T(pa));
-        if (ib || centre) Db = offset<SOLVER, T, U>(mb[0], mb[1], mb[2], T(pb));
-        if (centre) L.res[20] = F(Db);
-        __syncwarp();
-        D0 = T(L.res[20]);
-        quad_point_own<T, F>(qa, ia, Da, D0, ma, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, xa, ya, za);
-        quad_point_own<T, F>(qb, ib, Db, D0, mb, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, xb, yb, zb);
-    } else {
-        if (ia) Da = offset<SOLVER, T, U>(n0, n1, n2, T(pa));
-        if (ib || centre) Db = offset<SOLVER, T, U>(n0, n1, n2, T(pb));
-        if (centre) L.res[20] = F(Db);
-        __syncwarp();
-        D0 = T(L.res[20]);
-        quad_point<T, F>(qa, ia, Da, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, xa, ya, za);
-        quad_point<T, F>(qb, ib, Db, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, xb, yb, zb);
+    int k = 0;
+#pragma unroll 1
+    for (unsigned m = first_entries(list, j); m; m = next_entries(m), ++k) {
+        const int q = __ffs(static_cast<int>(m)) - 1;
+        const T p = T(s[at(q)]);
+        if constexpr (NBR) {
+            T mq[3] = {n0, n1, n2}, ih;
+            bool own = false;
+            if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, gx0, gy0, gz0, X, Y, Z, mq, own, ih);
+            L.D[k][lane] = offset<SOLVER, T, U>(mq[0], mq[1], mq[2], p);
+        } else {
+            L.D[k][lane] = offset<SOLVER, T, U>(n0, n1, n2, p);
+        }
     }
-    const F Qa[5] = {xa * xa, ya * ya, xa * ya, xa, ya}, Qb[5] = {xb * xb, yb * yb, xb * yb, xb, yb};
-    F row[20], sum[20];
+    __syncwarp();
+    const int c13 = __popc(mask & (kCentre - 1u));          // the centre's place in the list
+    const T D0 = L.D[c13 / kLanes][(lane & ~(kLanes - 1)) + c13 % kLanes];
+    F sum[20];
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
+    for (int i = 0; i < 20; ++i) sum[i] = F(0);
+    k = 0;
+#pragma unroll 1
+    for (unsigned m = first_entries(list, j); m; m = next_entries(m), ++k) {
+        const int q = __ffs(static_cast<int>(m)) - 1;
+        if (q == 13) continue;
+        const T D = L.D[k][lane];
+        F x, y, z;
+        if constexpr (NBR) {
+            T mq[3] = {n0, n1, n2}, ih;
+            bool own = false;
+            own_normal<NRM, T>(s, c, sy, sz, q, gx0, gy0, gz0, X, Y, Z, mq, own, ih);
+            cell_point_own<T, F>(q, D, D0, mq, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
+        } else {
+            cell_point<T, F>(q, D, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
+        }
+        const F Q[5] = {x * x, y * y, x * y, x, y};
 #pragma unroll
-        for (int k = 0; k <= i; ++k) row[tri(i, k)] = Qa[i] * Qa[k] + Qb[i] * Qb[k];
-        row[15 + i] = za * Qa[i] + zb * Qb[i];
+        for (int i = 0; i < 5; ++i) {
+#pragma unroll
+            for (int l = 0; l <= i; ++l) sum[tri(i, l)] += Q[i] * Q[l];
+            sum[15 + i] += z * Q[i];
+        }
     }
-    quad_colsum<F, 20, COLS>(L, j, row, sum);
+#pragma unroll
+    for (int i = 0; i < 20; ++i) sum[i] = group_sum(sum[i]);
     F m[5][5], b[5];
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
         b[i] = sum[15 + i];
 #pragma unroll
-        for (int k = 0; k <= i; ++k) m[i][k] = sum[tri(i, k)];
+        for (int l = 0; l <= i; ++l) m[i][l] = sum[tri(i, l)];
     }
+    const int npts = __popc(mask);
     bool act[5];
     F a[5], dinv[5];
     ldlt_factor<F>(m, npts < 5 ? npts : 5, act, dinv);
-    // in mixed precision the adjoint's solve reads the factor back from LDS
-    // (the staging tile is free until the adjoint's own sums): the same values,
-    // and the registers that held them are free in between, so that adjoint
-    // fits 4 waves per SIMD (in FP32 and FP64 the occupancy does not change and
-    // the factor stays in registers)
-    constexpr bool FAC = ADJ && sizeof(T) == 4 && sizeof(F) == 8;
-    F* const fac = &L.stage[0][0];
-    if constexpr (FAC) {
-        if (j == 0) {
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-#pragma unroll
-                for (int k = 0; k < i; ++k) fac[tri(i, k)] = m[i][k];
-                fac[15 + i] = dinv[i];
-            }
-        }
-    }
     ldlt_solve<F>(m, act, dinv, b, a);
     const float kappa = float(kappa_of<F>(a));
     if constexpr (ADJ) {
@@ -382,35 +391,30 @@ __device__ __forceinline__ float quad_cell(const float* __restrict__ s, int c, i
 #pragma unroll
         for (int i = 0; i < 5; ++i) abar[i] = act[i] ? abar[i] : F(0);
         F lam[5];
-        if constexpr (FAC) {
-            __syncwarp();
-            F lm[5][5], ld[5];
-#pragma unroll
-            for (int i = 0; i < 5; ++i) {
-#pragma unroll
-                for (int k = 0; k < i; ++k) lm[i][k] = fac[tri(i, k)];
-                lm[i][i] = F(0);                            // not read: the solve uses 1 / D
-                ld[i] = fac[15 + i];
-            }
-            ldlt_solve<F>(lm, act, ld, abar, lam);           // M symmetric: lambda = M^-1 abar
-        } else {
-            ldlt_solve<F>(m, act, dinv, abar, lam);
-        }
-        // each slot's point: zbar = lam.Q, Qbar = lam (z - a.Q) - a (lam.Q); the
-        // frame's adjoint rows of the two slots add up per lane
-        T phia = T(0), phibb = T(0);
-        T hba[3] = {T(0), T(0), T(0)}, hbb[3] = {T(0), T(0), T(0)};   // neighbour normals: adjoints of h
+        ldlt_solve<F>(m, act, dinv, abar, lam);              // M symmetric: lambda = M^-1 abar
+        // each point: zbar = lam.Q, Qbar = lam (z - a.Q) - a (lam.Q); the frame's
+        // adjoint rows of a lane's points add up
         F arow[10];
 #pragma unroll
         for (int i = 0; i < 10; ++i) arow[i] = F(0);
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-            const bool on = sl == 0 ? ia : ib;
-            if (!on) continue;
-            const int q = sl == 0 ? qa : qb;
-            const F x = sl == 0 ? xa : xb, y = sl == 0 ? ya : yb, z = sl == 0 ? za : zb;
-            const T D = sl == 0 ? Da : Db;
-            const float p = sl == 0 ? pa : pb;
+        k = 0;
+#pragma unroll 1
+        for (unsigned mm = first_entries(list, j); mm; mm = next_entries(mm), ++k) {
+            const int q = __ffs(static_cast<int>(mm)) - 1;
+            const T p = T(s[at(q)]), D = L.D[k][lane];
+            T mq[3] = {n0, n1, n2}, ih = T(0);
+            bool own = false;
+            if constexpr (NBR)
+                if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, gx0, gy0, gz0, X, Y, Z, mq, own, ih);
+            T cq[3];
+            const T dv = offset_grad_from_d0<T>(mq[0], mq[1], mq[2], p, D, cq);   // 1/A, centroid
+            if (q == 13) {
+                L.cen[cell][0] = cq[0]; L.cen[cell][1] = cq[1]; L.cen[cell][2] = cq[2]; L.cen[cell][3] = dv;
+                continue;
+            }
+            F x, y, z;
+            if constexpr (NBR) cell_point_own<T, F>(q, D, D0, mq, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
+            else cell_point<T, F>(q, D, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
             const F Q[5] = {x * x, y * y, x * y, x, y};
             F zq = F(0), aQ = F(0);
 #pragma unroll
@@ -424,59 +428,47 @@ __device__ __forceinline__ float quad_cell(const float* __restrict__ s, int c, i
             const T ex = T(q_dx(q)), ey = T(q_dy(q)), ez = T(q_dz(q));
             if constexpr (NBR) {
                 // x = P.b_x, y = P.b_y, z = P.n with P = e + D m - D0 n, D = d0(phi_q, m)
-                const T(&mm)[3] = sl == 0 ? ma : mb;
-                const bool own = sl == 0 ? owna : ownb;
-                const T P0 = ex + D * mm[0] - D0 * n0, P1 = ey + D * mm[1] - D0 * n1, P2 = ez + D * mm[2] - D0 * n2;
+                const T P0 = ex + D * mq[0] - D0 * n0, P1 = ey + D * mq[1] - D0 * n1, P2 = ez + D * mq[2] - D0 * n2;
                 const T Pb0 = xbar * bx0 + ybar * by0 + zt * n0;
                 const T Pb1 = xbar * bx1 + ybar * by1 + zt * n1;
                 const T Pb2 = xbar * bx2 + ybar * by2 + zt * n2;
-                T cq[3];
-                const T dv = offset_grad_from_d0<T>(mm[0], mm[1], mm[2], T(p), D, cq);   // 1/A, centroid for m
-                const T Dbar = Pb0 * mm[0] + Pb1 * mm[1] + Pb2 * mm[2];
+                const T Dbar = Pb0 * mq[0] + Pb1 * mq[1] + Pb2 * mq[2];
                 const T mb0 = D * Pb0 + Dbar * cq[0], mb1 = D * Pb1 + Dbar * cq[1], mb2 = D * Pb2 + Dbar * cq[2];
-                (sl == 0 ? phia : phibb) = Dbar * dv;
+                L.pb[cell][q] = Dbar * dv;
                 arow[0] += F(xbar * P0); arow[1] += F(xbar * P1); arow[2] += F(xbar * P2);
                 arow[3] += F(ybar * P0); arow[4] += F(ybar * P1); arow[5] += F(ybar * P2);
-                // n enters through z = P.n, through -D0 n in P, and as m where the slot keeps it
+                // n enters through z = P.n, through -D0 n in P, and as m where the neighbour keeps it
                 arow[6] += F(zt * P0 - D0 * Pb0 + (own ? T(0) : mb0));
                 arow[7] += F(zt * P1 - D0 * Pb1 + (own ? T(0) : mb1));
                 arow[8] += F(zt * P2 - D0 * Pb2 + (own ? T(0) : mb2));
                 arow[9] += F(zt);
-                if (own) {                                   // m = -h / |h|: the adjoint of h
-                    const T ih = sl == 0 ? iha : ihb;
-                    const T md = mm[0] * mb0 + mm[1] * mb1 + mm[2] * mb2;
-                    T(&hb)[3] = sl == 0 ? hba : hbb;
-                    hb[0] = -(mb0 - mm[0] * md) * ih;
-                    hb[1] = -(mb1 - mm[1] * md) * ih;
-                    hb[2] = -(mb2 - mm[2] * md) * ih;
-                }
+                // m = -h / |h|: the adjoint of h, gathered later at that neighbour
+                // and spread over its 3^3 by the gradient's weights
+                const T md = mq[0] * mb0 + mq[1] * mb1 + mq[2] * mb2;
+                float* o = outh + 3 * (q < 13 ? q : q - 1);
+                o[0] = own ? float(-(mb0 - mq[0] * md) * ih) : 0.0f;
+                o[1] = own ? float(-(mb1 - mq[1] * md) * ih) : 0.0f;
+                o[2] = own ? float(-(mb2 - mq[2] * md) * ih) : 0.0f;
             } else {
-                T cq[3];
-                const T dv = offset_grad_from_d0<T>(n0, n1, n2, T(p), D, cq);   // 1/A, centroid
-                (sl == 0 ? phia : phibb) = zt * dv;
+                L.pb[cell][q] = zt * dv;
                 arow[0] += F(xbar * ex); arow[1] += F(xbar * ey); arow[2] += F(xbar * ez);
                 arow[3] += F(ybar * ex); arow[4] += F(ybar * ey); arow[5] += F(ybar * ez);
                 arow[6] += F(zt * (ex + cq[0])); arow[7] += F(zt * (ey + cq[1])); arow[8] += F(zt * (ez + cq[2]));
                 arow[9] += F(zt);
             }
         }
-        T dvc = T(0);
-        if (centre) {
-            T cc[3];
-            dvc = offset_grad_from_d0<T>(n0, n1, n2, T(pb), Db, cc);
-            L.res[21] = F(cc[0]); L.res[22] = F(cc[1]); L.res[23] = F(cc[2]);
-        }
-        F asum[10];
-        quad_colsum<F, 10, COLS>(L, j, arow, asum);   // its barriers also publish res[21..23]
-        const T c00 = T(L.res[21]), c01 = T(L.res[22]), c02 = T(L.res[23]);
-        const T sbx0 = T(asum[0]), sbx1 = T(asum[1]), sbx2 = T(asum[2]);
-        const T sz_ = T(asum[9]);
+        __syncwarp();
+        T asum[10];
+#pragma unroll
+        for (int i = 0; i < 10; ++i) asum[i] = T(group_sum(arow[i]));
+        const T c00 = L.cen[cell][0], c01 = L.cen[cell][1], c02 = L.cen[cell][2], dvc = L.cen[cell][3];
+        const T sbx0 = asum[0], sbx1 = asum[1], sbx2 = asum[2], sz_ = asum[9];
         // the centre offset D0 enters every z with a minus sign
-        T nb0 = T(asum[6]) - sz_ * c00, nb1 = T(asum[7]) - sz_ * c01, nb2 = T(asum[8]) - sz_ * c02;
+        T nb0 = asum[6] - sz_ * c00, nb1 = asum[7] - sz_ * c01, nb2 = asum[8] - sz_ * c02;
         // b_x = b_y x n
-        const T yb0 = T(asum[3]) + (n1 * sbx2 - n2 * sbx1);
-        const T yb1 = T(asum[4]) + (n2 * sbx0 - n0 * sbx2);
-        const T yb2 = T(asum[5]) + (n0 * sbx1 - n1 * sbx0);
+        const T yb0 = asum[3] + (n1 * sbx2 - n2 * sbx1);
+        const T yb1 = asum[4] + (n2 * sbx0 - n0 * sbx2);
+        const T yb2 = asum[5] + (n0 * sbx1 - n1 * sbx0);
         nb0 += sbx1 * by2 - sbx2 * by1;
         nb1 += sbx2 * by0 - sbx0 * by2;
         nb2 += sbx0 * by1 - sbx1 * by0;
@@ -489,26 +481,24 @@ __device__ __forceinline__ float quad_cell(const float* __restrict__ s, int c, i
         // n = -g / |g|
         const T nd = n0 * nb0 + n1 * nb1 + n2 * nb2;
         const T gb0 = -(nb0 - n0 * nd) * ign, gb1 = -(nb1 - n1 * nd) * ign, gb2 = -(nb2 - n2 * nd) * ign;
-        {
-            const T ex = T(q_dx(qa)), ey = T(q_dy(qa)), ez = T(q_dz(qa));
-            const int e2 = q_dx(qa) * q_dx(qa) + q_dy(qa) * q_dy(qa) + q_dz(qa) * q_dz(qa);
-            out[qa] = float(phia + T(nrm_weight<NRM>(e2)) * (ex * gb0 + ey * gb1 + ez * gb2));
-        }
-        if (nbb) {
-            const T ex = T(q_dx(qb)), ey = T(q_dy(qb)), ez = T(q_dz(qb));
-            const int e2 = q_dx(qb) * q_dx(qb) + q_dy(qb) * q_dy(qb) + q_dz(qb) * q_dz(qb);
-            out[qb] = float(phibb + T(nrm_weight<NRM>(e2)) * (ex * gb0 + ey * gb1 + ez * gb2));
-        }
-        if (centre) out[13] = float(-sz_ * dvc);
-        if constexpr (NBR) {
-            // the adjoints of the slots' own fill-level gradients, gathered later at
-            // those neighbours and spread over their 3^3 by the gradient's weights
-            out[27 + 3 * j] = float(hba[0]); out[28 + 3 * j] = float(hba[1]); out[29 + 3 * j] = float(hba[2]);
-            if (nbb) {
-                out[27 + 3 * sb] = float(hbb[0]); out[28 + 3 * sb] = float(hbb[1]); out[29 + 3 * sb] = float(hbb[2]);
+#pragma unroll
+        for (int kk = 0; kk < kRounds; ++kk) {
+            const int q = j + kk * kLanes;
+            if (q < 27) {
+                const int dx = q_dx(q), dy = q_dy(q), dz = q_dz(q), e2 = dx * dx + dy * dy + dz * dz;
+                const bool on = (mask >> q) & 1u;
+                const T ph = on ? L.pb[cell][q] : T(0);
+                const float v = float(ph + T(nrm_weight<NRM>(e2)) * (T(dx) * gb0 + T(dy) * gb1 + T(dz) * gb2));
+                out[static_cast<unsigned>(q) * ostride] = q == 13 ? float(-sz_ * dvc) : v;
+                if constexpr (NBR) {
+                    if (!on && q != 13) {
+                        float* o = outh + 3 * (q < 13 ? q : q - 1);
+                        o[0] = 0.0f; o[1] = 0.0f; o[2] = 0.0f;
+                    }
+                }
             }
         }
-        __syncwarp();                              // res is reused by the next cell
+        __syncwarp();                              // L is reused by the next cell
     }
     return kappa;
 }
@@ -579,7 +569,9 @@ __device__ __forceinline__ int ordered_compact(int n, Pred pred, unsigned short*
 //   tiles     ntiles      backward gather tiles
 //   over      ntiles      row-prefix block totals, then the gather tiles with a
 //                         source cell without a stored row
-//   contrib   the rest:   27 floats per row (backward contributions)
+//   contrib   the rest:   27 floats per row (backward contributions), entry q
+//             of every row together (index q * rows + row): the gather's lanes
+//             read entry q of neighbouring cells' rows at once
 // The fixed part (everything but contrib) is 784 bytes per tile.  The
 // backward stores the 27 contributions of an interface cell in row
 // cbase[tile] + rank when that row fits; cells beyond the capacity are
@@ -594,15 +586,16 @@ constexpr size_t kRowBytes = 27 * sizeof(float);
 constexpr size_t kDefaultRowsPerTile = 16;    // contribution rows budgeted per tile by default
 // rows are 32-bit indices: first rows saturate at kRowCap, so that a first
 // row plus a rank (< kTile) never wraps and a saturated tile recomputes; the
-// capacity is at most kRowLimit rows, so an entry's index row * 27 + q stays
+// capacity is at most kRowLimit rows, so an entry's index q * rows + row stays
 // below 2^30 (a 32-bit byte offset from the store's base)
 constexpr unsigned kRowCap = 0xF0000000u;
 constexpr unsigned kRowLimit = (1u << 30) / 27u;
 // The neighbour-normal variant's backward: a row holds the 27 contributions
 // and, per neighbour, the adjoint of that neighbour's own fill-level gradient
-// (26 x 3), followed in the workspace by one 3-vector per row, the sum of
-// those adjoints at the row's cell
-constexpr int kRowFloatsNbr = 27 + 26 * 3;
+// (26 x 3, together, after the contributions of all rows), followed in the
+// workspace by one 3-vector per row, the sum of those adjoints at the row's cell
+constexpr int kRowFloatsH = 26 * 3;
+constexpr int kRowFloatsNbr = 27 + kRowFloatsH;
 constexpr size_t kRowBytesNbr = (kRowFloatsNbr + 3) * sizeof(float);
 constexpr unsigned kRowLimitNbr = (1u << 30) / kRowFloatsNbr;
 // budgeted per tile by default: without a fallback a missing row is NaN, so
@@ -850,13 +843,10 @@ __global__ __launch_bounds__(kThreads) void k_curv_prefix(Workspace ws, int ntil
 
 // ---------------------------------------------------------------------------
 // 2. work items: up to kPartCells interface cells of a tile, each cell on a
-// group of 16 lanes (k_curv_quads; the neighbour-normal variant stages each
-// cell's 5x5x5 neighbourhood, for each neighbour's own 3x3x3).  The group
-// finds its cell, the i-th interface cell of the tile in cell order, from the
-// tile's bitmask and prefix counts (two ballots), stages the cell's fill
-// levels in LDS, and runs the cell.  Groups never wait for each other: no
-// block barrier.  Forward: kappa.  Backward: the cell's contributions
-// gk * d kappa / d phi_q into its contribution row (when it fits).
+// group of 4 lanes (k_curv_quads; the neighbour-normal variant stages each
+// cell's 5x5x5 neighbourhood, for each neighbour's own 3x3x3).  Forward:
+// kappa.  Backward: the cell's contributions gk * d kappa / d phi_q into its
+// contribution row (when it fits).
 // ---------------------------------------------------------------------------
 
 // Lattice position of the interface cell of rank i (in cell order) of a
@@ -891,89 +881,95 @@ __device__ __forceinline__ int thread_index_per_iteration() {
     return t;
 }
 
-// The curvature without neighbour normals on groups of 16 lanes: a workgroup
-// takes two work items at a time (its first two waves the first, the last two
-// the second), each 32-lane half of a wave finds its two cells from the tile's
-// bitmask, and each group of 16 stages its cell's 3x3x3 fill levels and runs
-// quad_cell; the forward writes kappa, the backward (ADJ) the cell's
+// Workgroups of one wavefront: each 32-lane half takes a work item (8 cells of
+// a tile, 4 lanes each).  A group finds its cell, the i-th interface cell of
+// the tile in cell order, by a binary search over the tile's prefix counts and
+// one over the bits of the mask word found, stages the cell's fill levels and
+// runs curv_cell.  The forward writes kappa, the backward (ADJ) the cell's
 // contribution row when it fits the workspace.
-// waves per SIMD, the most that compile without spilling: the forward 8
-// (FP64: 4); the adjoint, which keeps two points' state per lane, 4 in FP32
-// and mixed precision (3 with neighbour normals), in FP64 3 for the iterative
-// solvers and 2 for the trigonometric ones and with neighbour normals
-template <int SOLVER, class T, class U, bool ADJ, bool NBR>
-constexpr int quad_waves() {
-    if (!ADJ) return sizeof(T) == 4 ? 8 : 4;
-    if (sizeof(U) == 4) return 4;                            // FP32
-    if (sizeof(T) == 4) return NBR ? 3 : 4;                  // mixed
-    return (!NBR && (SOLVER == kNewton || SOLVER == kNested)) ? 3 : 2;   // FP64
+template <class T, class U, bool ADJ, bool NBR>
+constexpr int cell_waves() {
+    if (!ADJ) return sizeof(T) == 4 ? 4 : 2;
+    return sizeof(T) == 4 ? 3 : 2;
 }
 
 template <int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR>
-__global__ __launch_bounds__(kThreads, (quad_waves<SOLVER, T, U, ADJ, NBR>())) void k_curv_quads(const float* __restrict__ phi,
-                                                                                   const float* __restrict__ gkap,
-                                                                                   float* __restrict__ kappa,
-                                                                                   Workspace ws, int X, int Y, int Z,
-                                                                                   int ntx, int nty) {
-    constexpr int COLS = 10;                                 // 2 passes; 25 KiB of LDS with an FP64 fit
+__global__ __launch_bounds__(64, (cell_waves<T, U, ADJ, NBR>())) void k_curv_quads(
+    const float* __restrict__ phi, const float* __restrict__ gkap, float* __restrict__ kappa, Workspace ws, int X,
+    int Y, int Z, int ntx, int nty) {
     // the cell's 3x3x3 fill levels (5x5x5 with neighbour normals)
     constexpr int H = NBR ? 2 : 1, W = 2 * H + 1, NB = W * W * W, C = (H * W + H) * W + H;
-    __shared__ float nbh[kQuads][NB];
-    __shared__ QuadLds<F, COLS> qlds[kQuads];
+    __shared__ float nbh[kWaveCells][NB];
+    __shared__ CellLds<T, ADJ> lds;
     const unsigned nitems = *static_cast<volatile unsigned*>(ws.counter);
     const unsigned npairs = (nitems + 1u) / 2u;
     for (unsigned pr = blockIdx.x; pr < npairs; pr += gridDim.x) {
-        const int tid = thread_index_per_iteration(), grp = tid / kQuad, j = tid % kQuad;
-        const int lane = tid & 63, l32 = tid & 31, half = tid & 32;
-        const unsigned item = 2u * pr + (tid >= kThreads / 2 ? 1u : 0u);
-        if (item >= nitems) continue;                        // uniform per pair of waves
+        const int lane = thread_index_per_iteration(), l32 = lane & 31, cell = lane / kLanes, j = lane % kLanes;
+        const unsigned item = 2u * pr + static_cast<unsigned>(lane >> 5);
+        if (item >= nitems) continue;                        // uniform per half
         const unsigned e = ws.items[item];
         const int tile = static_cast<int>(e >> 7), part = static_cast<int>(e & 127u);
-        // the two ranks of this half-wave's groups among the tile's interface cells
         const unsigned mw = ws.mask[tile * kWords + l32], pw = ws.prefix[tile * kWords + l32];
         const unsigned n = __shfl(pw + __popc(mw), kWords - 1, 32);
-        const unsigned i0 = static_cast<unsigned>(part * kPartCells + (grp % 8) / 2 * 2);
-        int cl[2];
+        const unsigned ic = static_cast<unsigned>(part * kPartCells + cell % kPartCells);
+        const unsigned ui = ic < n ? ic : n - 1u;            // n >= 1: the tile has an item
+        int w = 0;                                           // the last word with prefix <= ui
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const unsigned ui = i0 + r < n ? i0 + r : n - 1u;    // n >= 1: the tile has an item
-            const unsigned in_word = static_cast<unsigned>(__ballot(pw <= ui && ui < pw + __popc(mw)) >> half);
-            const int w = __ffs(static_cast<int>(in_word)) - 1;
-            const unsigned word = __shfl(mw, w, 32);
-            const unsigned k = ui - __shfl(pw, w, 32);
-            const bool hit = ((word >> l32) & 1u) && static_cast<unsigned>(__popc(word & ((1u << l32) - 1u))) == k;
-            const int b = __ffs(static_cast<int>(static_cast<unsigned>(__ballot(hit) >> half))) - 1;
-            cl[r] = w * 32 + b;
+        for (int st = kWords / 2; st; st >>= 1) w += __shfl(pw, w + st, 32) <= ui ? st : 0;
+        unsigned word = __shfl(mw, w, 32);
+        int k = static_cast<int>(ui - __shfl(pw, w, 32)), bit = 0;
+#pragma unroll
+        for (int st = 16; st; st >>= 1) {
+            const int low = __popc(word & ((1u << st) - 1u));
+            const bool up = k >= low;
+            k -= up ? low : 0;
+            bit += up ? st : 0;
+            word >>= up ? st : 0;
         }
-        const unsigned ic = i0 + (grp & 1);
         if (ic >= n) continue;                               // uniform per group
         unsigned row = 0u;
         if constexpr (ADJ) {
             row = ws.cbase[tile] + ic;
             if (row >= ws.rows) continue;                    // uniform per group; the gather recomputes
         }
-        const int c = (grp & 1) ? cl[1] : cl[0];
-        const int x0 = (tile % ntx) * TX, y0 = ((tile / ntx) % nty) * TY, z0 = (tile / (ntx * nty)) * TZ;
-        const int gx = x0 + c % TX, gy = y0 + (c / TX) % TY, gz = z0 + c / (TX * TY);
-        for (int t = j; t < NB; t += kQuad) {
-            const int ax = gx + t % W - H, ay = gy + (t / W) % W - H, az = gz + t / (W * W) - H;
-            nbh[grp][t] = (ax >= 0 && ax < X && ay >= 0 && ay < Y && az >= 0 && az < Z)
-                              ? phi[(static_cast<int64_t>(az) * Y + ay) * X + ax] : 0.0f;
+        const int cl = w * 32 + bit;
+        const int gx = (tile % ntx) * TX + cl % TX, gy = ((tile / ntx) % nty) * TY + (cl / TX) % TY,
+                  gz = (tile / (ntx * nty)) * TZ + cl / (TX * TY);
+        if constexpr (NBR) {
+            for (int t = j; t < NB; t += kLanes) {
+                const int ax = gx + t % W - H, ay = gy + (t / W) % W - H, az = gz + t / (W * W) - H;
+                nbh[cell][t] = (ax >= 0 && ax < X && ay >= 0 && ay < Y && az >= 0 && az < Z)
+                                   ? phi[(static_cast<int64_t>(az) * Y + ay) * X + ax] : 0.0f;
+            }
+        } else {
+            // 9 rows of 3 consecutive levels, all in the lattice (an interface
+            // cell lies off the outer layer)
+            float v[3][3];
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                const int r = min(j + u * kLanes, 8);
+                const float* p = phi + (static_cast<int64_t>(gz + r / 3 - 1) * Y + (gy + r % 3 - 1)) * X + (gx - 1);
+                v[u][0] = p[0]; v[u][1] = p[1]; v[u][2] = p[2];
+            }
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                const int r = j + u * kLanes;
+                if (r < 9) { nbh[cell][3 * r] = v[u][0]; nbh[cell][3 * r + 1] = v[u][1]; nbh[cell][3 * r + 2] = v[u][2]; }
+            }
         }
         __syncwarp();
         const int64_t gi = (static_cast<int64_t>(gz) * Y + gy) * X + gx;
         if constexpr (ADJ) {
-            constexpr int ROWF = NBR ? kRowFloatsNbr : 27;
-            quad_cell<SOLVER, T, U, F, true, NRM, COLS, NBR>(nbh[grp], C, W, W * W, j, lane, gkap[gi],
-                                                             ws.contrib + static_cast<size_t>(row) * ROWF, qlds[grp],
-                                                             gx, gy, gz, X, Y, Z);
+            curv_cell<SOLVER, T, U, F, true, NRM, NBR>(
+                nbh[cell], C, W, W * W, lane, gkap[gi], ws.contrib + row, ws.rows,
+                NBR ? ws.contrib + 27u * ws.rows + static_cast<size_t>(row) * kRowFloatsH : nullptr, lds, gx, gy, gz,
+                X, Y, Z);
         } else {
-            const float kv = quad_cell<SOLVER, T, U, F, false, NRM, COLS, NBR>(nbh[grp], C, W, W * W, j, lane, 0.0f,
-                                                                               nullptr, qlds[grp], gx, gy, gz, X, Y,
-                                                                               Z);
+            const float kv = curv_cell<SOLVER, T, U, F, false, NRM, NBR>(nbh[cell], C, W, W * W, lane, 0.0f, nullptr,
+                                                                         0u, nullptr, lds, gx, gy, gz, X, Y, Z);
             if (j == 0) kappa[gi] = kv;
         }
-        __syncwarp();                                        // nbh and qlds reused by the next pair
+        __syncwarp();                                        // nbh and lds reused by the next pair
     }
 }
 
@@ -1017,8 +1013,8 @@ __global__ __launch_bounds__(kThreads) void k_curv_gather_fallback(const float* 
     __shared__ float contrib[kChunk][27];
     __shared__ unsigned crow[kChunk];
     __shared__ int wcount[kThreads / 64];
-    __shared__ QuadLds<F, 10> qlds[kQuads];
-    const int tid = threadIdx.x, grp = tid / kQuad, j = tid % kQuad;
+    __shared__ CellLds<T, true> lds;
+    const int tid = threadIdx.x;
     for (int i = tid; i < C_REGION; i += kThreads) slot[i] = kNoSlot;
     const unsigned ntl = *static_cast<volatile unsigned*>(ws.counter + 2);
     for (unsigned it = blockIdx.x; it < ntl; it += gridDim.x) {
@@ -1056,22 +1052,23 @@ __global__ __launch_bounds__(kThreads) void k_curv_gather_fallback(const float* 
                     const int i = min(idx, nv - 1) / 27;
                     const unsigned r = idx < nv ? crow[i] : ws.rows;
                     at[u] = r < ws.rows ? static_cast<unsigned>(idx) : 0xFFFFFFFFu;
-                    v[u] = r < ws.rows ? ws.contrib[static_cast<size_t>(r) * 27 + (idx - i * 27)] : 0.0f;
+                    v[u] = r < ws.rows ? ws.contrib[static_cast<unsigned>(idx - i * 27) * ws.rows + r] : 0.0f;
                 }
 #pragma unroll
                 for (int u = 0; u < kCopyBatch; ++u)
                     if (at[u] != 0xFFFFFFFFu) contrib[at[u] / 27][at[u] % 27] = v[u];
             }
             {
-                // rows that did not fit: recomputed, one group of lanes per cell
-                for (int i = grp; i < nc; i += kQuads) {
+                // rows that did not fit: recomputed by the first wavefront, one
+                // group of lanes per cell
+                for (int i = tid / kLanes; tid < 64 && i < nc; i += kWaveCells) {
                     if (crow[i] < ws.rows) continue;                     // uniform per group
                     const int ci = cand[c0 + i];
                     const int lx = ci % C_RX, ly = (ci / C_RX) % C_RY, lz = ci / (C_RX * C_RY);
                     const int gx = x0 - 1 + lx, gy = y0 - 1 + ly, gz = z0 - 1 + lz;
                     const float gk = gkap[(static_cast<int64_t>(gz) * Y + gy) * X + gx];
-                    quad_cell<SOLVER, T, U, F, true, NRM, 10>(s, ((lz + 1) * RY + (ly + 1)) * RX + (lx + 1), RX,
-                                                              RX * RY, j, tid & 63, gk, contrib[i], qlds[grp]);
+                    curv_cell<SOLVER, T, U, F, true, NRM>(s, ((lz + 1) * RY + (ly + 1)) * RX + (lx + 1), RX, RX * RY,
+                                                          tid, gk, contrib[i], 1u, nullptr, lds);
                 }
             }
             __syncthreads();
@@ -1140,7 +1137,7 @@ __global__ __launch_bounds__(kThreads) void k_curv_hgather(Workspace ws, int X, 
         const bool miss = ((__ballot(src && !stored) >> half) & 0xffffffffull) != 0ull;
         float h0 = 0.0f, h1 = 0.0f, h2 = 0.0f;
         if (stored) {
-            const float* p = ws.contrib + static_cast<size_t>(r) * kRowFloatsNbr + 27 + 3 * j;
+            const float* p = ws.contrib + 27u * ws.rows + static_cast<size_t>(r) * kRowFloatsH + 3 * j;
             h0 = p[0];
             h1 = p[1];
             h2 = p[2];
@@ -1244,7 +1241,6 @@ template <bool NBR, int NRM, bool ZFILL>
 __global__ __launch_bounds__(kThreads, (NBR ? 5 : 8)) void k_curv_gather_direct(float* __restrict__ gphi, Workspace ws, int X,
                                                                   int Y, int Z, int ntx, int nty, int ntz,
                                                                   bool vec, unsigned ngather) {
-    constexpr unsigned ROWF = NBR ? kRowFloatsNbr : 27;
     __shared__ SourceMap m;
     __shared__ unsigned short band[kTile];
     __shared__ unsigned long long brow[TY * TZ];
@@ -1377,7 +1373,7 @@ __global__ __launch_bounds__(kThreads, (NBR ? 5 : 8)) void k_curv_gather_direct(
                             miss |= src && !stored;
                             has |= stored ? (1u << qq) : 0u;
                             const unsigned rr = stored ? r : 0u;  // rows >= 1: row 0 read and masked out
-                            v[qq] = ws.contrib[rr * ROWF + static_cast<unsigned>(q0 + qq)];
+                            v[qq] = ws.contrib[static_cast<unsigned>(q0 + qq) * ws.rows + rr];
                             hv[qq][0] = ws.hbar[3u * rr];
                             hv[qq][1] = ws.hbar[3u * rr + 1u];
                             hv[qq][2] = ws.hbar[3u * rr + 2u];
@@ -1434,7 +1430,7 @@ __global__ __launch_bounds__(kThreads, (NBR ? 5 : 8)) void k_curv_gather_direct(
                         miss |= src && !stored;
                         has |= stored ? (1u << qq) : 0u;
                         // a non-source reads entry q of row 0 (rows >= 1 here) and is masked out
-                        v[qq] = ws.contrib[(stored ? r : 0u) * 27u + static_cast<unsigned>(q0 + qq)];
+                        v[qq] = ws.contrib[static_cast<unsigned>(q0 + qq) * ws.rows + (stored ? r : 0u)];
                     }
 #pragma unroll
                     for (int qq = 0; qq < 9; ++qq) a += (has >> qq) & 1u ? v[qq] : 0.0f;
@@ -1533,9 +1529,10 @@ void launch_rows(Workspace ws, const Grid& g, hipStream_t st) {
 }
 
 template <int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR = false>
-void launch_quads(const float* phi, const float* gk, float* kappa, Workspace ws, int X, int Y, int Z, const Grid& g,
+void launch_cells(const float* phi, const float* gk, float* kappa, Workspace ws, int X, int Y, int Z, const Grid& g,
                   hipStream_t st) {
-    const dim3 grid(persistent_grid(static_cast<int64_t>(g.ntiles) * kMaxParts)), block(kThreads);
+    const int64_t most = static_cast<int64_t>(g.ntiles) * (kMaxParts / 2);
+    const dim3 grid(static_cast<unsigned>(most < kCellBlocks ? most : kCellBlocks)), block(64);
     hipLaunchKernelGGL((k_curv_quads<SOLVER, T, U, F, ADJ, NRM, NBR>), grid, block, 0, st, phi, gk, kappa, ws, X, Y, Z,
                        g.ntx, g.nty);
 }
@@ -1545,11 +1542,11 @@ template <int SOLVER, class T, class U, class F>
 void launch_fwd_t(int normal, bool nbr, const float* phi, float* kappa, Workspace ws, int X, int Y, int Z,
                   const Grid& g, hipStream_t st) {
     if (normal == kNormalCM) {
-        if (nbr) launch_quads<SOLVER, T, U, F, false, kNormalCM, true>(phi, nullptr, kappa, ws, X, Y, Z, g, st);
-        else launch_quads<SOLVER, T, U, F, false, kNormalCM>(phi, nullptr, kappa, ws, X, Y, Z, g, st);
+        if (nbr) launch_cells<SOLVER, T, U, F, false, kNormalCM, true>(phi, nullptr, kappa, ws, X, Y, Z, g, st);
+        else launch_cells<SOLVER, T, U, F, false, kNormalCM>(phi, nullptr, kappa, ws, X, Y, Z, g, st);
     } else {
-        if (nbr) launch_quads<SOLVER, T, U, F, false, kNormalPY, true>(phi, nullptr, kappa, ws, X, Y, Z, g, st);
-        else launch_quads<SOLVER, T, U, F, false, kNormalPY>(phi, nullptr, kappa, ws, X, Y, Z, g, st);
+        if (nbr) launch_cells<SOLVER, T, U, F, false, kNormalPY, true>(phi, nullptr, kappa, ws, X, Y, Z, g, st);
+        else launch_cells<SOLVER, T, U, F, false, kNormalPY>(phi, nullptr, kappa, ws, X, Y, Z, g, st);
     }
 }
 
@@ -1582,7 +1579,7 @@ template <int SOLVER, class T, class U, class F, int NRM>
 void launch_bwd_t(const float* phi, const float* gk, float* gp, Workspace ws, int X, int Y, int Z,
                   const Grid& g, bool zfill, hipStream_t st) {
     launch_rows(ws, g, st);
-    if (ws.rows > 0) launch_quads<SOLVER, T, U, F, true, NRM>(phi, gk, nullptr, ws, X, Y, Z, g, st);
+    if (ws.rows > 0) launch_cells<SOLVER, T, U, F, true, NRM>(phi, gk, nullptr, ws, X, Y, Z, g, st);
     launch_gather<false, 0>(gp, ws, X, Y, Z, g, zfill, st);
     // usually empty.  Its registers and LDS allow one workgroup per CU, so a
     // grid of one per CU (256) runs in a single round, cheap when nothing
@@ -1599,7 +1596,7 @@ template <int SOLVER, class T, class U, class F, int NRM>
 void launch_bwd_nbr_t(const float* phi, const float* gk, float* gp, Workspace ws, int X, int Y, int Z,
                       const Grid& g, bool zfill, hipStream_t st) {
     launch_rows(ws, g, st);
-    launch_quads<SOLVER, T, U, F, true, NRM, true>(phi, gk, nullptr, ws, X, Y, Z, g, st);
+    launch_cells<SOLVER, T, U, F, true, NRM, true>(phi, gk, nullptr, ws, X, Y, Z, g, st);
     hipLaunchKernelGGL(k_curv_hgather, dim3(persistent_grid(static_cast<int64_t>(g.ntiles) * kMaxParts)),
                        dim3(kThreads), 0, st, ws, X, Y, Z, g.ntx, g.nty);
     launch_gather<true, NRM>(gp, ws, X, Y, Z, g, zfill, st);
