@@ -203,9 +203,9 @@ PMC_DISPATCHES = {
     "offset_nested": ("k_offset<3, float, float, float, 4,",),
     "volume": ("k_volume<float, float, 4, false>",),
     "offset_backward_sz": ("k_offset_bwd<1, float, float, float, 4,",),
-    "curvature_fwd": ("k_curv_scan<true, true>", "k_curv_quads<0, float, double, double, false, 0, false>"),
-    "curvature_bwd": ("k_curv_scan<true, false>", "k_curv_quads<0, float, double, double, true, 0, false>",
-                      "k_curv_dilate", "k_curv_prefix", "k_curv_gather_direct",
+    "curvature_fwd": ("k_curv_scan<true,", "k_curv_quads<0, float, double, double, false, 0, false>"),
+    "curvature_bwd": ("k_curv_scan<false,", "k_curv_quads<0, float, double, double, true, 0, false>",
+                      "k_curv_rows", "k_curv_gather_direct",
                       "k_curv_gather_fallback<0, float, double, double, 0>"),
     "copy": ("__amd_rocclr_copyBuffer",),
 }
@@ -266,8 +266,7 @@ def write_traffic_profile(fetch_csv, write_csv, log2n, lattice, out=TRAFFIC_PROF
     ]
     for k, pats in PMC_DISPATCHES.items():
         # the dispatches of the launch that ran (the backward that reuses the
-        # forward's scan has none; lattices of at most 256 x 256 tiles run no
-        # second prefix pass)
+        # forward's scan has none)
         pats = tuple(p for p in pats if (k, p) in fetch and (k, p) in write)
         if not pats:
             continue
@@ -423,8 +422,7 @@ def write_trace_profile(trace_csv, out=None):
         "step's launches (2^26 problems: `k_offset` and `k_volume` at 16,777,216 work-items, `k_offset_bwd` "
         "at 16,777,216) are apart from the same kernels on other sizes (the differentiation workload's "
         "2^24 problems, the precision study).  One bench step launches every step kernel once (5 warm-up "
-        "+ 20 timed steps = 25 calls; the counter reset runs once for the forward and once for the "
-        "backward, the scan only for the forward: the step's backward reuses it).  The secondary timings after "
+        "+ 20 timed steps = 25 calls; the scan runs only for the forward: the step's backward reuses it).  The secondary timings after "
         "the timed steps (VALU "
         "probe `k_valu`, plane-sphere, Kawano's SZ, the FP64 solvers, the warm curvature and its variants, "
         "the 192^3 differentiation lattice, the paper-method benchmark `k_isolated`) appear with their own "
@@ -433,7 +431,7 @@ def write_trace_profile(trace_csv, out=None):
         "Template arguments: `k_offset<solver, storage, bulk, cubic, problems per lane, normals as rows>`, "
         "`k_curv_quads<solver, points, cubic, fit, backward, normal, neighbour normals>` (4 lanes per cell), "
         "`k_curv_gather_fallback<solver, points, cubic, fit, normal>`, "
-        "`k_curv_gather_direct<neighbour normals, normal, writes the zeros>`; solver 0 analytic, 1 optimized SZ, "
+        "`k_curv_scan<writes the zeros, wavefronts>`, `k_curv_gather_direct<neighbour normals, normal>`; solver 0 analytic, 1 optimized SZ, "
         "2 Newton-Raphson, 3 nested intervals, 4 Kawano's SZ; normal 0 Parker-Youngs.",
         "",
         "| kernel | work-items | calls | avg µs | min µs | share | VGPR | LDS B | scratch B |",

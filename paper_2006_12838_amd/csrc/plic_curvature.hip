@@ -2,26 +2,26 @@
 // Appendix B of Lehmann & Gekle, arXiv 2006.12838), forward and backward.
 //
 // Layout: phi, kappa, grad_kappa, grad_phi are X*Y*Z floats, x fastest.  The
-// lattice is cut into 64x4x4 tiles.  A call runs:
-//  1. a one-thread kernel that zeroes the work-list counters in the workspace
-//     (a kernel, not a memset, so the call can be captured in a graph);
-//  2. a streaming scan over the whole lattice (float4 loads and stores) that
-//     writes the zero result everywhere, records each tile's interface bitmask
-//     (0 < phi < 1, away from the outer layer) with its prefix counts, and
-//     lists one work item per 8 interface cells of each tile; the backward
-//     also records each tile's interface count;
-//  3. a persistent kernel over the work list in which each interface cell is
-//     computed by a group of 4 lanes: the group finds its cell from the
-//     bitmask, stages its neighbourhood in LDS, and its lanes share out the
+// lattice is cut into 64x4x4 tiles, the tiles into groups of 4 or 16 consecutive
+// ones (more where that would make over 8192 groups).  A forward is two launches:
+//  1. a streaming scan over the whole lattice, one workgroup per group, that
+//     writes the zero result everywhere and records each tile's interface
+//     bitmask (0 < phi < 1, away from the outer layer) with its prefix counts,
+//     and, per group, a list of work items (8 interface cells of a tile each);
+//  2. the work items, each interface cell on a group of 4 lanes: the wavefront
+//     finds its items through the groups' counts, a group finds its cell from
+//     the bitmask, stages its neighbourhood in LDS, and its lanes share out the
 //     interface neighbours (their PLIC offsets and rows of the normal
-//     equations).  Sums over the neighbours are formed in a fixed order, so
-//     results are bitwise reproducible.
-// The backward first assigns contribution rows by a prefix over the tiles'
-// interface counts in tile order and lists the tiles next to the interface;
-// the work items store each interface cell's 27 contributions in its row; a
-// direct gather sums, for every cell next to the interface, its sources' rows
-// in a fixed order; a fallback gather handles the tiles with a source whose
-// row did not fit the workspace, recomputing those rows.
+//     equations).  One workgroup turns the groups' cell counts into first rows
+//     for a later backward.
+// Sums over the neighbours are formed in a fixed order, so results are bitwise
+// reproducible.  No launch needs a cleared counter: nothing is reset first.
+// The backward (after the same scan, or reusing its forward's records) stores
+// each interface cell's 27 contributions in its row, rows in tile order; a
+// direct gather, one workgroup per tile, sums for every cell next to the
+// interface its sources' rows in a fixed order (tiles away from the interface
+// get their zeros beside the work items); a fallback gather handles the tiles with a source whose row did not fit the
+// workspace, recomputing those rows.
 // The interface is one cell thick (about 0.2 % of a 256^3 sphere lattice), so
 // the scan carries the HBM traffic and the list kernels the arithmetic.
 //
@@ -34,6 +34,7 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 #include <unordered_map>
 #include <vector>
 
@@ -47,10 +48,15 @@ constexpr int TX = 64, TY = 4, TZ = 4;       // tile
 constexpr int kTile = TX * TY * TZ;           // 1024 cells
 constexpr int kThreads = 256;                 // 4 wave64
 constexpr int kCellsPerThread = kTile / kThreads;
-constexpr int kGroup = 32;                    // lanes per interface cell
-constexpr int kGroups = kThreads / kGroup;    // 8 cells in flight per workgroup
+constexpr int kGroup = 32;                    // lanes per interface cell of the gradient adjoints' gather
 constexpr int kPersistentBlocks = 2048;
 constexpr int kCellBlocks = 4096;             // wavefronts of the cell kernels: 4 per SIMD
+constexpr int kGatherBlocks = 1792;           // workgroups of the direct gather: 7 per CU, all it holds
+// wavefronts of a scanning workgroup, one tile each: 16, or 4 on lattices whose
+// scan is no more than its latency (48 x 44 x 37: 5 us, against 8.5 with 16 on 7 CUs)
+constexpr int kScanWaves = 16, kFewScanWaves = 4, kFewTiles = 4096;
+constexpr int scan_waves(int ntiles) { return ntiles > kFewTiles ? kScanWaves : kFewScanWaves; }
+constexpr int kMaxGroups = 8192;              // groups of tiles: 128 per lane of a wavefront that looks for items
 constexpr int kFallbackBlocks = 256;            // one per CU of an MI355X
 
 // fixed auxiliary vector r of Sec. 4.2 (non-collinear with the normal)
@@ -72,21 +78,27 @@ __device__ __forceinline__ bool is_iface(float p) { return p > 0.0f && p < 1.0f;
 // (the fit and, in the backward, its adjoint) multiply instead of divide.
 // Only the leading N = min(5, #points) parameters are fitted (reduced
 // dimension, the rest stay 0); a pivot below pivot_rel times the largest
-// diagonal entry of the leading block drops its parameter.
+// diagonal entry of the leading block drops its parameter.  True when every
+// pivot is at least kSteady of that entry: rounding of M is then not enlarged
+// by more than about 1 / kSteady (to 1e-11 in FP64, 1e-5 in FP32).
 // ---------------------------------------------------------------------------
+template <class F> constexpr F kSteady = sizeof(F) == 8 ? F(1e-5) : F(0.0078125);
+
 template <class F>
-__device__ __forceinline__ void ldlt_factor(F (&m)[5][5], int N, bool (&act)[5], F (&dinv)[5]) {
+__device__ __forceinline__ bool ldlt_factor(F (&m)[5][5], int N, bool (&act)[5], F (&dinv)[5]) {
     F maxd = F(0);
 #pragma unroll
     for (int j = 0; j < 5; ++j)
         if (j < N) maxd = M<F>::fmax(maxd, m[j][j]);
     const F tol = M<F>::pivot_rel * maxd;
+    bool steady = true;
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
         F dj = m[j][j];
 #pragma unroll
         for (int k = 0; k < j; ++k) dj -= m[j][k] * m[j][k] * m[k][k];
         act[j] = (j < N) && (dj > tol) && (maxd > F(0));
+        steady = steady && (j >= N || dj >= kSteady<F> * maxd);
         const F inv = act[j] ? F(1) / dj : F(0);
         m[j][j] = act[j] ? dj : F(0);
         dinv[j] = inv;
@@ -98,6 +110,7 @@ __device__ __forceinline__ void ldlt_factor(F (&m)[5][5], int N, bool (&act)[5],
             m[i][j] = sij * inv;
         }
     }
+    return steady;
 }
 
 template <class F>
@@ -129,6 +142,16 @@ __device__ __forceinline__ F kappa_of(const F (&a)[5]) {
     return -(A * (I * I + F(1)) + B * (H * H + F(1)) - C * H * I) / (w * M<F>::sqrt(w));
 }
 
+// a value through an opaque move: what a loop derives from it is then
+// recomputed in every iteration (a few ALU instructions) instead of being kept
+// in registers across the loop, where it would spill
+__device__ __forceinline__ int opaque(int v) {
+    int t;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"(v));
+    return t;
+}
+__device__ __forceinline__ int thread_index_per_iteration() { return opaque(static_cast<int>(threadIdx.x)); }
+
 // lower-triangle index of the 5x5 normal matrix
 __host__ __device__ constexpr int tri(int i, int k) { return i * (i + 1) / 2 + k; }
 
@@ -155,36 +178,52 @@ __device__ __forceinline__ void gradient27(const float* __restrict__ s, int c, i
 }
 
 // ---------------------------------------------------------------------------
-// One interface cell on a group of kLanes = 4 lanes, sixteen cells per
-// wavefront.  About ten of a cell's 26 neighbours are interface cells, and only
-// those have a point: the group lists them (the centre among them) by a
-// bitmask, and lane j takes the list's entries j, j + 4, ...  So the lanes that
-// solve a PLIC problem are nearly always full, where one lane per slot of the
-// 3x3x3 leaves six of ten idle; and what is computed once per cell (normal,
-// frame, LDL^T, kappa) is repeated on 4 lanes instead of 16.  The fit's sums
-// run over the entries of each lane in list order and then over the group by
-// two quad permutations, always in the same order, so every call gives the
-// same bits.  Bound by instruction issue and the latency of its chains: with 16
-// lanes per cell, two slots each, a spray of 24 drops (512 x 384 x 384, mixed
-// precision) took 183 us forward and 308 us adjoint, the 256^3 sphere 16.4 us
-// forward; with 4 lanes 96, 158 and 11.8 us.
+// One interface cell on a group of kLanes = 4 lanes.  About ten of a cell's
+// 26 neighbours are interface cells, and only those have a point: the group
+// lists them (the centre among them) by a bitmask, and lane j takes the list's
+// entries j, j + kLanes, ...  So the lanes that solve a PLIC problem are nearly
+// always full, where one lane per slot of the 3x3x3 leaves six of ten idle; and
+// what is computed once per cell (normal, frame, LDL^T, kappa) is repeated on
+// few lanes.  The fit's sums run over the entries of each lane in list order
+// and then over the group by lane permutations, always in the same order, so
+// every call gives the same bits.  Bound by instruction issue and the latency
+// of its chains: with 16 lanes per cell, two slots each, a spray of 24 drops
+// (512 x 384 x 384, mixed precision) took 183 us forward and 308 us adjoint,
+// the 256^3 sphere 16.4 us forward; with 4 lanes 90, 175 and 15 us.
+// An ill-conditioned fit shows the rounding of its sums in its result, many
+// times enlarged.  Where a pivot falls below kSteady of the largest diagonal
+// entry, the sums are formed again over the 16 pairs of neighbours (l, l + 16)
+// of the 26 in order, so that they do not depend on how the lanes shared out
+// the list (one such cell moved by 5e-5 of the spray's whole gradient).
 // ---------------------------------------------------------------------------
+constexpr int kRowFloatsH = 26 * 3;             // a cell's adjoints of its neighbours' own gradients
+constexpr unsigned kCentre = 1u << 13;
 constexpr int kLanes = 4;                       // lanes per interface cell
 constexpr int kWaveCells = 64 / kLanes;         // cells of a wavefront
 constexpr int kRounds = (27 + kLanes - 1) / kLanes;
-constexpr unsigned kCentre = 1u << 13;
 
-// scratch of one wavefront: the offsets of each lane's entries by round; with
-// ADJ, the gradients of the points' fill levels by neighbour, and the centre's
+// scratch of one wavefront: the offsets of each lane's entries by round; the
+// neighbour offsets (x, y, z) with their weights in the gradient (taken apart
+// from q each time, they were a twelfth of the instructions); with ADJ, the gradients of the points' fill levels by neighbour, and the centre's
 // own derivatives
 template <class T, bool ADJ> struct CellLds {
     T D[kRounds][64];
+    float4 e[27];
 };
 template <class T> struct CellLds<T, true> {
     T D[kRounds][64];
+    float4 e[27];
     T pb[kWaveCells][27];
     T cen[kWaveCells][4];
 };
+
+template <int NRM, class Lds> __device__ __forceinline__ void init_cells(Lds& L, int lane) {
+    if (lane < 27) {
+        const int dx = q_dx(lane), dy = q_dy(lane), dz = q_dz(lane);
+        L.e[lane] = make_float4(dx, dy, dz, nrm_weight<NRM>(dx * dx + dy * dy + dz * dz));
+    }
+    __syncwarp();
+}
 
 template <int CTRL> __device__ __forceinline__ float quad_move(float x) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
@@ -196,12 +235,33 @@ template <int CTRL> __device__ __forceinline__ double quad_move(double x) {
 template <int CTRL> __device__ __forceinline__ unsigned quad_move(unsigned x) {
     return static_cast<unsigned>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), CTRL, 0xF, 0xF, true));
 }
-constexpr int kSwap1 = 0xB1, kSwap2 = 0x4E;     // quad_perm [1,0,3,2] and [2,3,0,1]
+// quad_perm [1,0,3,2] and [2,3,0,1]; lane i of 8 to lane 7 - i
+constexpr int kSwap1 = 0xB1, kSwap2 = 0x4E, kHalfMirror = 0x141;
 
 // sum over the 4 lanes of the group, the same bits on each
 template <class F> __device__ __forceinline__ F group_sum(F x) {
     x += quad_move<kSwap1>(x);
     return x + quad_move<kSwap2>(x);
+}
+
+// inclusive sums over the lanes below, in each half of the wavefront or all of
+// it, by row shifts and row broadcasts (every lane active); through LDS
+// (__shfl_up) a step of these costs about a hundred cycles of latency
+template <int CTRL, int ROWS> __device__ __forceinline__ unsigned scan_step(unsigned x) {
+    return x + static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ unsigned half_scan(unsigned x) {
+    x = scan_step<0x111, 0xF>(x);                 // row_shr 1, 2, 4, 8
+    x = scan_step<0x112, 0xF>(x);
+    x = scan_step<0x114, 0xF>(x);
+    x = scan_step<0x118, 0xF>(x);
+    return scan_step<0x142, 0xA>(x);              // row_bcast 15 into rows 1 and 3
+}
+__device__ __forceinline__ unsigned wave_scan(unsigned x) {
+    return scan_step<0x143, 0xC>(half_scan(x));   // row_bcast 31 into rows 2 and 3
+}
+__device__ __forceinline__ unsigned from_lane(unsigned x, int lane) {   // lane: the same on every lane
+    return static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(x), lane));
 }
 
 // the list's entries of lane j (the first is the lowest set bit), and the next
@@ -218,24 +278,30 @@ __device__ __forceinline__ unsigned next_entries(unsigned list) {
 
 // neighbour q's point (x, y in the frame, z along n), centre normal
 template <class T, class F>
-__device__ __forceinline__ void cell_point(int q, T D, T D0, T bx0, T bx1, T bx2, T by0, T by1, T by2,
+__device__ __forceinline__ void cell_point(const float4& e, T D, T D0, T bx0, T bx1, T bx2, T by0, T by1, T by2,
                                            T n0, T n1, T n2, F& x, F& y, F& z) {
-    const T ex = T(q_dx(q)), ey = T(q_dy(q)), ez = T(q_dz(q));
+    const T ex = T(e.x), ey = T(e.y), ez = T(e.z);
     x = F(ex * bx0 + ey * bx1 + ez * bx2);
     y = F(ex * by0 + ey * by1 + ez * by2);
     z = F(ex * n0 + ey * n1 + ez * n2 + (D - D0));
 }
+
+// where a cell lies in the lattice (the neighbour-normal variant asks whether
+// its neighbours' 3^3 does too)
+struct Place {
+    int x, y, z, X, Y, Z;
+};
 
 // neighbour-normal variant: the normal of interface neighbour q's plane, its
 // own -h / |h| (h its 3^3 fill-level gradient) when its 3^3 lies in the lattice
 // and h does not vanish, else the centre normal that m holds on entry (the rule
 // of the oracle's variant)
 template <int NRM, class T>
-__device__ __forceinline__ void own_normal(const float* __restrict__ s, int c, int sy, int sz, int q, int gx0,
-                                           int gy0, int gz0, int X, int Y, int Z, T (&m)[3], bool& own, T& ih_out) {
+__device__ __forceinline__ void own_normal(const float* __restrict__ s, int c, int sy, int sz, int q,
+                                           const Place& at, T (&m)[3], bool& own, T& ih_out) {
     const int dx = q_dx(q), dy = q_dy(q), dz = q_dz(q);
-    const int ax = gx0 + dx, ay = gy0 + dy, az = gz0 + dz;
-    const bool inside = ax >= 1 && ay >= 1 && az >= 1 && ax <= X - 2 && ay <= Y - 2 && az <= Z - 2;
+    const int ax = at.x + dx, ay = at.y + dy, az = at.z + dz;
+    const bool inside = ax >= 1 && ay >= 1 && az >= 1 && ax <= at.X - 2 && ay <= at.Y - 2 && az <= at.Z - 2;
     if (inside) {
         T hx, hy, hz;
         gradient27<NRM, T>(s, c + dz * sz + dy * sy + dx, sy, sz, hx, hy, hz);
@@ -252,42 +318,96 @@ __device__ __forceinline__ void own_normal(const float* __restrict__ s, int c, i
 // neighbour-normal variant: neighbour q's point, the foot of its own plane
 // e + D m - D0 n, in the frame
 template <class T, class F>
-__device__ __forceinline__ void cell_point_own(int q, T D, T D0, const T (&m)[3], T bx0, T bx1, T bx2,
+__device__ __forceinline__ void cell_point_own(const float4& e, T D, T D0, const T (&m)[3], T bx0, T bx1, T bx2,
                                                T by0, T by1, T by2, T n0, T n1, T n2, F& x, F& y, F& z) {
-    const T P0 = T(q_dx(q)) + D * m[0] - D0 * n0, P1 = T(q_dy(q)) + D * m[1] - D0 * n1,
-            P2 = T(q_dz(q)) + D * m[2] - D0 * n2;
+    const T P0 = T(e.x) + D * m[0] - D0 * n0, P1 = T(e.y) + D * m[1] - D0 * n1, P2 = T(e.z) + D * m[2] - D0 * n2;
     x = F(P0 * bx0 + P1 * bx1 + P2 * bx2);
     y = F(P0 * by0 + P1 * by1 + P2 * by2);
     z = F(P0 * n0 + P1 * n1 + P2 * n2);
 }
 
+// The fit's 20 sums over the pairs of neighbours (l, l + 16) of the 26 in
+// order, for the few cells that need them so.  Lane j of each four forms up to
+// six, its factor times each of (x^2, y^2, xy, x, y, z): factors x^2, y^2, xy
+// and x; lane 2, whose first two are lanes 0's and 1's, takes y y and y z.
+template <class F, class Point>
+__device__ __forceinline__ void ordered_sums(int j, unsigned mask, unsigned list, Point point, F (&sum)[20]) {
+    F acc[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) acc[k] = F(0);
+#pragma unroll 1
+    for (int l = 0; l < 16; ++l) {
+        const int qa = l < 13 ? l : l + 1, qb = min(l + 17, 26);
+        const bool ia = (mask >> qa) & 1u, ib = l < 10 && ((mask >> qb) & 1u);
+        if (!ia && !ib) continue;
+        F u[2][6], v[2][6];                       // factors of the six sums, of each of the pair
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int q = h ? qb : qa;
+            F x = F(0), y = F(0), z = F(0);
+            if (h ? ib : ia) point(q, __popc(list & ((1u << q) - 1u)), x, y, z);
+            const F f = j == 0 ? x * x : (j == 1 ? y * y : (j == 2 ? x * y : x));
+            u[h][0] = j == 2 ? y : f;
+            u[h][1] = u[h][0];
+            u[h][2] = u[h][3] = u[h][4] = u[h][5] = f;
+            v[h][0] = j == 2 ? y : x * x;
+            v[h][1] = j == 2 ? z : y * y;
+            v[h][2] = x * y; v[h][3] = x; v[h][4] = y; v[h][5] = z;
+        }
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const F t = u[0][k] * v[0][k] + u[1][k] * v[1][k];
+            acc[k] += t;
+        }
+    }
+    auto from = [&](auto lane, int k) { return quad_move<lane.value * 0x55>(acc[k]); };   // quad_perm: one lane to all
+    const std::integral_constant<int, 0> l0;
+    const std::integral_constant<int, 1> l1;
+    const std::integral_constant<int, 2> l2;
+    const std::integral_constant<int, 3> l3;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) sum[tri(i, 0)] = from(l0, i);
+#pragma unroll
+    for (int i = 1; i < 5; ++i) sum[tri(i, 1)] = from(l1, i);
+#pragma unroll
+    for (int i = 2; i < 5; ++i) sum[tri(i, 2)] = from(l2, i);
+    sum[tri(3, 3)] = from(l3, 3);
+    sum[tri(4, 3)] = from(l3, 4);
+    sum[tri(4, 4)] = from(l2, 0);
+    sum[15] = from(l0, 5); sum[16] = from(l1, 5); sum[17] = from(l2, 5); sum[18] = from(l3, 5); sum[19] = from(l2, 1);
+}
+
 // s: LDS fill levels, c: centre index, sy/sz: LDS strides, lane: lane in the
-// wavefront.  Every lane of the group must call it; returns kappa (same bits
-// on every lane).  With ADJ, also writes out[q * ostride] = gk * d kappa /
-// d phi_q (q = 0..26), with the interface mask, the PLIC cases and the active
-// fit parameters held fixed.  With NBR (neighbour normals: each interface
-// neighbour's point from its own normal m = -h / |h|; gx0.. and X.. locate the
-// cell in the lattice), out holds the derivative with every m held fixed, and
+// wavefront.  Every lane of the group must call it.  False, with nothing
+// written, when the fit is ill-conditioned and the sums were not ORDERED: the
+// caller then calls it again with ORDERED (from the fill levels, so that nothing
+// is kept in registers for it).  kappa: the same bits on every lane.  With ADJ,
+// also writes out[q * ostride] = gk * d kappa / d phi_q (q = 0..26), with the
+// interface mask, the PLIC cases and the active fit parameters held fixed.
+// With NBR (neighbour normals: each interface neighbour's point from its own
+// normal m = -h / |h|), out holds the derivative with every m held fixed, and
 // outh[3t .. 3t+2] = gk * d kappa / d h of neighbour slot t (the 26 offsets
 // other than the centre; zero where the neighbour keeps the centre normal);
 // spreading that over the neighbour's 3^3 is left to the gathers.
-template <int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR = false>
-__device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, int sy, int sz, int lane,
-                                           float gk, float* __restrict__ out, unsigned ostride,
-                                           float* __restrict__ outh, CellLds<T, ADJ>& L, int gx0 = 0,
-                                           int gy0 = 0, int gz0 = 0, int X = 0, int Y = 0, int Z = 0) {
+template <bool ORDERED, int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR = false>
+__device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, int sy, int sz, int lane,
+                                          float gk, float* __restrict__ out, unsigned ostride,
+                                          float* __restrict__ outh, CellLds<T, ADJ>& L, float& kappa,
+                                          const Place& where = {}) {
     using mt = M<T>;
     const int j = lane % kLanes, cell = lane / kLanes;
     T gx, gy, gz;
     gradient27<NRM, T>(s, c, sy, sz, gx, gy, gz);
-    auto at = [&](int q) { return c + q_dz(q) * sz + q_dy(q) * sy + q_dx(q); };
+    // (strides 3 and 9, known at compile time: the 27 levels are in a row)
+    auto at = [&](int q) { return sy == 3 && sz == 9 ? c - 13 + q : c + q_dz(q) * sz + q_dy(q) * sy + q_dx(q); };
     // interface mask of the 27 cells, 7 tests per lane
     unsigned mask = 0u;
 #pragma unroll
     for (int k = 0; k < kRounds; ++k) {
         const int q = j + k * kLanes;
-        if (q < 27 && is_iface(s[at(q < 27 ? q : 0)])) mask |= 1u << q;
+        if (is_iface(s[at(min(q, 26))]) && q < 27) mask |= 1u << (k * kLanes);
     }
+    mask <<= j;
     mask |= quad_move<kSwap1>(mask);
     mask |= quad_move<kSwap2>(mask);
     mask &= ~kCentre;
@@ -299,7 +419,8 @@ __device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, i
             if constexpr (NBR)
                 for (int t = j; t < 78; t += kLanes) outh[t] = 0.0f;
         }
-        return 0.0f;
+        kappa = 0.0f;
+        return true;
     }
     const T ign = mt::rcp(mt::sqrt(gn2));
     const T n0 = -gx * ign, n1 = -gy * ign, n2 = -gz * ign;
@@ -325,7 +446,7 @@ __device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, i
         if constexpr (NBR) {
             T mq[3] = {n0, n1, n2}, ih;
             bool own = false;
-            if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, gx0, gy0, gz0, X, Y, Z, mq, own, ih);
+            if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, where, mq, own, ih);
             L.D[k][lane] = offset<SOLVER, T, U>(mq[0], mq[1], mq[2], p);
         } else {
             L.D[k][lane] = offset<SOLVER, T, U>(n0, n1, n2, p);
@@ -337,31 +458,40 @@ __device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, i
     F sum[20];
 #pragma unroll
     for (int i = 0; i < 20; ++i) sum[i] = F(0);
-    k = 0;
-#pragma unroll 1
-    for (unsigned m = first_entries(list, j); m; m = next_entries(m), ++k) {
-        const int q = __ffs(static_cast<int>(m)) - 1;
-        if (q == 13) continue;
-        const T D = L.D[k][lane];
-        F x, y, z;
+    // the point of neighbour q, whose offset is entry e of the list
+    auto point = [&](int q, int e, F& x, F& y, F& z) {
+        const T D = L.D[e / kLanes][(lane & ~(kLanes - 1)) + e % kLanes];
         if constexpr (NBR) {
             T mq[3] = {n0, n1, n2}, ih;
             bool own = false;
-            own_normal<NRM, T>(s, c, sy, sz, q, gx0, gy0, gz0, X, Y, Z, mq, own, ih);
-            cell_point_own<T, F>(q, D, D0, mq, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
+            own_normal<NRM, T>(s, c, sy, sz, q, where, mq, own, ih);
+            cell_point_own<T, F>(L.e[q], D, D0, mq, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
         } else {
-            cell_point<T, F>(q, D, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
+            cell_point<T, F>(L.e[q], D, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
         }
-        const F Q[5] = {x * x, y * y, x * y, x, y};
+    };
+    if constexpr (!ORDERED) {
+        int e = j;
+#pragma unroll 1
+        for (unsigned m = first_entries(list, j); m; m = next_entries(m), e += kLanes) {
+            const int q = __ffs(static_cast<int>(m)) - 1;
+            if (q == 13) continue;
+            F x, y, z;
+            point(q, e, x, y, z);
+            const F Q[5] = {x * x, y * y, x * y, x, y};
 #pragma unroll
-        for (int i = 0; i < 5; ++i) {
+            for (int i = 0; i < 5; ++i) {
 #pragma unroll
-            for (int l = 0; l <= i; ++l) sum[tri(i, l)] += Q[i] * Q[l];
-            sum[15 + i] += z * Q[i];
+                for (int l = 0; l <= i; ++l) sum[tri(i, l)] += Q[i] * Q[l];
+                sum[15 + i] += z * Q[i];
+            }
         }
+#pragma unroll
+        for (int i = 0; i < 20; ++i) sum[i] = group_sum(sum[i]);
+    } else {
+        ordered_sums<F>(j % 4, mask, list, point, sum);
     }
-#pragma unroll
-    for (int i = 0; i < 20; ++i) sum[i] = group_sum(sum[i]);
+    const int npts = __popc(mask);
     F m[5][5], b[5];
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
@@ -369,12 +499,13 @@ __device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, i
 #pragma unroll
         for (int l = 0; l <= i; ++l) m[i][l] = sum[tri(i, l)];
     }
-    const int npts = __popc(mask);
     bool act[5];
     F a[5], dinv[5];
-    ldlt_factor<F>(m, npts < 5 ? npts : 5, act, dinv);
+    const bool steady = ldlt_factor<F>(m, npts < 5 ? npts : 5, act, dinv);
+    if constexpr (!ORDERED)
+        if (!steady) return false;
     ldlt_solve<F>(m, act, dinv, b, a);
-    const float kappa = float(kappa_of<F>(a));
+    kappa = float(kappa_of<F>(a));
     if constexpr (ADJ) {
         // d kappa / d(A,B,C,H,I), kappa = -(A(I^2+1) + B(H^2+1) - CHI) / W^(3/2)
         const F A = a[0], B = a[1], C = a[2], H = a[3], I = a[4];
@@ -405,7 +536,7 @@ __device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, i
             T mq[3] = {n0, n1, n2}, ih = T(0);
             bool own = false;
             if constexpr (NBR)
-                if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, gx0, gy0, gz0, X, Y, Z, mq, own, ih);
+                if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, where, mq, own, ih);
             T cq[3];
             const T dv = offset_grad_from_d0<T>(mq[0], mq[1], mq[2], p, D, cq);   // 1/A, centroid
             if (q == 13) {
@@ -413,8 +544,8 @@ __device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, i
                 continue;
             }
             F x, y, z;
-            if constexpr (NBR) cell_point_own<T, F>(q, D, D0, mq, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
-            else cell_point<T, F>(q, D, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
+            if constexpr (NBR) cell_point_own<T, F>(L.e[q], D, D0, mq, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
+            else cell_point<T, F>(L.e[q], D, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
             const F Q[5] = {x * x, y * y, x * y, x, y};
             F zq = F(0), aQ = F(0);
 #pragma unroll
@@ -425,7 +556,7 @@ __device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, i
             const T xbar = T(F(2) * x * Qbar[0] + y * Qbar[2] + Qbar[3]);
             const T ybar = T(F(2) * y * Qbar[1] + x * Qbar[2] + Qbar[4]);
             const T zt = T(zq);
-            const T ex = T(q_dx(q)), ey = T(q_dy(q)), ez = T(q_dz(q));
+            const T ex = T(L.e[q].x), ey = T(L.e[q].y), ez = T(L.e[q].z);
             if constexpr (NBR) {
                 // x = P.b_x, y = P.b_y, z = P.n with P = e + D m - D0 n, D = d0(phi_q, m)
                 const T P0 = ex + D * mq[0] - D0 * n0, P1 = ey + D * mq[1] - D0 * n1, P2 = ez + D * mq[2] - D0 * n2;
@@ -485,10 +616,10 @@ __device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, i
         for (int kk = 0; kk < kRounds; ++kk) {
             const int q = j + kk * kLanes;
             if (q < 27) {
-                const int dx = q_dx(q), dy = q_dy(q), dz = q_dz(q), e2 = dx * dx + dy * dy + dz * dz;
+                const float4 e = L.e[q];
                 const bool on = (mask >> q) & 1u;
                 const T ph = on ? L.pb[cell][q] : T(0);
-                const float v = float(ph + T(nrm_weight<NRM>(e2)) * (T(dx) * gb0 + T(dy) * gb1 + T(dz) * gb2));
+                const float v = float(ph + T(e.w) * (T(e.x) * gb0 + T(e.y) * gb1 + T(e.z) * gb2));
                 out[static_cast<unsigned>(q) * ostride] = q == 13 ? float(-sz_ * dvc) : v;
                 if constexpr (NBR) {
                     if (!on && q != 13) {
@@ -498,9 +629,8 @@ __device__ __forceinline__ float curv_cell(const float* __restrict__ s, int c, i
                 }
             }
         }
-        __syncwarp();                              // L is reused by the next cell
     }
-    return kappa;
+    return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -558,27 +688,32 @@ __device__ __forceinline__ int ordered_compact(int n, Pred pred, unsigned short*
 
 // ---------------------------------------------------------------------------
 // Workspace (caller device memory, 4-byte aligned):
-//   [0, 256)  header: [0] work items, [1] gather tiles, [2] overflow tiles,
-//             [4..5] the call's interface-cell count (read by the status query)
-//   flags     ntiles      interface cells in the tile (backward)
-//   cbase     ntiles      first contribution row of the tile's interface cells
-//                         (prefix of flags in tile order)
+//   [0, 256)  header: [2] overflow tiles, [16..] activity of lattices of 1 or 2 tiles
+//   flags     ntiles      interface cells in the tile
+//   grows     ntiles      first contribution row of each group (the prefix of
+//                         the groups' cell counts in order; before that pass
+//                         the counts themselves)
 //   mask      32 ntiles   interface bit of each of the tile's 1024 cells
-//   prefix    32 ntiles   set bits of mask before word w
-//   items     128 ntiles  work items (tile << 7 | part), 8 interface cells each
-//   tiles     ntiles      backward gather tiles
-//   over      ntiles      row-prefix block totals, then the gather tiles with a
-//                         source cell without a stored row
+//   prefix    32 ntiles   set bits of mask before word w; word 0, where that
+//                         is 0, holds the interface cells of the group before
+//                         the tile
+//   items     128 ntiles  work items (tile << 7 | part), 8 interface cells
+//                         each, every group's from its first tile's place on
+//   gitems    ntiles      work items of each group; then, 64 bits per 64 tiles,
+//                         the tiles with an interface cell in their 3x3x3
+//                         tiles (backward)
+//   over      ntiles      the gather's tiles with a source cell without a row
 //   contrib   the rest:   27 floats per row (backward contributions), entry q
 //             of every row together (index q * rows + row): the gather's lanes
 //             read entry q of neighbouring cells' rows at once
-// The fixed part (everything but contrib) is 784 bytes per tile.  The
-// backward stores the 27 contributions of an interface cell in row
-// cbase[tile] + rank when that row fits; cells beyond the capacity are
-// recomputed by the fallback gather, so every workspace size >= the fixed part
-// is correct and a larger one is faster.
+// mask and prefix are written, and read, only for tiles with interface cells.
+// The fixed part (everything but contrib) is 784 bytes per tile.
+// The backward stores the 27 contributions of an interface cell in its row
+// when that fits; cells beyond the capacity are recomputed by the fallback
+// gather, so every workspace size >= the fixed part is correct and a larger
+// one is faster.
 // ---------------------------------------------------------------------------
-constexpr int kPartCells = kGroups;           // interface cells per work item
+constexpr int kPartCells = 8;                 // interface cells per work item
 constexpr int kMaxParts = kTile / kPartCells; // 128
 constexpr int kWords = kTile / 32;            // mask words per tile
 constexpr size_t kFixedPerTile = sizeof(unsigned) * (1 + 1 + kWords + kWords + kMaxParts + 1 + 1);
@@ -594,7 +729,6 @@ constexpr unsigned kRowLimit = (1u << 30) / 27u;
 // and, per neighbour, the adjoint of that neighbour's own fill-level gradient
 // (26 x 3, together, after the contributions of all rows), followed in the
 // workspace by one 3-vector per row, the sum of those adjoints at the row's cell
-constexpr int kRowFloatsH = 26 * 3;
 constexpr int kRowFloatsNbr = 27 + kRowFloatsH;
 constexpr size_t kRowBytesNbr = (kRowFloatsNbr + 3) * sizeof(float);
 constexpr unsigned kRowLimitNbr = (1u << 30) / kRowFloatsNbr;
@@ -602,244 +736,238 @@ constexpr unsigned kRowLimitNbr = (1u << 30) / kRowFloatsNbr;
 // the default leaves room for interfaces that cross a tile several times
 constexpr size_t kDefaultRowsPerTileNbr = 64;
 
-// header words: [0] work items, [1] gather tiles, [2] overflow tiles,
-// [3] workgroup tickets of the one-pass row prefix
-constexpr int kCounters = 4;
-constexpr int kTicket = 3;
+constexpr int kOverflow = 2;                    // header word: overflow tiles
 
 struct Workspace {
-    unsigned* counter;  // header words (kCounters)
+    unsigned* counter;  // header
     unsigned* flags;
-    unsigned* cbase;
+    unsigned* grows;
     unsigned* mask;
     unsigned* prefix;
     unsigned* items;
-    unsigned* tiles;
+    unsigned* gitems;
     unsigned* over;
     float* contrib;
     float* hbar;        // neighbour-normal backward: 3 floats per row
+    unsigned* act;      // activity, 2 words per 64 tiles
     unsigned rows;      // contribution capacity
+    int per;            // tiles per group
+    int groups;
+    int segs;           // runs of 64 tiles
 };
 
-// clears the header words and the first nstatus words of the overflow list
-// (the one-pass row prefix publishes its workgroup totals there)
-// (from header word first on: a backward that reuses a forward's records
-// keeps its work item count, word 0)
-__global__ void k_curv_zero(unsigned* counter, int first, unsigned* status, int nstatus) {
-    const int t = threadIdx.x;
-    if (t >= first && t < kCounters) counter[t] = 0u;
-    for (int i = t; i < nstatus; i += blockDim.x) status[i] = 0u;
+// 16 bytes at any 4-byte boundary (one access on gfx950)
+struct Four {
+    float v[4];
+};
+
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// 4 consecutive cells along x, those inside the lattice
+__device__ __forceinline__ void store_four(float* __restrict__ out, int x, int y, int z, int X, int Y, int Z,
+                                           const Four& r) {
+    if (x < X && y < Y && z < Z) {
+        float* p = out + (static_cast<int64_t>(z) * Y + y) * X + x;
+        if (x + 4 <= X) {
+            __builtin_memcpy(p, &r, sizeof(r));
+        } else {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (x + k < X) p[k] = r.v[k];
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
-// 1. streaming scan: zero output everywhere; the tile's interface bitmask and
-// the set bits before each of its words; one work item (tile << 7 | part) per
-// kPartCells interface cells of the tile; the tile's interface count (its
-// flag), from which the backward assigns contribution rows.  (A backward that
-// reuses a forward's records runs no scan: its gather writes the zeros.)  Thread t handles 4 consecutive cells along x, which are the cells
-// 4t .. 4t+3 of the tile in cell order (x fastest, then y, z).
+// 1. streaming scan, one workgroup per group of tiles: zero output everywhere
+// (ZERO: the forward; the backward's gather writes the zeros), each tile's
+// interface count; of the tiles with interface cells the bitmask, the set bits
+// before each of its words and the work items; the group's counts.  A wavefront
+// takes a tile (one more per round where a group has over 16): lane l handles,
+// in layer u = 0..3, the 4 consecutive cells 4l .. 4l+3.  Bound by HBM: many
+// short workgroups stream faster than wavefronts that walk over several tiles
+// with the next one's loads in flight (97 against 111 us for 512 x 384 x 384).
+// The zeros are non-temporal stores: they are not read again, and 256 MB of
+// last-level cache then keep phi, which is (256^3, repeated: 17 against 24 us).
 // ---------------------------------------------------------------------------
-template <bool VEC, bool FWD>
-__global__ __launch_bounds__(kThreads) void k_curv_scan(const float* __restrict__ phi, float* __restrict__ out,
-                                                        Workspace ws, int X, int Y, int Z, int ntx, int nty) {
-    __shared__ int wsum[kThreads / 64];
-    __shared__ unsigned smask[kWords];
-    const int tile = blockIdx.x;
-    const int x0 = (tile % ntx) * TX, y0 = ((tile / ntx) % nty) * TY, z0 = (tile / (ntx * nty)) * TZ;
-    const int t = threadIdx.x;
-    const int x = x0 + (t % 16) * 4, y = y0 + (t / 16) % TY, z = z0 + t / (16 * TY);
-    if (t < kWords) smask[t] = 0u;
-    unsigned nib = 0u;
-    if (y < Y && z < Z) {
-        const bool yz_in = y >= 1 && y <= Y - 2 && z >= 1 && z <= Z - 2;
-        const int64_t row = (static_cast<int64_t>(z) * Y + y) * X;
-        if (VEC && x + 4 <= X) {
-            // a plain load: with the non-temporal hint this scan measured slower
-            // (34 against 26 us at 256^3)
-            const float4 v = *reinterpret_cast<const float4*>(phi + row + x);
-            *reinterpret_cast<float4*>(out + row + x) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            const float vv[4] = {v.x, v.y, v.z, v.w};
+template <bool ZERO, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_curv_scan(const float* __restrict__ phi, float* __restrict__ out,
+                                                          Workspace ws, int X, int Y, int Z, int ntx, int nty,
+                                                          int ntiles) {
+    __shared__ unsigned count[WAVES];
+    const int g = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int gfirst = g * ws.per, glast = min(gfirst + ws.per, ntiles);
+    unsigned* items = ws.items + static_cast<size_t>(gfirst) * kMaxParts;
+    unsigned nitems = 0u, ncells = 0u;                        // of the rounds before
+    for (int r0 = gfirst; r0 < glast; r0 += WAVES) {
+        const int tile = r0 + wave;
+        unsigned total = 0u;
+        if (tile < glast) {                                   // uniform per wavefront
+            const int x0 = (tile % ntx) * TX, y0 = ((tile / ntx) % nty) * TY, z0 = (tile / (ntx * nty)) * TZ;
+            const int x = x0 + (lane % 16) * 4, y = y0 + lane / 16;
+            float v[4][4];
+            if (x0 + TX <= X && y0 + TY <= Y && z0 + TZ <= Z) {
+                const int64_t at = (static_cast<int64_t>(z0) * Y + y) * X + x, plane = static_cast<int64_t>(Y) * X;
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                nib |= (yz_in && x + k >= 1 && x + k <= X - 2 && is_iface(vv[k])) ? (1u << k) : 0u;
-        } else {
+                for (int u = 0; u < 4; ++u) __builtin_memcpy(v[u], phi + at + u * plane, 16);
+                if constexpr (ZERO) {
+                    const float4u zero = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (x + k < X) {
-                    const float v = phi[row + x + k];
-                    out[row + x + k] = 0.0f;
-                    nib |= (yz_in && x + k >= 1 && x + k <= X - 2 && is_iface(v)) ? (1u << k) : 0u;
+                    for (int u = 0; u < 4; ++u)
+                        __builtin_nontemporal_store(zero, reinterpret_cast<float4u*>(out + at + u * plane));
+                }
+            } else {
+                // cells outside the lattice read one inside (no branch, whose
+                // join would wait for each load; the mask leaves them out)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float* p = phi + (static_cast<int64_t>(min(z0 + u, Z - 1)) * Y + min(y, Y - 1)) * X;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[u][k] = p[min(x + k, X - 1)];
+                }
+                if constexpr (ZERO) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) store_four(out, x, y, z0 + u, X, Y, Z, Four{{0.0f, 0.0f, 0.0f, 0.0f}});
+                }
+            }
+            unsigned nib[4], some = 0u;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                nib[u] = 0u;
+                const bool yz_in = y >= 1 && y <= Y - 2 && z0 + u >= 1 && z0 + u <= Z - 2;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    nib[u] |= (yz_in && x + k >= 1 && x + k <= X - 2 && is_iface(v[u][k])) ? (1u << k) : 0u;
+                some |= nib[u];
+            }
+            if (__any(some != 0u)) {                          // uniform
+                // mask word 8u + l / 8 from the nibbles of 8 lanes, then word l
+                // to lane l and the set bits before it
+                unsigned mw = 0u;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    unsigned w = nib[u] << (4 * (lane % 8));
+                    w |= quad_move<kSwap1>(w);
+                    w |= quad_move<kSwap2>(w);
+                    w |= quad_move<kHalfMirror>(w);
+                    const unsigned o = __shfl(w, (lane % 8) * 8, 64);
+                    mw = lane / 8 == u ? o : mw;
+                }
+                const unsigned c = __popc(mw), incl = half_scan(c);
+                total = from_lane(incl, kWords - 1);
+                if (lane < kWords) {
+                    ws.mask[static_cast<size_t>(tile) * kWords + lane] = mw;
+                    if (lane) ws.prefix[static_cast<size_t>(tile) * kWords + lane] = incl - c;
                 }
             }
         }
+        if (lane == 0) count[wave] = total;
+        __syncthreads();
+        // the round's tiles, one per lane: the cells and items before each
+        const unsigned mine = lane < WAVES ? count[lane] : 0u, parts = (mine + kPartCells - 1) / kPartCells;
+        const unsigned cells = wave_scan(mine), its = wave_scan(parts);
+        if (wave == 0 && lane < WAVES && r0 + lane < glast) {
+            ws.flags[r0 + lane] = mine;
+            if (mine) ws.prefix[static_cast<size_t>(r0 + lane) * kWords] = ncells + cells - mine;
+        }
+        const unsigned n = from_lane(parts, wave), before = nitems + from_lane(its, wave) - n;
+        for (unsigned p = static_cast<unsigned>(lane); p < n; p += 64u)
+            items[before + p] = (static_cast<unsigned>(tile) << 7) | p;
+        ncells += from_lane(cells, 63);
+        nitems += from_lane(its, 63);
+        if (r0 + WAVES < glast) __syncthreads();         // count reused by the next round
     }
-    // block count of interface cells (wave butterflies, then 4 waves)
-    int cnt = __popc(nib);
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) cnt += __shfl_xor(cnt, m, 64);
-    if ((t & 63) == 0) wsum[t >> 6] = cnt;
-    __syncthreads();                                      // smask cleared
-    if (nib) atomicOr(&smask[t / 8], nib << ((t % 8) * 4));
-    __syncthreads();
-    int total = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) total += wsum[w];
-    const unsigned parts = (total + kPartCells - 1) / kPartCells;
-    if (t < 64) {                                         // the first wave writes the tile's records
-        // mask words and the set bits before each (exclusive scan over lanes 0..31)
-        const unsigned mw = t < kWords ? smask[t] : 0u, c = __popc(mw);
-        unsigned incl = c;
-#pragma unroll
-        for (int d = 1; d < kWords; d <<= 1) {
-            const unsigned o = __shfl_up(incl, d, 64);
-            if (t >= d) incl += o;
-        }
-        if (t < kWords) {
-            ws.mask[tile * kWords + t] = mw;
-            ws.prefix[tile * kWords + t] = incl - c;
-        }
-        // the tile's interface count: the backward assigns rows from these,
-        // and plic_curvature_status sums them (no shared counter here: every
-        // atomic on one word serialises at the memory side)
-        if (t == 0) ws.flags[tile] = static_cast<unsigned>(total);
-        // only a tile with interface cells waits for an atomic's result (the
-        // wait also covers the block's stores); parts is uniform per block
-        if (parts) {
-            unsigned base = 0u;
-            if (t == 0) base = atomicAdd(ws.counter, parts);
-            base = __shfl(base, 0, 64);
-            for (unsigned p = static_cast<unsigned>(t); p < parts; p += 64u)
-                ws.items[base + p] = (static_cast<unsigned>(tile) << 7) | p;
-        }
+    if (threadIdx.x == 0) {
+        ws.gitems[g] = nitems;
+        ws.grows[g] = ncells;
+        if (g == 0) ws.counter[kOverflow] = 0u;
     }
 }
 
-// Contribution rows in tile order: cbase[tile] = number of interface cells in
-// the tiles before it (exclusive prefix of flags), saturated at kRowCap, so
-// the cells that get a row for a given workspace size do not depend on the
-// order in which the scan's blocks ran.  Two passes over workgroups of 256
-// tiles: the first, with the gather list, writes each workgroup's local
-// prefix and its total; the second adds the totals of the workgroups before
-// it.  The totals live in the overflow list until the gather uses it.
-
-// Gather list and the first prefix pass, one tile per thread.  The list holds
-// every tile whose 3x3x3 tile neighbourhood has an interface cell (its cells
-// can receive a contribution); its order does not affect any result.
-// With ONEPASS (lattices of at most kOnePassBlocks workgroups of tiles) the
-// workgroups also finish the prefix themselves: each takes a ticket, which
-// orders it after every workgroup that took one before (those have started
-// and never wait before they publish), publishes its total in the overflow
-// list (cleared at the start of the call) with a ready bit, and adds up the
-// totals of the workgroups before it, one per lane of its first wave, waiting
-// for each to be published.  Otherwise the totals go to the overflow list for
-// the second pass.
-constexpr int kOnePassBlocks = 256;
-constexpr unsigned kPublished = 0x80000000u;                   // totals are at most 256 * 1024
-
-template <bool ONEPASS>
-__global__ __launch_bounds__(kThreads) void k_curv_dilate(Workspace ws, int ntx, int nty, int ntz, int ntiles) {
-    __shared__ unsigned wsum[kThreads / 64];
-    __shared__ unsigned wact[kThreads / 64];
-    __shared__ unsigned long long boff;
-    __shared__ unsigned gbase;
-    __shared__ int ticket;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    int b = static_cast<int>(blockIdx.x);
-    if constexpr (ONEPASS) {
-        if (t == 0) ticket = static_cast<int>(atomicAdd(ws.counter + kTicket, 1u));
-        __syncthreads();
-        b = ticket;
-    }
-    const int tile = b * kThreads + t;
-    bool act = false;
-    unsigned c = 0u;
-    if (tile < ntiles) {
-        c = ws.flags[tile];
-        const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = tile / (ntx * nty);
-#pragma unroll
-        for (int q = 0; q < 27; ++q) {
-            const int ax = tx + q_dx(q), ay = ty + q_dy(q), az = tz + q_dz(q);
-            if (ax >= 0 && ax < ntx && ay >= 0 && ay < nty && az >= 0 && az < ntz)
-                act |= ws.flags[(az * nty + ay) * ntx + ax] != 0u;
-        }
-    }
-    unsigned incl = c;                                        // inclusive scan over the wave
+// First rows of the groups, by one wavefront: lane l takes a run of consecutive
+// groups.  Rows go to the interface cells in tile order, saturated at kRowCap,
+// so the cells that get a row for a given workspace size are always the same.
+__device__ __forceinline__ void group_rows(const Workspace& ws) {
+    const int lane = threadIdx.x, run = (ws.groups + 63) / 64, g0 = lane * run;
+    const unsigned* cells = ws.grows;
+    unsigned long long sum = 0ull;
+#pragma unroll 8
+    for (int k = 0; k < run; ++k) sum += g0 + k < ws.groups ? cells[g0 + k] : 0u;
+    unsigned long long before = sum;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
-        const unsigned o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
+        const unsigned long long o = __shfl_up(before, d, 64);
+        if (lane >= d) before += o;
     }
-    if (lane == 63) wsum[wave] = incl;
-    const unsigned long long bal = __ballot(act);
-    if (lane == 0) wact[wave] = static_cast<unsigned>(__popcll(bal));
-    __syncthreads();
-    unsigned woff = 0u, total = 0u, aoff = 0u, atotal = 0u;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) {
-        woff += w < wave ? wsum[w] : 0u;
-        total += wsum[w];
-        aoff += w < wave ? wact[w] : 0u;
-        atotal += wact[w];
-    }
-    // the gather list: one atomic per workgroup (the atomics on one word are
-    // served one at a time), taken after the total is published
-    if constexpr (ONEPASS) {
-        if (t == 0) {
-            __hip_atomic_store(ws.over + b, total | kPublished, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            gbase = atotal ? atomicAdd(ws.counter + 1, atotal) : 0u;
-        }
-        if (wave == 0) {
-            unsigned long long acc = 0ull;
-            for (int p = lane; p < b; p += 64) {
-                unsigned v;
-                do {
-                    v = __hip_atomic_load(ws.over + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                } while (!(v & kPublished));
-                acc += v & ~kPublished;
-            }
-#pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-            if (lane == 0) boff = acc;
-        }
-        __syncthreads();
-        if (tile < ntiles) {
-            const unsigned long long r = boff + woff + incl - c;
-            ws.cbase[tile] = static_cast<unsigned>(r < kRowCap ? r : kRowCap);
-        }
-    } else {
-        if (tile < ntiles) ws.cbase[tile] = woff + incl - c;
-        if (t == 0) {
-            ws.over[blockIdx.x] = total;                      // at most 256 * 1024 = 2^18
-            gbase = atotal ? atomicAdd(ws.counter + 1, atotal) : 0u;
-        }
-        __syncthreads();
-    }
-    if (act) {
-        const unsigned long long below = lane ? (bal & ((~0ull) >> (64 - lane))) : 0ull;
-        ws.tiles[gbase + aoff + __popcll(below)] = static_cast<unsigned>(tile);
+    before -= sum;
+    for (int k = 0; k < run; ++k) {
+        if (g0 + k >= ws.groups) break;
+        const unsigned c = cells[g0 + k];
+        ws.grows[g0 + k] = static_cast<unsigned>(before < kRowCap ? before : kRowCap);
+        before += c;
     }
 }
 
-// second prefix pass: workgroup b's offset is the sum of the totals of
-// workgroups 0..b-1 (64-bit), added to its local prefixes with saturation
-__global__ __launch_bounds__(kThreads) void k_curv_prefix(Workspace ws, int ntiles) {
-    __shared__ unsigned long long part[kThreads / 64];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    unsigned long long acc = 0ull;
-    for (int i = t; i < static_cast<int>(blockIdx.x); i += kThreads) acc += ws.over[i];
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-    if (lane == 0) part[wave] = acc;
-    __syncthreads();
-    unsigned long long off = 0ull;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) off += part[w];
-    const int tile = blockIdx.x * kThreads + t;
-    if (tile < ntiles) {
-        const unsigned long long r = off + ws.cbase[tile];
-        ws.cbase[tile] = static_cast<unsigned>(r < kRowCap ? r : kRowCap);
+__global__ __launch_bounds__(64) void k_curv_rows(Workspace ws) { group_rows(ws); }
+
+// The work items in one sequence: lane l owns the groups l, l + 64, ... and the
+// items go by lane, then by group.  A wavefront sums its lanes' groups once
+// (256^3: 16 coalesced loads) and finds any item from that: there is no list
+// over the whole lattice, so no counter to clear first and none that every tile
+// would have to wait for (one word's atomics are served one at a time, about 12
+// ns each: over 9000 tiles with interface cells, half of the scan's time).
+struct ItemFinder {
+    unsigned mine, before, total;       // items of this lane's groups, of lower lanes, of all
+
+    __device__ __forceinline__ static unsigned of_group(const Workspace& ws, int g) {
+        return g < ws.groups ? ws.gitems[g] : 0u;
     }
-}
+
+    __device__ __forceinline__ explicit ItemFinder(const Workspace& ws) {
+        const int lane = threadIdx.x & 63, n = (ws.groups + 63) / 64;
+        mine = 0u;
+        for (int k0 = 0; k0 < n; k0 += 8) {
+            unsigned c[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) c[k] = of_group(ws, (k0 + k) * 64 + lane);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) mine += c[k];
+        }
+        const unsigned incl = wave_scan(mine);
+        before = incl - mine;
+        total = from_lane(incl, 63);
+    }
+
+    // item lo for the wavefront's lower half, hi for its upper half (both below
+    // total); every lane must call it
+    __device__ __forceinline__ unsigned item(const Workspace& ws, int lane, unsigned lo, unsigned hi) const {
+        const int l0 = __ffsll(__ballot(before <= lo && lo - before < mine)) - 1;
+        const int l1 = __ffsll(__ballot(before <= hi && hi - before < mine)) - 1;
+        const int owner = lane & 32 ? l1 : l0, k = lane & 31;
+        unsigned rest = lane & 32 ? hi - from_lane(before, l1) : lo - from_lane(before, l0);
+        // the owner's groups, a run of up to 4 per lane of the half
+        const int run = (ws.groups + 64 * 32 - 1) / (64 * 32);
+        unsigned c[kMaxGroups / (64 * 32)], sum = 0u;
+#pragma unroll
+        for (int i = 0; i < kMaxGroups / (64 * 32); ++i) {
+            c[i] = i < run ? of_group(ws, (k * run + i) * 64 + owner) : 0u;
+            sum += c[i];
+        }
+        const unsigned excl = half_scan(sum) - sum;
+        const unsigned hit = static_cast<unsigned>(__ballot(excl <= rest && rest - excl < sum) >> (lane & 32));
+        const int at = __ffs(static_cast<int>(hit)) - 1;
+        rest -= __shfl(excl, at, 32);
+        int g = at * run;
+        if (run > 1) {
+#pragma unroll
+            for (int i = 0; i < kMaxGroups / (64 * 32) - 1; ++i) {
+                const unsigned n = __shfl(c[i], at, 32);
+                if (i + 1 < run && rest >= n && g == at * run + i) { rest -= n; ++g; }
+            }
+        }
+        return ws.items[(static_cast<size_t>(g) * 64 + owner) * ws.per * kMaxParts + rest];
+    }
+};
 
 // ---------------------------------------------------------------------------
 // 2. work items: up to kPartCells interface cells of a tile, each cell on a
@@ -849,97 +977,158 @@ __global__ __launch_bounds__(kThreads) void k_curv_prefix(Workspace ws, int ntil
 // contribution row (when it fits).
 // ---------------------------------------------------------------------------
 
-// Lattice position of the interface cell of rank i (in cell order) of a
-// tile, found by the 32 lanes of a group together: lane j reads mask word j
-// and the count of set bits before it.  False, for the whole group, when the
-// tile has no more than i interface cells.
-__device__ __forceinline__ bool tile_cell(const Workspace& ws, int tile, int i, int j, int half, int ntx, int nty,
-                                          int& gx, int& gy, int& gz) {
-    const unsigned mw = ws.mask[tile * kWords + j], pw = ws.prefix[tile * kWords + j];
-    const int n = static_cast<int>(__shfl(pw + __popc(mw), kWords - 1, kGroup));
-    if (i >= n) return false;
-    const unsigned ui = static_cast<unsigned>(i);
-    const unsigned in_word = static_cast<unsigned>(__ballot(pw <= ui && ui < pw + __popc(mw)) >> half);
-    const int w = __ffs(static_cast<int>(in_word)) - 1;
-    const unsigned word = __shfl(mw, w, kGroup);
-    const unsigned k = ui - __shfl(pw, w, kGroup);
-    const bool hit = ((word >> j) & 1u) && static_cast<unsigned>(__popc(word & ((1u << j) - 1u))) == k;
-    const int b = __ffs(static_cast<int>(static_cast<unsigned>(__ballot(hit) >> half))) - 1;
-    const int cl = w * 32 + b;
-    gx = (tile % ntx) * TX + cl % TX;
-    gy = ((tile / ntx) % nty) * TY + (cl / TX) % TY;
-    gz = (tile / (ntx * nty)) * TZ + cl / (TX * TY);
-    return true;
+// this half wavefront's view of a tile: lane j (0..31) holds mask word j and
+// the set bits before it; row: the tile's first contribution row
+__device__ __forceinline__ void tile_words(const Workspace& ws, int tile, int j, unsigned& mw, unsigned& pw,
+                                           unsigned& row) {
+    mw = ws.mask[static_cast<size_t>(tile) * kWords + j];
+    const unsigned p = ws.prefix[static_cast<size_t>(tile) * kWords + j];
+    row = ws.grows[tile / ws.per] + __shfl(p, 0, 32);
+    pw = j ? p : 0u;
 }
 
-// threadIdx.x through an opaque move: what a loop derives from it is then
-// recomputed in every iteration (a few ALU instructions) instead of being
-// kept in registers across the loop, where it would spill
-__device__ __forceinline__ int thread_index_per_iteration() {
-    int t;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"(static_cast<int>(threadIdx.x)));
-    return t;
+// the cell of rank first + r (in cell order) of the half's tile, below its
+// count; r: 0 .. RANKS-1.  The word that holds each rank by one ballot.
+template <int RANKS>
+__device__ __forceinline__ int tile_cell(unsigned mw, unsigned pw, unsigned first, int r, int lane) {
+    unsigned words = 0u;
+    const unsigned end = pw + __popc(mw);
+#pragma unroll
+    for (int k = 0; k < RANKS; ++k) {
+        const unsigned long long in = __ballot(pw <= first + k && first + k < end);
+        const unsigned half = lane & 32 ? static_cast<unsigned>(in >> 32) : static_cast<unsigned>(in);
+        words = r == k ? half : words;
+    }
+    const int w = __ffs(static_cast<int>(words)) - 1;
+    unsigned word = __shfl(mw, w, 32);
+    int k = static_cast<int>(first + r - __shfl(pw, w, 32)), bit = 0;
+#pragma unroll
+    for (int st = 16; st; st >>= 1) {                        // the word's k-th set bit
+        const int low = __popc(word & ((1u << st) - 1u));
+        const bool up = k >= low;
+        k -= up ? low : 0;
+        bit += up ? st : 0;
+        word >>= up ? st : 0;
+    }
+    return w * 32 + bit;
+}
+
+// zero on the whole tile, by one wavefront
+__device__ __forceinline__ void zero_tile(float* __restrict__ out, int tile, int lane, int X, int Y, int Z, int ntx,
+                                          int nty) {
+    const int x0 = (tile % ntx) * TX, y0 = ((tile / ntx) % nty) * TY, z0 = (tile / (ntx * nty)) * TZ;
+    const int x = x0 + (lane % 16) * 4, y = y0 + lane / 16;
+    if (x0 + TX <= X && y0 + TY <= Y && z0 + TZ <= Z) {
+        const int64_t at = (static_cast<int64_t>(z0) * Y + y) * X + x, plane = static_cast<int64_t>(Y) * X;
+        const float4u zero = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) __builtin_nontemporal_store(zero, reinterpret_cast<float4u*>(out + at + u * plane));
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) store_four(out, x, y, z0 + u, X, Y, Z, Four{{0.0f, 0.0f, 0.0f, 0.0f}});
+    }
+}
+
+// Backward, one wavefront per 64 tiles: which of them have an interface cell in
+// their 3x3x3 tiles (their cells can receive a contribution: the gather's
+// tiles), and a zero gradient for the others.  Beside the work items in one
+// launch: those are bound by instruction issue and leave HBM idle.
+__device__ __forceinline__ void zero_away(float* __restrict__ gphi, const Workspace& ws, int seg, int X, int Y, int Z,
+                                          int ntx, int nty, int ntiles) {
+    const int lane = threadIdx.x, tile = seg * 64 + lane, ntz = ntiles / (ntx * nty);
+    bool act = false;
+    if (tile < ntiles) {
+        const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = tile / (ntx * nty);
+        unsigned any = 0u;
+#pragma unroll
+        for (int q = 0; q < 27; ++q) {
+            // (a neighbour outside the lattice is taken for the nearest inside: one of the 27 as well)
+            const int ax = min(max(tx + q_dx(q), 0), ntx - 1), ay = min(max(ty + q_dy(q), 0), nty - 1),
+                      az = min(max(tz + q_dz(q), 0), ntz - 1);
+            any |= ws.flags[(az * nty + ay) * ntx + ax];
+        }
+        act = any != 0u;
+    }
+    const unsigned long long bits = __ballot(act);
+    if (lane < 2) ws.act[2 * seg + lane] = static_cast<unsigned>(bits >> (32 * lane));
+    const int left = ntiles - seg * 64;
+    unsigned long long away = ~bits & (left >= 64 ? ~0ull : (1ull << left) - 1ull);
+    for (; away; away &= away - 1ull) zero_tile(gphi, seg * 64 + __ffsll(away) - 1, lane, X, Y, Z, ntx, nty);
 }
 
 // Workgroups of one wavefront: each 32-lane half takes a work item (8 cells of
-// a tile, 4 lanes each).  A group finds its cell, the i-th interface cell of
-// the tile in cell order, by a binary search over the tile's prefix counts and
-// one over the bits of the mask word found, stages the cell's fill levels and
-// runs curv_cell.  The forward writes kappa, the backward (ADJ) the cell's
-// contribution row when it fits the workspace.
-template <class T, class U, bool ADJ, bool NBR>
+// a tile, 4 lanes per cell).  A group finds its cell, the i-th interface cell of
+// the tile in cell order, from the tile's bitmask and prefix counts, stages the
+// cell's fill levels and runs curv_cell.  The forward writes kappa, the backward
+// (ADJ) the cell's contribution row when it fits the workspace; its first
+// workgroups are zero_away's, one per CU at most (one per run of tiles, 1152 of
+// them, kept the work items from the SIMDs: 209 against 183 us for the spray).
+__host__ __device__ inline unsigned zero_blocks(const Workspace& ws) { return ws.segs < 256 ? ws.segs : 256; }
+
+template <class T, bool ADJ>
 constexpr int cell_waves() {
-    if (!ADJ) return sizeof(T) == 4 ? 4 : 2;
-    return sizeof(T) == 4 ? 3 : 2;
+    return sizeof(T) == 4 ? (ADJ ? 3 : 4) : 2;
 }
 
 template <int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR>
-__global__ __launch_bounds__(64, (cell_waves<T, U, ADJ, NBR>())) void k_curv_quads(
-    const float* __restrict__ phi, const float* __restrict__ gkap, float* __restrict__ kappa, Workspace ws, int X,
-    int Y, int Z, int ntx, int nty) {
+__global__ __launch_bounds__(64, (cell_waves<T, ADJ>())) void k_curv_quads(
+    const float* __restrict__ phi, const float* __restrict__ gkap, float* __restrict__ out_field, Workspace ws, int X,
+    int Y, int Z, int ntx, int nty, int ntiles) {
     // the cell's 3x3x3 fill levels (5x5x5 with neighbour normals)
     constexpr int H = NBR ? 2 : 1, W = 2 * H + 1, NB = W * W * W, C = (H * W + H) * W + H;
+    constexpr unsigned kItems = kWaveCells / kPartCells;     // of a wavefront
     __shared__ float nbh[kWaveCells][NB];
     __shared__ CellLds<T, ADJ> lds;
-    const unsigned nitems = *static_cast<volatile unsigned*>(ws.counter);
-    const unsigned npairs = (nitems + 1u) / 2u;
-    for (unsigned pr = blockIdx.x; pr < npairs; pr += gridDim.x) {
+    unsigned block = blockIdx.x, blocks = gridDim.x;
+    if constexpr (ADJ) {
+        if (block == 0 && threadIdx.x == 0) ws.counter[kOverflow] = 0u;   // the gather, a later launch, counts there
+        const unsigned nzero = zero_blocks(ws);
+        if (block < nzero) {
+            for (int seg = static_cast<int>(block); seg < ws.segs; seg += static_cast<int>(nzero))
+                zero_away(out_field, ws, seg, X, Y, Z, ntx, nty, ntiles);
+            return;
+        }
+        block -= nzero;
+        blocks -= nzero;
+    } else {
+        --blocks;                                            // the last one: the groups' first rows
+        if (__builtin_expect(block == blocks, 0)) {
+            group_rows(ws);
+            return;
+        }
+    }
+    init_cells<NRM>(lds, static_cast<int>(threadIdx.x));
+    const ItemFinder finder(ws);
+    for (unsigned it = kItems * block; it < finder.total; it += kItems * blocks) {
         const int lane = thread_index_per_iteration(), l32 = lane & 31, cell = lane / kLanes, j = lane % kLanes;
-        const unsigned item = 2u * pr + static_cast<unsigned>(lane >> 5);
-        if (item >= nitems) continue;                        // uniform per half
-        const unsigned e = ws.items[item];
+        const bool second = it + kItems - 1u < finder.total;
+        const unsigned e = finder.item(ws, lane, it, it + (second ? kItems - 1u : 0u));
         const int tile = static_cast<int>(e >> 7), part = static_cast<int>(e & 127u);
-        const unsigned mw = ws.mask[tile * kWords + l32], pw = ws.prefix[tile * kWords + l32];
+        unsigned mw, pw, row;
+        tile_words(ws, tile, l32, mw, pw, row);
         const unsigned n = __shfl(pw + __popc(mw), kWords - 1, 32);
-        const unsigned ic = static_cast<unsigned>(part * kPartCells + cell % kPartCells);
-        const unsigned ui = ic < n ? ic : n - 1u;            // n >= 1: the tile has an item
-        int w = 0;                                           // the last word with prefix <= ui
-#pragma unroll
-        for (int st = kWords / 2; st; st >>= 1) w += __shfl(pw, w + st, 32) <= ui ? st : 0;
-        unsigned word = __shfl(mw, w, 32);
-        int k = static_cast<int>(ui - __shfl(pw, w, 32)), bit = 0;
-#pragma unroll
-        for (int st = 16; st; st >>= 1) {
-            const int low = __popc(word & ((1u << st) - 1u));
-            const bool up = k >= low;
-            k -= up ? low : 0;
-            bit += up ? st : 0;
-            word >>= up ? st : 0;
-        }
-        if (ic >= n) continue;                               // uniform per group
-        unsigned row = 0u;
-        if constexpr (ADJ) {
-            row = ws.cbase[tile] + ic;
-            if (row >= ws.rows) continue;                    // uniform per group; the gather recomputes
-        }
-        const int cl = w * 32 + bit;
+        const unsigned i0 = static_cast<unsigned>(part * kPartCells), ic = i0 + cell % kPartCells;
+        // n > i0: the tile has the item
+        const int cl = tile_cell<kPartCells>(mw, pw, i0, static_cast<int>(min(ic, n - 1u) - i0), lane);
+        row += ic;
+        // uniform per group; a row that does not fit is recomputed by the gather
+        if (ic >= n || (!second && lane >= 32) || (ADJ && row >= ws.rows)) continue;
         const int gx = (tile % ntx) * TX + cl % TX, gy = ((tile / ntx) % nty) * TY + (cl / TX) % TY,
                   gz = (tile / (ntx * nty)) * TZ + cl / (TX * TY);
+        const int64_t gi = (static_cast<int64_t>(gz) * Y + gy) * X + gx;
+        float gk = 0.0f;
+        if constexpr (ADJ) gk = gkap[gi];
         if constexpr (NBR) {
-            for (int t = j; t < NB; t += kLanes) {
-                const int ax = gx + t % W - H, ay = gy + (t / W) % W - H, az = gz + t / (W * W) - H;
-                nbh[cell][t] = (ax >= 0 && ax < X && ay >= 0 && ay < Y && az >= 0 && az < Z)
-                                   ? phi[(static_cast<int64_t>(az) * Y + ay) * X + ax] : 0.0f;
+            // 25 rows of 5 levels, those outside the lattice read as 0
+            for (int r = j; r < W * W; r += kLanes) {
+                const int ay = gy + r % W - H, az = gz + r / W - H;
+                const bool in = ay >= 0 && ay < Y && az >= 0 && az < Z;
+                const float* p = phi + (static_cast<int64_t>(az) * Y + ay) * X + (gx - H);
+                float v[W];
+#pragma unroll
+                for (int t = 0; t < W; ++t) v[t] = in && gx + t - H >= 0 && gx + t - H < X ? p[t] : 0.0f;
+#pragma unroll
+                for (int t = 0; t < W; ++t) nbh[cell][r * W + t] = v[t];
             }
         } else {
             // 9 rows of 3 consecutive levels, all in the lattice (an interface
@@ -958,17 +1147,19 @@ __global__ __launch_bounds__(64, (cell_waves<T, U, ADJ, NBR>())) void k_curv_qua
             }
         }
         __syncwarp();
-        const int64_t gi = (static_cast<int64_t>(gz) * Y + gy) * X + gx;
-        if constexpr (ADJ) {
-            curv_cell<SOLVER, T, U, F, true, NRM, NBR>(
-                nbh[cell], C, W, W * W, lane, gkap[gi], ws.contrib + row, ws.rows,
-                NBR ? ws.contrib + 27u * ws.rows + static_cast<size_t>(row) * kRowFloatsH : nullptr, lds, gx, gy, gz,
-                X, Y, Z);
-        } else {
-            const float kv = curv_cell<SOLVER, T, U, F, false, NRM, NBR>(nbh[cell], C, W, W * W, lane, 0.0f, nullptr,
-                                                                         0u, nullptr, lds, gx, gy, gz, X, Y, Z);
-            if (j == 0) kappa[gi] = kv;
+        const Place where{gx, gy, gz, X, Y, Z};
+        float kv = 0.0f;
+        float* out = ADJ ? ws.contrib + row : nullptr;
+        float* outh = ADJ && NBR ? ws.contrib + 27u * ws.rows + static_cast<size_t>(row) * kRowFloatsH : nullptr;
+        const bool done = curv_cell<false, SOLVER, T, U, F, ADJ, NRM, NBR>(nbh[cell], C, W, W * W, lane, gk, out,
+                                                                           ws.rows, outh, lds, kv, where);
+        if (__builtin_expect(!done, 0)) {                    // uniform per group
+            __syncwarp();
+            curv_cell<true, SOLVER, T, U, F, ADJ, NRM, NBR>(nbh[cell], C, W, W * W, lane, gk, out, ws.rows, outh, lds,
+                                                            kv, where);
         }
+        if constexpr (!ADJ)
+            if (j == 0) out_field[gi] = kv;
         __syncwarp();                                        // nbh and lds reused by the next pair
     }
 }
@@ -986,13 +1177,14 @@ constexpr int kChunk = 128;
 constexpr int kCopyBatch = 8;                 // contribution loads in flight per thread
 constexpr unsigned short kNoSlot = 0xFFFFu;
 
-// contribution row of an interior interface cell: cbase of its tile plus its
-// rank among the tile's interface cells in cell order
+// contribution row of an interior interface cell: its group's first row, the
+// group's cells before its tile, and its rank in the tile in cell order
 __device__ __forceinline__ unsigned contrib_row(const Workspace& ws, int gx, int gy, int gz, int ntx, int nty) {
     const int ctile = ((gz / TZ) * nty + gy / TY) * ntx + gx / TX;
     const int l = ((gz % TZ) * TY + gy % TY) * TX + gx % TX;
-    const unsigned w = ws.mask[ctile * kWords + l / 32];
-    return ws.cbase[ctile] + ws.prefix[ctile * kWords + l / 32] + __popc(w & ((1u << (l % 32)) - 1u));
+    const unsigned* pre = ws.prefix + static_cast<size_t>(ctile) * kWords;
+    const unsigned w = ws.mask[static_cast<size_t>(ctile) * kWords + l / 32];
+    return ws.grows[ctile / ws.per] + pre[0] + (l >= 32 ? pre[l / 32] : 0u) + __popc(w & ((1u << (l % 32)) - 1u));
 }
 
 // Fallback gather over the overflow list: the tiles with a source cell whose
@@ -1013,10 +1205,12 @@ __global__ __launch_bounds__(kThreads) void k_curv_gather_fallback(const float* 
     __shared__ float contrib[kChunk][27];
     __shared__ unsigned crow[kChunk];
     __shared__ int wcount[kThreads / 64];
-    __shared__ CellLds<T, true> lds;
+    __shared__ CellLds<T, true> cells[kThreads / 64];
     const int tid = threadIdx.x;
+    CellLds<T, true>& lds = cells[tid >> 6];
+    init_cells<NRM>(lds, tid & 63);
     for (int i = tid; i < C_REGION; i += kThreads) slot[i] = kNoSlot;
-    const unsigned ntl = *static_cast<volatile unsigned*>(ws.counter + 2);
+    const unsigned ntl = *static_cast<volatile unsigned*>(ws.counter + kOverflow);
     for (unsigned it = blockIdx.x; it < ntl; it += gridDim.x) {
         const int tile = static_cast<int>(ws.over[it]);
         const int x0 = (tile % ntx) * TX, y0 = ((tile / ntx) % nty) * TY, z0 = (tile / (ntx * nty)) * TZ;
@@ -1059,16 +1253,22 @@ __global__ __launch_bounds__(kThreads) void k_curv_gather_fallback(const float* 
                     if (at[u] != 0xFFFFFFFFu) contrib[at[u] / 27][at[u] % 27] = v[u];
             }
             {
-                // rows that did not fit: recomputed by the first wavefront, one
-                // group of lanes per cell
-                for (int i = tid / kLanes; tid < 64 && i < nc; i += kWaveCells) {
+                // rows that did not fit: recomputed, one group of lanes per cell
+                for (int i = tid / kLanes; i < nc; i += kThreads / kLanes) {
                     if (crow[i] < ws.rows) continue;                     // uniform per group
                     const int ci = cand[c0 + i];
                     const int lx = ci % C_RX, ly = (ci / C_RX) % C_RY, lz = ci / (C_RX * C_RY);
                     const int gx = x0 - 1 + lx, gy = y0 - 1 + ly, gz = z0 - 1 + lz;
                     const float gk = gkap[(static_cast<int64_t>(gz) * Y + gy) * X + gx];
-                    curv_cell<SOLVER, T, U, F, true, NRM>(s, ((lz + 1) * RY + (ly + 1)) * RX + (lx + 1), RX, RX * RY,
-                                                          tid, gk, contrib[i], 1u, nullptr, lds);
+                    const int centre = ((lz + 1) * RY + (ly + 1)) * RX + (lx + 1);
+                    float kv;
+                    const bool done = curv_cell<false, SOLVER, T, U, F, true, NRM>(s, centre, RX, RX * RY, tid & 63, gk,
+                                                                                   contrib[i], 1u, nullptr, lds, kv);
+                    __syncwarp();
+                    if (!done)
+                        curv_cell<true, SOLVER, T, U, F, true, NRM>(s, centre, RX, RX * RY, tid & 63, gk, contrib[i], 1u,
+                                                                    nullptr, lds, kv);
+                    __syncwarp();                                        // lds reused by the next cell
                 }
             }
             __syncthreads();
@@ -1114,24 +1314,29 @@ __global__ __launch_bounds__(kThreads) void k_curv_hgather(Workspace ws, int X, 
     const int tid = threadIdx.x, grp = tid / kGroup, j = tid % kGroup;
     const int half = tid & 32;
     const int q = j < 13 ? j : j + 1;
-    const unsigned nitems = *static_cast<volatile unsigned*>(ws.counter);
-    for (unsigned item = blockIdx.x; item < nitems; item += gridDim.x) {
-        const unsigned e = ws.items[item];
+    const ItemFinder finder(ws);
+    for (unsigned item = blockIdx.x; item < finder.total; item += gridDim.x) {
+        const unsigned e = finder.item(ws, tid & 63, item, item);
         const int tile = static_cast<int>(e >> 7), part = static_cast<int>(e & 127u);
-        const int i = part * kPartCells + grp;
-        const unsigned row = ws.cbase[tile] + static_cast<unsigned>(i);
-        if (row >= ws.rows) continue;                        // uniform per group; the gather sees the miss
-        int gx, gy, gz;
-        if (!tile_cell(ws, tile, i, j, half, ntx, nty, gx, gy, gz)) continue;
+        unsigned mw, pw, row;
+        tile_words(ws, tile, j, mw, pw, row);
+        const unsigned n = __shfl(pw + __popc(mw), kWords - 1, kGroup);
+        // both halves of a wavefront look at the same tile, each for its rank
+        const unsigned i0 = static_cast<unsigned>(part * kPartCells + (grp & ~1)), i = i0 + (grp & 1);
+        if (i0 >= n) continue;                               // uniform per wavefront
+        const int cl = tile_cell<2>(mw, pw, i0, static_cast<int>(min(i, n - 1u) - i0), tid & 63);
+        row += i;
+        if (i >= n || row >= ws.rows) continue;              // uniform per group; the gather sees the miss
+        const int gx = (tile % ntx) * TX + cl % TX, gy = ((tile / ntx) % nty) * TY + (cl / TX) % TY,
+                  gz = (tile / (ntx * nty)) * TZ + cl / (TX * TY);
         const int cx = gx - q_dx(q), cy = gy - q_dy(q), cz = gz - q_dz(q);
         bool src = j < 26 && cx >= 0 && cx < X && cy >= 0 && cy < Y && cz >= 0 && cz < Z;
         unsigned r = 0u;
         if (src) {
             const int ctile = ((cz / TZ) * nty + cy / TY) * ntx + cx / TX;
             const int l = ((cz % TZ) * TY + cy % TY) * TX + cx % TX;
-            const unsigned w = ws.mask[ctile * kWords + l / 32], bit = 1u << (l % 32);
-            src = (w & bit) != 0u;
-            r = ws.cbase[ctile] + ws.prefix[ctile * kWords + l / 32] + __popc(w & (bit - 1u));
+            src = ws.flags[ctile] != 0u && ((ws.mask[static_cast<size_t>(ctile) * kWords + l / 32] >> (l % 32)) & 1u);
+            if (src) r = contrib_row(ws, cx, cy, cz, ntx, nty);
         }
         const bool stored = src && r < ws.rows;
         const bool miss = ((__ballot(src && !stored) >> half) & 0xffffffffull) != 0ull;
@@ -1155,298 +1360,258 @@ __global__ __launch_bounds__(kThreads) void k_curv_hgather(Workspace ws, int X, 
     }
 }
 
-// Direct backward gather for the tiles whose sources all have a stored row.
-// The interface bitmasks, prefix counts and first rows of the 3x3x3 tiles
-// around the tile are staged in LDS.  Each of the tile's cells tests its 27
-// sources (target - e_q) there; the cells with a source (the band along the
-// interface; the rest keep the scan's zero) are listed in cell order, and each
-// adds entry q of its sources' rows for q = 0..26 in order, all loads issued
-// before the first add.  A tile with a source beyond the store goes to the
-// overflow list; the fallback gather rewrites every cell of it.
-struct SourceMap {
-    unsigned smask[27][kWords];
-    unsigned spref[27][kWords];
-    unsigned sbase[27];
+// Direct backward gather over the tiles with an interface cell in their 3x3x3
+// tiles (zero_away wrote the others), one workgroup per tile, one wavefront per
+// layer of it.  The mask rows of the 6 x 6 rows of cells around the tile are
+// staged, each with one bit of the columns left and right of the tile and the
+// contribution rows before it; a row's band (cells with an interface source
+// within one cell) is the OR of its 9 neighbouring rows, each dilated by one
+// cell in x.  A lane takes a band cell and adds entry q of its sources' rows
+// for q = 0..26 in order, all loads issued before the first add; the tile is
+// put together in LDS and written as whole lines.
+// A tile with a source beyond the store goes to the overflow list, and the
+// fallback gather, a later launch, rewrites all of its cells; with neighbour
+// normals (NBR, which adds each source's own-gradient adjoint spread by the
+// gradient weights of NRM, and has no fallback) its band becomes NaN.
+// Bound by the latency of a tile's dependent loads (activity, masks, rows) and
+// by instruction issue (27 sources per band cell), so compiled for 7 wavefronts
+// per SIMD.  A flat interface fills a tile's layers: one wavefront per tile
+// would be a chain of 12 rounds for its 768 band cells.
+struct GatherLds {
+    uint4 win[36][2];                             // per mask row (y, then z, from -1 to 4): see row_sources
+    unsigned edge[36][2];                         // contribution rows of the sources left and right of the tile
+    unsigned long long dilated[36];
+    unsigned long long band[TY * TZ];
+    int before[TY * TZ];                          // band cells before the row
+    alignas(16) float out[kTile];
 };
 
-// row of source q of the cell (cx, cy, cz) of the centre tile; sets src when
-// that source is an interface cell
-__device__ __forceinline__ unsigned source_row(const SourceMap& m, int cx, int cy, int cz, int q, bool& src) {
-    const int sx = cx - q_dx(q), sy = cy - q_dy(q), sz = cz - q_dz(q);
-    const int rx = sx < 0 ? -1 : (sx >= TX ? 1 : 0);
-    const int ry = sy < 0 ? -1 : (sy >= TY ? 1 : 0);
-    const int rz = sz < 0 ? -1 : (sz >= TZ ? 1 : 0);
-    const int tq = (rz + 1) * 9 + (ry + 1) * 3 + (rx + 1);
-    const int l = ((sz - rz * TZ) * TY + (sy - ry * TY)) * TX + (sx - rx * TX);
-    const unsigned word = m.smask[tq][l >> 5];
-    const unsigned bit = 1u << (l & 31);
-    src = (word & bit) != 0u;
-    return m.sbase[tq] + m.spref[tq][l >> 5] + __popc(word & (bit - 1u));
-}
-
-// NBR: the neighbour-normal variant's rows, plus each source's own-gradient
-// adjoint spread by the gradient weights of NRM; a tile with a source beyond
-// the store gets NaN on its band (that variant has no fallback)
-// thread t's cells 4t .. 4t+3 of a tile (row t / 16 in cell order) set to
-// zero where bit k of keep is clear; vec: 16-byte stores are aligned
-__device__ __forceinline__ void zero_cells(float* __restrict__ gphi, int tile, unsigned keep, bool vec, int X,
-                                           int Y, int Z, int ntx, int nty) {
-    const int t = threadIdx.x;
-    const int gx = (tile % ntx) * TX + (t % (TX / 4)) * 4, gy = ((tile / ntx) % nty) * TY + (t / (TX / 4)) % TY,
-              gz = (tile / (ntx * nty)) * TZ + t / (TX / 4 * TY);
-    if (gx >= X || gy >= Y || gz >= Z) return;
-    float* o = gphi + (static_cast<int64_t>(gz) * Y + gy) * X + gx;
-    if (vec && keep == 0u) {
-        *reinterpret_cast<float4*>(o) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    } else {
+// x of the k-th set bit of d (k below their number)
+__device__ __forceinline__ int set_bit(unsigned long long d, int k) {
+    unsigned word = static_cast<unsigned>(d);
+    const int low32 = __popc(word);
+    int x = 0;
+    if (k >= low32) { k -= low32; x = 32; word = static_cast<unsigned>(d >> 32); }
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (gx + k < X && !((keep >> k) & 1u)) o[k] = 0.0f;
+    for (int st = 16; st; st >>= 1) {
+        const int low = __popc(word & ((1u << st) - 1u));
+        const bool up = k >= low;
+        k -= up ? low : 0;
+        x += up ? st : 0;
+        word >>= up ? st : 0;
     }
+    return x;
 }
 
-constexpr int kZeroBatch = kThreads / 32;     // tiles checked at a time by the zero fill
+// The sources at x + 1, x, x - 1 of mask row rr (offsets q, q + 1, q + 2 of the
+// 27): bits 2, 1, 0 of the result where they are interface cells, and their
+// contribution rows (at most last, where they are none).  Bit p of the extended
+// row is cell p - 1, from the cell left of the tile to the one right of it; win
+// holds for either half of it the contribution row of its first set bit, the
+// half and the word after it.
+__device__ __forceinline__ unsigned row_sources(const GatherLds& m, int rr, int x, unsigned last, unsigned (&r)[3]) {
+    const uint4 w = m.win[rr][x >> 5];
+    const unsigned sh = static_cast<unsigned>(x) & 31u;
+    const unsigned three = __builtin_amdgcn_alignbit(w.z, w.y, sh) & 7u;
+    r[2] = w.x + __popc(w.y & ((1u << sh) - 1u));
+    r[1] = r[2] + (three & 1u);
+    r[0] = r[1] + ((three >> 1) & 1u);
+    if (x == 0) r[2] = m.edge[rr][0];
+    if (x == TX - 1) r[0] = m.edge[rr][1];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r[k] = min(r[k], last);
+    return three;
+}
 
-// Zero fill of a backward that ran no scan, tiles b0 .. b0 + kZeroBatch - 1:
-// those with no interface cell in their 3x3x3 tile neighbourhood (the ones the
-// gather list leaves out) get a zero gradient.  The 32 threads of group u
-// check the 27 neighbours of tile b0 + u (the gather list's own test), then the
-// workgroup zeroes the inactive ones.  zact: kZeroBatch words of LDS.
-__device__ __forceinline__ void zero_away_batch_at(float* __restrict__ gphi, const Workspace& ws, int b0, bool vec,
-                                                   int X, int Y, int Z, int ntx, int nty, int ntz, unsigned* zact) {
-    const int ntiles = ntx * nty * ntz;
-    const int tid = threadIdx.x, u = tid / 32, q = tid % 32;
-    const int tile = b0 + u;
-    bool act = false;
-    if (tile < ntiles && q < 27) {
-        const int ax = tile % ntx + q_dx(q), ay = (tile / ntx) % nty + q_dy(q), az = tile / (ntx * nty) + q_dz(q);
-        if (ax >= 0 && ax < ntx && ay >= 0 && ay < nty && az >= 0 && az < ntz)
-            act = ws.flags[(az * nty + ay) * ntx + ax] != 0u;
+// The gather's tiles in one sequence over up to 4096 runs of 64 tiles, as
+// ItemFinder: lane l owns runs l, l + 64, ...
+struct TileFinder {
+    unsigned mine, before, total;
+    int seg0;
+
+    __device__ __forceinline__ static unsigned long long of(const Workspace& ws, int seg) {
+        return seg < ws.segs ? ws.act[2 * seg] | (static_cast<unsigned long long>(ws.act[2 * seg + 1]) << 32) : 0ull;
     }
-    const unsigned long long bal = __ballot(act);
-    if (q == 0) zact[u] = static_cast<unsigned>((tid & 32) ? (bal >> 32) : (bal & 0xFFFFFFFFull)) != 0u;
-    __syncthreads();
+
+    __device__ __forceinline__ TileFinder(const Workspace& ws, int first) : seg0(first) {
+        const int lane = threadIdx.x & 63, n = (min(ws.segs - seg0, 4096) + 63) / 64;
+        mine = 0u;
+        for (int k0 = 0; k0 < n; k0 += 4) {
+            unsigned long long c[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) c[k] = k0 + k < n ? of(ws, seg0 + (k0 + k) * 64 + lane) : 0ull;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) mine += static_cast<unsigned>(__popcll(c[k]));
+        }
+        const unsigned incl = wave_scan(mine);
+        before = incl - mine;
+        total = from_lane(incl, 63);
+    }
+
+    // the i-th tile, i below total, the same for the whole wavefront
+    __device__ __forceinline__ int tile(const Workspace& ws, int lane, unsigned i) const {
+        const int owner = __ffsll(__ballot(before <= i && i - before < mine)) - 1;
+        const unsigned rest = i - from_lane(before, owner);
+        const unsigned long long bits = lane * 64 + owner < 4096 ? of(ws, seg0 + lane * 64 + owner) : 0ull;
+        const unsigned n = static_cast<unsigned>(__popcll(bits)), excl = wave_scan(n) - n;
+        const int at = __ffsll(__ballot(excl <= rest && rest - excl < n)) - 1;
+        const unsigned long long found = from_lane(static_cast<unsigned>(bits), at) |
+                                         (static_cast<unsigned long long>(from_lane(static_cast<unsigned>(bits >> 32), at)) << 32);
+        return (seg0 + at * 64 + owner) * 64 + set_bit(found, static_cast<int>(rest - from_lane(excl, at)));
+    }
+};
+
+template <bool NBR, int NRM>
+__global__ __launch_bounds__(kThreads, NBR ? 5 : 7) void k_curv_gather_direct(float* __restrict__ gphi, Workspace ws, int X,
+                                                                       int Y, int Z, int ntx, int nty, int ntz) {
+    static_assert(kThreads * 4 == kTile, "four cells of the output per thread");
+    __shared__ GatherLds m;
+    for (int seg0 = 0; seg0 < ws.segs; seg0 += 4096) {
+        const TileFinder finder(ws, seg0);
 #pragma unroll 1
-    for (int uu = 0; uu < kZeroBatch; ++uu) {
-        const int tl = b0 + uu;
-        if (tl < ntiles && !zact[uu]) zero_cells(gphi, tl, 0u, vec, X, Y, Z, ntx, nty);   // uniform test
-    }
-}
-
-// ZFILL: the call ran no scan (it reuses a forward's records), so nothing
-// zeroed grad_phi: the gather writes the zeros on its tiles' cells off the
-// band, and workgroups added past the first ngather zero the tiles it does not
-// gather, one batch of kZeroBatch tiles each
-template <bool NBR, int NRM, bool ZFILL>
-__global__ __launch_bounds__(kThreads, (NBR ? 5 : 8)) void k_curv_gather_direct(float* __restrict__ gphi, Workspace ws, int X,
-                                                                  int Y, int Z, int ntx, int nty, int ntz,
-                                                                  bool vec, unsigned ngather) {
-    __shared__ SourceMap m;
-    __shared__ unsigned short band[kTile];
-    __shared__ unsigned long long brow[TY * TZ];
-    __shared__ int bpref[TY * TZ];
-    __shared__ int bcount;
-    __shared__ unsigned zact[kZeroBatch];
-    if constexpr (ZFILL) {
-        // workgroups past the first ngather: one zero-fill batch each (they
-        // start as the gathering ones with fewer tiles finish)
-        if (blockIdx.x >= ngather) {
-            zero_away_batch_at(gphi, ws, static_cast<int>(blockIdx.x - ngather) * kZeroBatch, vec, X, Y, Z, ntx, nty,
-                               ntz, zact);
-            return;
-        }
-    }
-    const unsigned ntl = *static_cast<volatile unsigned*>(ws.counter + 1);
-    for (unsigned it = blockIdx.x; it < ntl; it += ngather) {
-        const int tid = thread_index_per_iteration();
-        const int tile = static_cast<int>(ws.tiles[it]);
-        if (ws.rows == 0u) {                                         // nothing stored: all recomputed
-            if (tid == 0) ws.over[atomicAdd(ws.counter + 2, 1u)] = static_cast<unsigned>(tile);
-            continue;
-        }
-        const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = tile / (ntx * nty);
-        const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
-        {
-            // the 3x3x3 tiles' bitmasks, prefix counts and first rows (zeros
-            // outside): word tid % 32 of tiles tid / 32 + 8u, and first row
-            // tid for tid < 27; every load before the first store
-            constexpr int kPer = kThreads / kWords, kStageIt = (27 + kPer - 1) / kPer;
-            const int w = tid % kWords;
-            unsigned smv[kStageIt], spv[kStageIt], sb = 0u;
-#pragma unroll
-            for (int u = 0; u < kStageIt; ++u) {
-                const int t = tid / kWords + kPer * u;
-                const int ax = tx + q_dx(t), ay = ty + q_dy(t), az = tz + q_dz(t);
-                const bool in = t < 27 && ax >= 0 && ax < ntx && ay >= 0 && ay < nty && az >= 0 && az < ntz;
-                const int nt = (az * nty + ay) * ntx + ax;
-                smv[u] = in ? ws.mask[nt * kWords + w] : 0u;
-                spv[u] = in ? ws.prefix[nt * kWords + w] : 0u;
+        for (unsigned i = blockIdx.x; i < finder.total; i += gridDim.x) {
+            const int tid = thread_index_per_iteration(), lane = tid & 63, cz = tid >> 6;
+            const int tile = finder.tile(ws, lane, i);
+            if (ws.rows == 0u) {                                     // nothing stored: all recomputed
+                if (tid == 0) ws.over[atomicAdd(ws.counter + kOverflow, 1u)] = static_cast<unsigned>(tile);
+                continue;
             }
-            if (tid < 27) {
-                const int ax = tx + q_dx(tid), ay = ty + q_dy(tid), az = tz + q_dz(tid);
-                if (ax >= 0 && ax < ntx && ay >= 0 && ay < nty && az >= 0 && az < ntz)
-                    sb = ws.cbase[(az * nty + ay) * ntx + ax];
-            }
+            const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = tile / (ntx * nty);
+            const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
+            const int ox = x0 + (lane % 16) * 4, oy = y0 + lane / 16, oz = z0 + cz;   // this lane's cells of the output
+            bool miss = false;
+            if (tid < 36) {
+                const int yy = tid % 6 - 1, zz = tid / 6 - 1;
+                const int ry = yy < 0 ? -1 : (yy >= TY ? 1 : 0), rz = zz < 0 ? -1 : (zz >= TZ ? 1 : 0);
+                const int ay = ty + ry, az = tz + rz;
+                const int w = ((zz - rz * TZ) * TY + (yy - ry * TY)) * 2;    // the row's first mask word
+                const bool yz_in = ay >= 0 && ay < nty && az >= 0 && az < ntz;
+                unsigned lo[3], hi[3], row[3], pre[3], has[3];
 #pragma unroll
-            for (int u = 0; u < kStageIt; ++u) {
-                const int t = tid / kWords + kPer * u;
-                if (t < 27) {
-                    m.smask[t][w] = smv[u];
-                    m.spref[t][w] = spv[u];
+                for (int t = 0; t < 3; ++t) {                        // columns left, own, right: loads
+                    const int ax = tx + t - 1;
+                    const bool in = yz_in && ax >= 0 && ax < ntx;
+                    const int nt = in ? (az * nty + ay) * ntx + ax : tile;
+                    const size_t b = static_cast<size_t>(nt) * kWords;
+                    has[t] = in ? ws.flags[nt] : 0u;
+                    lo[t] = ws.mask[b + w];
+                    hi[t] = ws.mask[b + w + 1];
+                    row[t] = ws.grows[nt / ws.per] + ws.prefix[b];
+                    pre[t] = ws.prefix[b + w];
                 }
-            }
-            if (tid < 27) m.sbase[tid] = sb;
-        }
-        __syncthreads();
-        // the band: cells with an interface source within one cell.  Row
-        // (y, z) of a tile is one 64-bit word of its mask (bit = x); a target
-        // row's band is the OR over the 9 neighbouring rows of the source row
-        // dilated by one cell in x (bits carried in from the x-neighbour tiles)
-        if (tid < TY * TZ) {
-            const int cy = tid % TY, cz = tid / TY;
-            unsigned long long d = 0ull;
 #pragma unroll
-            for (int dz = -1; dz <= 1; ++dz) {
-#pragma unroll
-                for (int dy = -1; dy <= 1; ++dy) {
-                    const int sy = cy + dy, sz = cz + dz;
-                    const int ry = sy < 0 ? -1 : (sy >= TY ? 1 : 0), rz = sz < 0 ? -1 : (sz >= TZ ? 1 : 0);
-                    const int w = ((sz - rz * TZ) * TY + (sy - ry * TY)) * 2;
-                    const int tc = (rz + 1) * 9 + (ry + 1) * 3;                 // + (rx + 1)
-                    const unsigned long long lft = m.smask[tc][w] | (static_cast<unsigned long long>(m.smask[tc][w + 1]) << 32);
-                    const unsigned long long mid = m.smask[tc + 1][w] | (static_cast<unsigned long long>(m.smask[tc + 1][w + 1]) << 32);
-                    const unsigned long long rgt = m.smask[tc + 2][w] | (static_cast<unsigned long long>(m.smask[tc + 2][w + 1]) << 32);
-                    d |= mid | (mid << 1) | (mid >> 1) | (lft >> 63) | ((rgt & 1ull) << 63);
+                for (int t = 0; t < 3; ++t) {                        // masks are there only where has is not 0
+                    lo[t] = has[t] ? lo[t] : 0u;
+                    hi[t] = has[t] ? hi[t] : 0u;
+                    row[t] += w ? pre[t] : 0u;
                 }
+                const unsigned left = hi[0] >> 31, right = lo[2] & 1u;
+                const unsigned e0 = (lo[1] << 1) | left, e1 = (lo[1] >> 31) | (hi[1] << 1), e2 = (hi[1] >> 31) | (right << 1);
+                const unsigned first = row[1] - left, before_left = row[0] + __popc(lo[0]) + __popc(hi[0] & 0x7FFFFFFFu);
+                m.win[tid][0] = make_uint4(first, e0, e1, 0u);
+                m.win[tid][1] = make_uint4(first + __popc(e0), e1, e2, 0u);
+                m.edge[tid][0] = before_left;
+                m.edge[tid][1] = row[2];
+                const unsigned long long mid = lo[1] | (static_cast<unsigned long long>(hi[1]) << 32);
+                m.dilated[tid] = mid | (mid << 1) | (mid >> 1) | left | (static_cast<unsigned long long>(right) << 63);
+                // a staged source beyond the store
+                miss = (mid && row[1] + static_cast<unsigned>(__popcll(mid)) > ws.rows) ||
+                       (left && before_left >= ws.rows) || (right && row[2] >= ws.rows);
             }
-            // cells past the lattice edge are not targets
-            const int gy = y0 + cy, gz = z0 + cz, nx = X - x0;
-            if (gy >= Y || gz >= Z) d = 0ull;
-            else if (nx < TX) d &= (1ull << nx) - 1ull;
-            brow[tid] = d;
-            // exclusive prefix of the rows' band counts (the 16 rows are lanes
-            // 0..15 of the first wave)
-            const int c = __popcll(d);
-            int inc = c;
-#pragma unroll
-            for (int o = 1; o < TY * TZ; o <<= 1) {
-                const int v = __shfl_up(inc, o, TY * TZ);
-                if (tid >= o) inc += v;
+            const bool missing = __syncthreads_or(miss);             // uniform
+            if (!NBR && missing) {
+                if (tid == 0) ws.over[atomicAdd(ws.counter + kOverflow, 1u)] = static_cast<unsigned>(tile);
+                __syncthreads();                                     // LDS reused by the next tile
+                continue;
             }
-            bpref[tid] = inc - c;
-            if (tid == TY * TZ - 1) bcount = inc;
-        }
-        __syncthreads();
-        // band cells listed in cell order (rows in order, x ascending): each
-        // band cell's place is its row's prefix plus the band bits before it
+            // every wavefront forms the band of the 16 rows (the same values)
+            int inc = 0;
+            if (lane < TY * TZ) {
+                const int by = lane % TY, bz = lane / TY;
+                unsigned long long d = 0ull;
 #pragma unroll
-        for (int k = 0; k < kCellsPerThread; ++k) {
-            const int cl = k * kThreads + tid, r = cl / TX, x = cl % TX;
-            const unsigned long long d = brow[r];
-            if ((d >> x) & 1ull)
-                band[bpref[r] + __popcll(d & ((1ull << x) - 1ull))] = static_cast<unsigned short>(cl);
-        }
-        const int nband = bcount;
-        __syncthreads();
-        if constexpr (NBR) {
-            // band cells: rows of their sources, all loads of a group of 9
-            // issued before its adds; sums kept until the tile is known to be
-            // complete (a missing row makes the tile's band NaN)
-            float acc[kCellsPerThread];
-            int miss = 0;
+                for (int dz = 0; dz < 3; ++dz) {
 #pragma unroll
-            for (int k = 0; k < kCellsPerThread; ++k) {
-                const int e = k * kThreads + tid;
-                float a = 0.0f;
-                if (e < nband) {
-                    const int cl = band[e];
-                    const int cx = cl % TX, cy = (cl / TX) % TY, cz = cl / (TX * TY);
-#pragma unroll 1
-                    for (int q0 = 0; q0 < 27; q0 += 9) {
-                        float v[9], hv[9][3];
-                        unsigned has = 0u;
-#pragma unroll
-                        for (int qq = 0; qq < 9; ++qq) {
-                            bool src;
-                            const unsigned r = source_row(m, cx, cy, cz, q0 + qq, src);
-                            const bool stored = src && r < ws.rows;
-                            miss |= src && !stored;
-                            has |= stored ? (1u << qq) : 0u;
-                            const unsigned rr = stored ? r : 0u;  // rows >= 1: row 0 read and masked out
-                            v[qq] = ws.contrib[static_cast<unsigned>(q0 + qq) * ws.rows + rr];
-                            hv[qq][0] = ws.hbar[3u * rr];
-                            hv[qq][1] = ws.hbar[3u * rr + 1u];
-                            hv[qq][2] = ws.hbar[3u * rr + 2u];
-                        }
-#pragma unroll
-                        for (int qq = 0; qq < 9; ++qq) {
-                            // the source's own gradient h = sum_q w_q e_q phi_(source + e_q)
-                            const int q = q0 + qq;
-                            const int e2 = q_dx(q) * q_dx(q) + q_dy(q) * q_dy(q) + q_dz(q) * q_dz(q);
-                            const float wq = static_cast<float>(q == 13 ? 0 : nrm_weight<NRM>(e2));
-                            const float t = v[qq] + wq * (static_cast<float>(q_dx(q)) * hv[qq][0] +
-                                                          static_cast<float>(q_dy(q)) * hv[qq][1] +
-                                                          static_cast<float>(q_dz(q)) * hv[qq][2]);
-                            a += (has >> qq) & 1u ? t : 0.0f;
-                        }
-                    }
+                    for (int dy = 0; dy < 3; ++dy) d |= m.dilated[(bz + dz) * 6 + by + dy];
                 }
-                acc[k] = a;
+                // cells past the lattice edge are not targets
+                if (y0 + by >= Y || z0 + bz >= Z) d = 0ull;
+                else if (X - x0 < TX) d &= (1ull << (X - x0)) - 1ull;
+                const int c = __popcll(d);
+                inc = static_cast<int>(half_scan(static_cast<unsigned>(c)));
+                m.band[lane] = d;
+                m.before[lane] = inc - c;
             }
-            if (__syncthreads_or(miss)) {                            // uniform per workgroup
-#pragma unroll
-                for (int k = 0; k < kCellsPerThread; ++k) acc[k] = __builtin_nanf("");
-            }
-#pragma unroll
-            for (int k = 0; k < kCellsPerThread; ++k) {
-                const int e = k * kThreads + tid;
-                if (e < nband) {
-                    const int cl = band[e];
-                    const int cx = cl % TX, cy = (cl / TX) % TY, cz = cl / (TX * TY);
-                    gphi[(static_cast<int64_t>(z0 + cz) * Y + (y0 + cy)) * X + (x0 + cx)] = acc[k];
-                }
-            }
-        } else {
-            // band cells: each sums entry q of its sources' rows in q order, the
-            // loads of a group of 9 issued before its adds, and stores the sum
-            // at once.  A tile with a source beyond the store goes to the
-            // overflow list; the fallback gather, a later launch, rewrites all
-            // of its cells.
-            int miss = 0;
+            const int nband = static_cast<int>(from_lane(static_cast<unsigned>(inc), TY * TZ - 1));
+            *reinterpret_cast<float4*>(m.out + tid * 4) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            __syncthreads();
+            const unsigned last = ws.rows - 1u;
 #pragma unroll 1
             for (int e = tid; e < nband; e += kThreads) {
-                const int cl = band[e];
-                const int cx = cl % TX, cy = (cl / TX) % TY, cz = cl / (TX * TY);
-                float a = 0.0f;                                      // +0 + 0 stays +0: same bits as skipping
-#pragma unroll 1
-                for (int q0 = 0; q0 < 27; q0 += 9) {
-                    float v[9];
-                    unsigned has = 0u;
+                int row = 0;                                         // the last row with before <= e
 #pragma unroll
-                    for (int qq = 0; qq < 9; ++qq) {
-                        bool src;
-                        const unsigned r = source_row(m, cx, cy, cz, q0 + qq, src);
-                        const bool stored = src && r < ws.rows;
-                        miss |= src && !stored;
-                        has |= stored ? (1u << qq) : 0u;
-                        // a non-source reads entry q of row 0 (rows >= 1 here) and is masked out
-                        v[qq] = ws.contrib[static_cast<unsigned>(q0 + qq) * ws.rows + (stored ? r : 0u)];
+                for (int st = TY * TZ / 2; st; st >>= 1) row += m.before[row + st] <= e ? st : 0;
+                const int x = set_bit(m.band[row], e - m.before[row]), at = row / TY * 6 + row % TY;   // mask row of (y - 1, z - 1)
+                float a = 0.0f;                                      // +0 + 0 stays +0: same bits as skipping
+                if constexpr (NBR) {
+#pragma unroll 1
+                    for (int dz = -1; dz <= 1; ++dz) {
+                        float v[9], hv[9][3];
+                        unsigned has = 0u;                           // bit 3 row + 2 - dx
+#pragma unroll
+                        for (int i3 = 0; i3 < 9; i3 += 3) {
+                            unsigned r[3];
+                            has |= row_sources(m, at + (1 - dz) * 6 + 2 - i3 / 3, x, last, r) << i3;
+#pragma unroll
+                            for (int dx = 0; dx < 3; ++dx) {
+                                v[i3 + dx] = (ws.contrib + static_cast<size_t>((dz + 1) * 9 + i3 + dx) * ws.rows)[r[dx]];
+                                hv[i3 + dx][0] = ws.hbar[3u * r[dx]];
+                                hv[i3 + dx][1] = ws.hbar[3u * r[dx] + 1u];
+                                hv[i3 + dx][2] = ws.hbar[3u * r[dx] + 2u];
+                            }
+                        }
+#pragma unroll
+                        for (int k = 0; k < 9; ++k) {
+                            // the source's own gradient h = sum_q w_q e_q phi_(source + e_q)
+                            const int dx = k % 3 - 1, dy = k / 3 - 1, e2 = dx * dx + dy * dy + dz * dz;
+                            const float wq = static_cast<float>(e2 == 0 ? 0 : nrm_weight<NRM>(e2));
+                            const float t = v[k] + wq * (static_cast<float>(dx) * hv[k][0] + static_cast<float>(dy) * hv[k][1] +
+                                                         static_cast<float>(dz) * hv[k][2]);
+                            a += (has >> (k / 3 * 3 + 2 - k % 3)) & 1u ? t : 0.0f;
+                        }
+                    }
+                } else {
+                    float v[27];
+                    unsigned has = 0u;                               // bit 3 row + 2 - dx
+#pragma unroll
+                    for (int i3 = 0; i3 < 27; i3 += 3) {
+                        unsigned r[3];
+                        has |= row_sources(m, at + (2 - i3 / 9) * 6 + 2 - (i3 / 3) % 3, x, last, r) << i3;
+#pragma unroll
+                        for (int dx = 0; dx < 3; ++dx)
+                            v[i3 + dx] = (ws.contrib + static_cast<size_t>(i3 + dx) * ws.rows)[r[dx]];
                     }
 #pragma unroll
-                    for (int qq = 0; qq < 9; ++qq) a += (has >> qq) & 1u ? v[qq] : 0.0f;
+                    for (int q = 0; q < 27; ++q) {
+                        const int on = __builtin_amdgcn_sbfe(static_cast<int>(has), q / 3 * 3 + 2 - q % 3, 1);   // 0 or all ones
+                        a += __uint_as_float(__float_as_uint(v[q]) & static_cast<unsigned>(on));
+                    }
                 }
-                gphi[(static_cast<int64_t>(z0 + cz) * Y + (y0 + cy)) * X + (x0 + cx)] = a;
+                m.out[row * TX + x] = a;
             }
-            if (__syncthreads_or(miss) && tid == 0) ws.over[atomicAdd(ws.counter + 2, 1u)] = static_cast<unsigned>(tile);
+            __syncthreads();
+            if (NBR && missing) {
+#pragma unroll 1
+                for (int r = cz * TY; r < (cz + 1) * TY; ++r)
+                    if ((m.band[r] >> lane) & 1ull) m.out[r * TX + lane] = __builtin_nanf("");
+                __syncwarp();
+            }
+            Four o;
+            const float4 t4 = *reinterpret_cast<const float4*>(m.out + tid * 4);
+            o.v[0] = t4.x; o.v[1] = t4.y; o.v[2] = t4.z; o.v[3] = t4.w;
+            store_four(gphi, ox, oy, oz, X, Y, Z, o);
+            __syncthreads();                                         // LDS reused by the next tile
         }
-        // the tile's cells outside the band have a zero gradient; thread t
-        // takes cells 4t .. 4t+3, row t / 16.  After the sums' loads: loads and
-        // stores share one in-order counter, so stores issued before them
-        // would be waited for with them.
-        if constexpr (ZFILL)
-            zero_cells(gphi, tile, static_cast<unsigned>(brow[tid / (TX / 4)] >> ((tid % (TX / 4)) * 4)) & 0xFu, vec,
-                       X, Y, Z, ntx, nty);
-        __syncthreads();                                             // LDS reused by the next tile
     }
 }
 
@@ -1485,56 +1650,50 @@ Workspace carve(void* base, size_t bytes, const Grid& g, bool nbr = false) {
     Workspace w;
     w.counter = reinterpret_cast<unsigned*>(p);
     w.flags = reinterpret_cast<unsigned*>(p + 256);
-    w.cbase = w.flags + nt;
-    w.mask = w.cbase + nt;
+    w.grows = w.flags + nt;
+    w.mask = w.grows + nt;
     w.prefix = w.mask + nt * kWords;
     w.items = w.prefix + nt * kWords;
-    w.tiles = w.items + nt * kMaxParts;
-    w.over = w.tiles + nt;
+    w.gitems = w.items + nt * kMaxParts;
+    w.over = w.gitems + nt;
     w.contrib = reinterpret_cast<float*>(w.over + nt);
     const size_t rows = (bytes - fixed_bytes(g)) / (nbr ? kRowBytesNbr : kRowBytes);
     const unsigned limit = nbr ? kRowLimitNbr : kRowLimit;
     w.rows = static_cast<unsigned>(rows < limit ? rows : limit);
     w.hbar = nbr ? w.contrib + static_cast<size_t>(w.rows) * kRowFloatsNbr : nullptr;
+    const int waves = scan_waves(g.ntiles), rounds = (g.ntiles + waves * kMaxGroups - 1) / (waves * kMaxGroups);
+    w.per = waves * rounds;
+    w.groups = (g.ntiles + w.per - 1) / w.per;
+    w.segs = (g.ntiles + 63) / 64;
+    w.act = w.groups + 2 * w.segs <= g.ntiles ? w.gitems + w.groups : w.counter + 16;   // (2 segments: 3 tiles and more)
     return w;
 }
 
 template <bool FWD>
 void launch_scan(const float* phi, float* out, Workspace ws, int X, int Y, int Z, const Grid& g,
                  hipStream_t st) {
-    const int nb = (g.ntiles + kThreads - 1) / kThreads;
-    hipLaunchKernelGGL(k_curv_zero, dim3(1), dim3(kThreads), 0, st, ws.counter, 0, ws.over,
-                       nb <= kOnePassBlocks ? nb : 0);
-    const bool vec = X % 4 == 0 && aligned(phi, 16) && aligned(out, 16);
-    if (vec)
-        hipLaunchKernelGGL((k_curv_scan<true, FWD>), dim3(g.ntiles), dim3(kThreads), 0, st, phi, out, ws, X, Y, Z, g.ntx, g.nty);
+    if (scan_waves(g.ntiles) == kScanWaves)
+        hipLaunchKernelGGL((k_curv_scan<FWD, kScanWaves>), dim3(ws.groups), dim3(64 * kScanWaves), 0, st, phi, out, ws,
+                           X, Y, Z, g.ntx, g.nty, g.ntiles);
     else
-        hipLaunchKernelGGL((k_curv_scan<false, FWD>), dim3(g.ntiles), dim3(kThreads), 0, st, phi, out, ws, X, Y, Z, g.ntx, g.nty);
+        hipLaunchKernelGGL((k_curv_scan<FWD, kFewScanWaves>), dim3(ws.groups), dim3(64 * kFewScanWaves), 0, st, phi,
+                           out, ws, X, Y, Z, g.ntx, g.nty, g.ntiles);
+    // (a forward's work items finish the rows in a workgroup of their launch)
+    if (!FWD) hipLaunchKernelGGL(k_curv_rows, dim3(1), dim3(64), 0, st, ws);
 }
 
 unsigned persistent_grid(int64_t items_max) {
     return static_cast<unsigned>(items_max < kPersistentBlocks ? items_max : kPersistentBlocks);
 }
 
-// gather list and contribution rows (one pass up to kOnePassBlocks workgroups
-// of tiles, else two prefix passes)
-void launch_rows(Workspace ws, const Grid& g, hipStream_t st) {
-    const int nb = (g.ntiles + kThreads - 1) / kThreads;
-    if (nb <= kOnePassBlocks) {
-        hipLaunchKernelGGL(k_curv_dilate<true>, dim3(nb), dim3(kThreads), 0, st, ws, g.ntx, g.nty, g.ntz, g.ntiles);
-    } else {
-        hipLaunchKernelGGL(k_curv_dilate<false>, dim3(nb), dim3(kThreads), 0, st, ws, g.ntx, g.nty, g.ntz, g.ntiles);
-        hipLaunchKernelGGL(k_curv_prefix, dim3(nb), dim3(kThreads), 0, st, ws, g.ntiles);
-    }
-}
-
 template <int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR = false>
-void launch_cells(const float* phi, const float* gk, float* kappa, Workspace ws, int X, int Y, int Z, const Grid& g,
+void launch_cells(const float* phi, const float* gk, float* out, Workspace ws, int X, int Y, int Z, const Grid& g,
                   hipStream_t st) {
-    const int64_t most = static_cast<int64_t>(g.ntiles) * (kMaxParts / 2);
-    const dim3 grid(static_cast<unsigned>(most < kCellBlocks ? most : kCellBlocks)), block(64);
-    hipLaunchKernelGGL((k_curv_quads<SOLVER, T, U, F, ADJ, NRM, NBR>), grid, block, 0, st, phi, gk, kappa, ws, X, Y, Z,
-                       g.ntx, g.nty);
+    // a forward's last workgroup forms the groups' first rows, a backward's first ones zero the tiles away
+    const int64_t most = static_cast<int64_t>(g.ntiles) * kTile * kLanes / 64;
+    const dim3 grid(static_cast<unsigned>(most < kCellBlocks ? most : kCellBlocks) + (ADJ ? zero_blocks(ws) : 1u)), block(64);
+    hipLaunchKernelGGL((k_curv_quads<SOLVER, T, U, F, ADJ, NRM, NBR>), grid, block, 0, st, phi, gk, out, ws, X, Y, Z,
+                       g.ntx, g.nty, g.ntiles);
 }
 
 // forward: precision picks the types, then the normal and the variant
@@ -1558,29 +1717,20 @@ void launch_fwd(int precision, int normal, bool nbr, const float* phi, float* ka
     else launch_fwd_t<SOLVER, double, double, double>(normal, nbr, phi, kappa, ws, X, Y, Z, g, st);
 }
 
-// backward: adjoint work items (rows that fit), gather list, lean gather of
-// the stored rows (independent of solver and precision), then the fallback
-// gather that recomputes the rows that did not fit
+// backward: adjoint work items (rows that fit), direct gather of the stored
+// rows (independent of solver and precision), then the fallback gather that
+// recomputes the rows that did not fit
 template <bool NBR, int NRM>
-void launch_gather(float* gp, Workspace ws, int X, int Y, int Z, const Grid& g, bool zfill, hipStream_t st) {
-    const bool vec = X % 4 == 0 && aligned(gp, 16);
-    const unsigned ngather = persistent_grid(g.ntiles);
-    if (zfill) {
-        const unsigned nbatch = static_cast<unsigned>((g.ntiles + kZeroBatch - 1) / kZeroBatch);
-        hipLaunchKernelGGL((k_curv_gather_direct<NBR, NRM, true>), dim3(ngather + nbatch), dim3(kThreads), 0, st, gp,
-                           ws, X, Y, Z, g.ntx, g.nty, g.ntz, vec, ngather);
-    } else {
-        hipLaunchKernelGGL((k_curv_gather_direct<NBR, NRM, false>), dim3(ngather), dim3(kThreads), 0, st, gp, ws, X,
-                           Y, Z, g.ntx, g.nty, g.ntz, vec, ngather);
-    }
+void launch_gather(float* gp, Workspace ws, int X, int Y, int Z, const Grid& g, hipStream_t st) {
+    hipLaunchKernelGGL((k_curv_gather_direct<NBR, NRM>), dim3(g.ntiles < kGatherBlocks ? g.ntiles : kGatherBlocks),
+                       dim3(kThreads), 0, st, gp, ws, X, Y, Z, g.ntx, g.nty, g.ntz);
 }
 
 template <int SOLVER, class T, class U, class F, int NRM>
 void launch_bwd_t(const float* phi, const float* gk, float* gp, Workspace ws, int X, int Y, int Z,
-                  const Grid& g, bool zfill, hipStream_t st) {
-    launch_rows(ws, g, st);
-    if (ws.rows > 0) launch_cells<SOLVER, T, U, F, true, NRM>(phi, gk, nullptr, ws, X, Y, Z, g, st);
-    launch_gather<false, 0>(gp, ws, X, Y, Z, g, zfill, st);
+                  const Grid& g, hipStream_t st) {
+    launch_cells<SOLVER, T, U, F, true, NRM>(phi, gk, gp, ws, X, Y, Z, g, st);
+    launch_gather<false, 0>(gp, ws, X, Y, Z, g, st);
     // usually empty.  Its registers and LDS allow one workgroup per CU, so a
     // grid of one per CU (256) runs in a single round, cheap when nothing
     // overflowed and as concurrent as any larger grid when something did
@@ -1594,35 +1744,34 @@ void launch_bwd_t(const float* phi, const float* gk, float* gp, Workspace ws, in
 // gather; there is no fallback (the entry point requires one row at least)
 template <int SOLVER, class T, class U, class F, int NRM>
 void launch_bwd_nbr_t(const float* phi, const float* gk, float* gp, Workspace ws, int X, int Y, int Z,
-                      const Grid& g, bool zfill, hipStream_t st) {
-    launch_rows(ws, g, st);
-    launch_cells<SOLVER, T, U, F, true, NRM, true>(phi, gk, nullptr, ws, X, Y, Z, g, st);
+                      const Grid& g, hipStream_t st) {
+    launch_cells<SOLVER, T, U, F, true, NRM, true>(phi, gk, gp, ws, X, Y, Z, g, st);
     hipLaunchKernelGGL(k_curv_hgather, dim3(persistent_grid(static_cast<int64_t>(g.ntiles) * kMaxParts)),
                        dim3(kThreads), 0, st, ws, X, Y, Z, g.ntx, g.nty);
-    launch_gather<true, NRM>(gp, ws, X, Y, Z, g, zfill, st);
+    launch_gather<true, NRM>(gp, ws, X, Y, Z, g, st);
 }
 
 template <int SOLVER, class T, class U, class F>
 void launch_bwd_n(int normal, bool nbr, const float* phi, const float* gk, float* gp, Workspace ws, int X, int Y,
-                  int Z, const Grid& g, bool zfill, hipStream_t st) {
+                  int Z, const Grid& g, hipStream_t st) {
     if (nbr) {
-        if (normal == kNormalCM) launch_bwd_nbr_t<SOLVER, T, U, F, kNormalCM>(phi, gk, gp, ws, X, Y, Z, g, zfill, st);
-        else launch_bwd_nbr_t<SOLVER, T, U, F, kNormalPY>(phi, gk, gp, ws, X, Y, Z, g, zfill, st);
+        if (normal == kNormalCM) launch_bwd_nbr_t<SOLVER, T, U, F, kNormalCM>(phi, gk, gp, ws, X, Y, Z, g, st);
+        else launch_bwd_nbr_t<SOLVER, T, U, F, kNormalPY>(phi, gk, gp, ws, X, Y, Z, g, st);
     } else {
-        if (normal == kNormalCM) launch_bwd_t<SOLVER, T, U, F, kNormalCM>(phi, gk, gp, ws, X, Y, Z, g, zfill, st);
-        else launch_bwd_t<SOLVER, T, U, F, kNormalPY>(phi, gk, gp, ws, X, Y, Z, g, zfill, st);
+        if (normal == kNormalCM) launch_bwd_t<SOLVER, T, U, F, kNormalCM>(phi, gk, gp, ws, X, Y, Z, g, st);
+        else launch_bwd_t<SOLVER, T, U, F, kNormalPY>(phi, gk, gp, ws, X, Y, Z, g, st);
     }
 }
 
 template <int SOLVER>
 void launch_bwd(int precision, int normal, bool nbr, const float* phi, const float* gk, float* gp, Workspace ws,
-                int X, int Y, int Z, const Grid& g, bool zfill, hipStream_t st) {
+                int X, int Y, int Z, const Grid& g, hipStream_t st) {
     if (precision == PLIC_FP32)
-        launch_bwd_n<SOLVER, float, float, float>(normal, nbr, phi, gk, gp, ws, X, Y, Z, g, zfill, st);
+        launch_bwd_n<SOLVER, float, float, float>(normal, nbr, phi, gk, gp, ws, X, Y, Z, g, st);
     else if (precision == PLIC_MIXED)
-        launch_bwd_n<SOLVER, float, double, double>(normal, nbr, phi, gk, gp, ws, X, Y, Z, g, zfill, st);
+        launch_bwd_n<SOLVER, float, double, double>(normal, nbr, phi, gk, gp, ws, X, Y, Z, g, st);
     else
-        launch_bwd_n<SOLVER, double, double, double>(normal, nbr, phi, gk, gp, ws, X, Y, Z, g, zfill, st);
+        launch_bwd_n<SOLVER, double, double, double>(normal, nbr, phi, gk, gp, ws, X, Y, Z, g, st);
 }
 
 // shared argument checks of the two entry points (the workspace's size is
@@ -1647,44 +1796,29 @@ int check_common(const float* phi, int64_t X, int64_t Y, int64_t Z, int solver, 
 // the phi and lattice of the last call that scanned into it, so that
 // plic_curvature_backward_reuse_f32 skips the scan only when they match.  The
 // table is bounded (cleared when full: a miss only costs a scan).
-// clean: the last call was a forward, whose counter reset also cleared the
-// backward's counters and row-prefix totals (nothing in the forward writes
-// them afterwards), so a backward right after it needs no reset of its own
 struct ScanRecord {
     const float* phi;
     int64_t X, Y, Z;
-    bool clean;
 };
 constexpr size_t kMaxRecords = 4096;
 std::mutex g_record_mutex;
 std::unordered_map<const void*, ScanRecord> g_records;
 
-void note_scan(const void* ws, const float* phi, int64_t X, int64_t Y, int64_t Z, bool ok, bool clean) {
+void note_scan(const void* ws, const float* phi, int64_t X, int64_t Y, int64_t Z, bool ok) {
     std::lock_guard<std::mutex> lock(g_record_mutex);
     if (!ok) {
         g_records.erase(ws);
         return;
     }
     if (g_records.size() >= kMaxRecords && g_records.find(ws) == g_records.end()) g_records.clear();
-    g_records[ws] = ScanRecord{phi, X, Y, Z, clean};
+    g_records[ws] = ScanRecord{phi, X, Y, Z};
 }
 
-// 0: no records of this phi; 1: records; 2: records and clean counters.  The
-// note turns unclean (a backward is about to use the counters).
-int take_scan(const void* ws, const float* phi, int64_t X, int64_t Y, int64_t Z) {
+bool has_scan(const void* ws, const float* phi, int64_t X, int64_t Y, int64_t Z) {
     std::lock_guard<std::mutex> lock(g_record_mutex);
     const auto it = g_records.find(ws);
-    if (it == g_records.end() || it->second.phi != phi || it->second.X != X || it->second.Y != Y ||
-        it->second.Z != Z)
-        return 0;
-    const bool clean = it->second.clean;
-    it->second.clean = false;
-    return clean ? 2 : 1;
-}
-
-bool capturing(hipStream_t st) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+    return it != g_records.end() && it->second.phi == phi && it->second.X == X && it->second.Y == Y &&
+           it->second.Z == Z;
 }
 
 // the forward launches, after validation
@@ -1700,7 +1834,7 @@ int curvature_forward(const float* phi, int64_t X, int64_t Y, int64_t Z, float* 
         default: launch_fwd<kAnalytic>(precision, normal, nbr, phi, kappa, ws, x, y, z, g, st); break;
     }
     const int rc = launch_status();
-    note_scan(workspace, phi, X, Y, Z, rc == PLIC_OK, true);
+    note_scan(workspace, phi, X, Y, Z, rc == PLIC_OK);
     return rc;
 }
 
@@ -1728,30 +1862,22 @@ int curvature_backward(const float* phi, int64_t X, int64_t Y, int64_t Z, const 
     const bool nbr = neighbour_normals != 0;
     const Workspace ws = carve(workspace, workspace_bytes, g, nbr);
     const int x = static_cast<int>(X), y = static_cast<int>(Y), z = static_cast<int>(Z);
-    const int rec = reuse ? take_scan(workspace, phi, X, Y, Z) : 0;
-    const bool scan = rec == 0;
-    if (scan) {
-        launch_scan<false>(phi, grad_phi, ws, x, y, z, g, st);
-    } else if (rec == 1 || capturing(st)) {
-        // (a captured graph may replay this backward without its forward)
-        const int nb = (g.ntiles + kThreads - 1) / kThreads;
-        hipLaunchKernelGGL(k_curv_zero, dim3(1), dim3(kThreads), 0, st, ws.counter, 1, ws.over,
-                           nb <= kOnePassBlocks ? nb : 0);
-    }
+    const bool scan = !(reuse && has_scan(workspace, phi, X, Y, Z));
+    if (scan) launch_scan<false>(phi, grad_phi, ws, x, y, z, g, st);
     switch (solver) {
-        case kSZ: launch_bwd<kSZ>(precision, normal, nbr, phi, grad_kappa, grad_phi, ws, x, y, z, g, !scan, st); break;
+        case kSZ: launch_bwd<kSZ>(precision, normal, nbr, phi, grad_kappa, grad_phi, ws, x, y, z, g, st); break;
         case kNewton:
-            launch_bwd<kNewton>(precision, normal, nbr, phi, grad_kappa, grad_phi, ws, x, y, z, g, !scan, st);
+            launch_bwd<kNewton>(precision, normal, nbr, phi, grad_kappa, grad_phi, ws, x, y, z, g, st);
             break;
         case kNested:
-            launch_bwd<kNested>(precision, normal, nbr, phi, grad_kappa, grad_phi, ws, x, y, z, g, !scan, st);
+            launch_bwd<kNested>(precision, normal, nbr, phi, grad_kappa, grad_phi, ws, x, y, z, g, st);
             break;
         default:
-            launch_bwd<kAnalytic>(precision, normal, nbr, phi, grad_kappa, grad_phi, ws, x, y, z, g, !scan, st);
+            launch_bwd<kAnalytic>(precision, normal, nbr, phi, grad_kappa, grad_phi, ws, x, y, z, g, st);
             break;
     }
     const int rc = launch_status();
-    if (scan || rc != PLIC_OK) note_scan(workspace, phi, X, Y, Z, rc == PLIC_OK, false);
+    if (scan || rc != PLIC_OK) note_scan(workspace, phi, X, Y, Z, rc == PLIC_OK);
     return rc;
 }
 
