@@ -6,7 +6,8 @@ Volume-of-Fluid Simulation Codes" (arXiv 2006.12838).
 
 All computation runs in the hand-written HIP kernels of ``libplic.so``; this
 package marshals torch tensors (device memory, the current stream) into its C
-ABI and wraps the forward/backward pairs as ``torch.autograd.Function``s.
+ABI and wraps the forward/backward pairs as autograd functions: native ones for
+plain contiguous tensors (``_native``), ``torch.autograd.Function``s for the rest.
 
     d0 = offset(n, V0, solver="sz")          # n (..., 3), V0 (...) -> d0 (...)
     V0 = volume(n, d0)
@@ -23,6 +24,7 @@ from ._lib import (  # noqa: F401  (re-exported: the C ABI by name)
     PRECISIONS,
     SOLVERS,
     VALU_OPS,
+    _enum,
     plic_bench_isolated_f32,
     plic_bench_valu,
     plic_curvature_backward_ex_f32,
@@ -54,6 +56,11 @@ from ._lib import (  # noqa: F401  (re-exported: the C ABI by name)
     plic_volume_rows_f32,
     plic_volume_rows_f64,
 )
+
+try:  # after _lib: both use the one libplic.so
+    from . import _native
+except ImportError as e:
+    raise ImportError(f"{__name__}._native is not built (run __graft_entry__.build()): {e}") from e
 
 __all__ = ["offset", "volume", "curvature", "PlicOffset", "PlicCurvature", "SOLVERS", "PAPER_SOLVERS", "PRECISIONS",
            "NORMALS",
@@ -99,44 +106,17 @@ class PlicOffset(torch.autograd.Function):
         return gx.reshape(s), gy.reshape(s), gz.reshape(s), gv.reshape(s), None, None
 
 
-def _as_rows(n, x):
-    """Whether n is one contiguous (..., 3) tensor of x's type and device, a row
-    per element of a contiguous x: such normals go to the kernels as they are
-    (three strided columns would each be copied first).  Anything else
-    (broadcast shapes, views, tuples) takes the general path."""
-    plain = (torch.Tensor, torch.nn.Parameter)
-    return type(n) in plain and type(x) in plain and n.is_cuda and n.device == x.device and n.dtype is x.dtype and \
-        n.dtype in (torch.float32, torch.float64) and n.dim() > 0 and n.shape == (*x.shape, 3) and \
-        n.is_contiguous() and x.is_contiguous() and not n.is_neg() and not x.is_neg()
+def _native_may():
+    """Whether the native functions may be tried: not under a function
+    transform, a trace or a dispatch mode, which the Python path meets (or
+    refuses) as ever."""
+    return not (torch._C._are_functorch_transforms_active() or torch._C._len_torch_dispatch_stack()
+                or torch._C._get_tracing_state() is not None or torch.compiler.is_compiling())
 
 
-class _PlicOffsetRows(torch.autograd.Function):
-    """PlicOffset for normals as rows.  The backward works on a copy of n that
-    the forward's kernel writes beside d0, so n may change in between."""
-
-    @staticmethod
-    def forward(ctx, n, V0, solver, precision, grad_mode):
-        d0 = torch.empty_like(V0)
-        keep = torch.empty_like(n) if grad_mode and any(ctx.needs_input_grad) else None
-        if V0.dtype == torch.float64:
-            plic_offset_rows_f64(n, V0, d0, keep, solver)
-        else:
-            plic_offset_rows_f32(n, V0, d0, keep, solver, precision)
-        if keep is not None:
-            ctx.save_for_backward(keep, V0)
-            ctx.solver, ctx.precision = solver, precision
-        return d0
-
-    @staticmethod
-    def backward(ctx, grad_d0):
-        n, V0 = ctx.saved_tensors
-        g = grad_d0.contiguous()
-        gn, gv = torch.empty_like(n), torch.empty_like(V0)
-        if V0.dtype == torch.float64:
-            plic_offset_backward_rows_f64(n, V0, g, gn, gv, ctx.solver)
-        else:
-            plic_offset_backward_rows_f32(n, V0, g, gn, gv, ctx.solver, ctx.precision)
-        return gn, gv, None, None, None
+def _precision(t, precision):
+    """The precision's number; float64 tensors compute in FP64 whatever it says."""
+    return 0 if t.dtype == torch.float64 else _enum(PRECISIONS, precision, "precision")
 
 
 def offset(n, V0, solver: str = "sz", precision: str = "fp32"):
@@ -147,19 +127,22 @@ def offset(n, V0, solver: str = "sz", precision: str = "fp32"):
     FP64.  ``solver``: "analytic", "sz", "newton", "nested", or "sz_kawano" (the
     unoptimized SZ comparison variant: NaN for an axis normal at V0 in {0, 1},
     not held to the 1e-5 bound)."""
-    if _as_rows(n, V0):
-        return _PlicOffsetRows.apply(n, V0, solver, precision, torch.is_grad_enabled())
+    if isinstance(V0, torch.Tensor) and _native_may():
+        opts = _enum(SOLVERS, solver, "solver"), _precision(V0, precision)
+        d0 = _native.offset_rows(n, V0, *opts) if isinstance(n, torch.Tensor) else \
+            _native.offset_parts(*n, V0, *opts) if isinstance(n, (tuple, list)) and len(n) == 3 else None
+        if d0 is not None:
+            return d0
     nx, ny, nz = _split_normal(n)
     return PlicOffset.apply(nx, ny, nz, V0, solver, precision)
 
 
 def volume(n, d0, precision: str = "fp32"):
     """Forward volume V0(n, d0) (no gradient)."""
-    if _as_rows(n, d0):
-        n, d0 = n.detach(), d0.detach()
-        out = torch.empty_like(d0)
-        return plic_volume_rows_f64(n, d0, out) if d0.dtype == torch.float64 else \
-            plic_volume_rows_f32(n, d0, out, precision)
+    if isinstance(n, torch.Tensor) and isinstance(d0, torch.Tensor) and _native_may():
+        V0 = _native.volume_rows(n, d0, _precision(d0, precision))
+        if V0 is not None:
+            return V0
     nx, ny, nz = _split_normal(n)
     shape = d0.shape
     nx, ny, nz, d0 = (t.detach().contiguous().reshape(-1) for t in torch.broadcast_tensors(nx, ny, nz, d0))
@@ -206,4 +189,9 @@ def curvature(phi, solver: str = "analytic", precision: str = "mixed", normal: s
     0 off the interface, +1/R for a fluid sphere of radius R.  normal: "py"
     (Parker-Youngs) or "cm" (centre of mass); neighbour_normals: each interface
     neighbour's PLIC plane from its own normal."""
+    if _native_may():
+        kappa = _native.curvature(phi, _enum(SOLVERS, solver, "solver"), _enum(PRECISIONS, precision, "precision"),
+                                  _enum(NORMALS, normal, "normal"), bool(neighbour_normals))
+        if kappa is not None:
+            return kappa
     return PlicCurvature.apply(phi, solver, precision, normal, neighbour_normals)

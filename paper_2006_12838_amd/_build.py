@@ -1,4 +1,5 @@
-"""Builds libplic.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc."""
+"""Builds libplic.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc, and
+_native.so (the torch functions over that ABI, host code) with the host compiler."""
 from __future__ import annotations
 
 import os
@@ -8,6 +9,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libplic.so")
+NATIVE = os.path.join(PKG, "_native.so")
 BUILD = os.path.join(os.path.dirname(PKG), "_build")
 SOURCES = ["plic_offset.hip", "plic_curvature.hip", "plic_bench.hip", "plic_abi.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -17,9 +19,32 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
+def _native_object():
+    """The command that compiles plic_torch.cpp, and what links it."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    obj = os.path.join(BUILD, "plic_torch.o")
+    # packaged headers as system headers: their warnings are not ours
+    inc = [f for p in cpp_extension.include_paths() + [sysconfig.get_paths()["include"], "/opt/rocm/include"]
+           for f in ("-isystem", p)]
+    compile_ = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+                f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+                "-c", os.path.join(CSRC, "plic_torch.cpp"), "-o", obj]
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    link = [os.environ.get("CXX", "g++"), "-shared", "-fPIC", obj, "-L" + PKG, "-lplic", "-L" + lib, "-ltorch_python",
+            "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", "-Wl,-rpath," + lib]
+    return compile_, link
+
+
 def build_library(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    procs = []
+    native, native_link = _native_object()
+    if verbose:
+        print(" ".join(native), flush=True)
+    procs = [("plic_torch.cpp", subprocess.Popen(native, stdout=subprocess.PIPE, stderr=subprocess.STDOUT))]
     objs = []
     for src in SOURCES:
         obj = os.path.join(BUILD, src.rsplit(".", 1)[0] + ".o")
@@ -48,6 +73,12 @@ def build_library(verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, LIB)
+    tmp = NATIVE + ".tmp"
+    cmd = [*native_link, "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, NATIVE)
     return LIB
 
 

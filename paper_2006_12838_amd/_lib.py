@@ -148,7 +148,8 @@ def _ptr(t: torch.Tensor, dtype, n: int, what: str):
 
 
 def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    # the handle of torch.cuda.current_stream(t.device), without making the object
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(t.device.index))
 
 
 def _enum(table, value, what):
