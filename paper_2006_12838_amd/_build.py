@@ -16,7 +16,11 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 # Packed FP32 (v_pk_*_f32) is disabled for all device code.
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # keep the execution mask's restore at the end of each inner branch:
+         # without it, register reloads that the allocator puts there run for the
+         # branch's lanes only, and the others go on with a stale value
+         "-Xarch_device", "-mllvm=-amdgpu-remove-redundant-endcf=0"]
 
 
 def _native_object():

@@ -8,8 +8,9 @@
 //     writes the zero result everywhere and records each tile's interface
 //     bitmask (0 < phi < 1, away from the outer layer) with its prefix counts,
 //     and, per group, a list of work items (8 interface cells of a tile each);
-//  2. the work items, each interface cell on a group of 4 lanes: the wavefront
-//     finds its items through the groups' counts, a group finds its cell from
+//  2. the work items, each interface cell on a group of 4 lanes (16 where items
+//     are few): the wavefront finds its items through the groups' counts, a
+//     group finds its cell from
 //     the bitmask, stages its neighbourhood in LDS, and its lanes share out the
 //     interface neighbours (their PLIC offsets and rows of the normal
 //     equations).  One workgroup turns the groups' cell counts into first rows
@@ -194,27 +195,40 @@ __device__ __forceinline__ void gradient27(const float* __restrict__ s, int c, i
 // times enlarged.  Where a pivot falls below kSteady of the largest diagonal
 // entry, the sums are formed again over the 16 pairs of neighbours (l, l + 16)
 // of the 26 in order, so that they do not depend on how the lanes shared out
-// the list (one such cell moved by 5e-5 of the spray's whole gradient).
+// the list (one such cell moved by 5e-5 of the spray's whole gradient).  Those
+// cells are done again four at a time on 16 lanes each: on their own 4 lanes,
+// whose wavefront waits for them, a 100 x 98 x 99 lattice's forward and backward
+// took 47.2 us instead of 44.0, a 120 x 118 x 119 one's 44.7 instead of 42.6.
 // ---------------------------------------------------------------------------
 constexpr int kRowFloatsH = 26 * 3;             // a cell's adjoints of its neighbours' own gradients
 constexpr unsigned kCentre = 1u << 13;
 constexpr int kLanes = 4;                       // lanes per interface cell
+constexpr int kWideLanes = 16;                  // where cells are few
 constexpr int kWaveCells = 64 / kLanes;         // cells of a wavefront
 constexpr int kRounds = (27 + kLanes - 1) / kLanes;
 
 // scratch of one wavefront: the offsets of each lane's entries by round; the
 // neighbour offsets (x, y, z) with their weights in the gradient (taken apart
-// from q each time, they were a twelfth of the instructions); with ADJ, the gradients of the points' fill levels by neighbour, and the centre's
+// from q each time, they were a twelfth of the instructions); with ADJ, the
+// gradients of the points' fill levels by neighbour, and the centre's
 // own derivatives
-template <class T, bool ADJ> struct CellLds {
+template <class T, class F> union OffsetLds {
     T D[kRounds][64];
+    struct {                                    // a call with 16 lanes per cell has two rounds of offsets,
+        T D[2][64];                             // and room for two entries' terms of each cell's sums
+        F terms[64 / kWideLanes][2 * 20];
+    } wide;
+};
+template <class T, class F, bool ADJ> struct CellLds {
+    OffsetLds<T, F> o;
     float4 e[27];
 };
-template <class T> struct CellLds<T, true> {
-    T D[kRounds][64];
+template <class T, class F> struct CellLds<T, F, true> {
+    OffsetLds<T, F> o;
     float4 e[27];
     T pb[kWaveCells][27];
     T cen[kWaveCells][4];
+    int4 at[kWaveCells];                        // place and row (kept here, not in registers, for a second call)
 };
 
 template <int NRM, class Lds> __device__ __forceinline__ void init_cells(Lds& L, int lane) {
@@ -235,13 +249,36 @@ template <int CTRL> __device__ __forceinline__ double quad_move(double x) {
 template <int CTRL> __device__ __forceinline__ unsigned quad_move(unsigned x) {
     return static_cast<unsigned>(__builtin_amdgcn_mov_dpp(static_cast<int>(x), CTRL, 0xF, 0xF, true));
 }
-// quad_perm [1,0,3,2] and [2,3,0,1]; lane i of 8 to lane 7 - i
-constexpr int kSwap1 = 0xB1, kSwap2 = 0x4E, kHalfMirror = 0x141;
+// quad_perm [1,0,3,2] and [2,3,0,1]; each row of 16 turned up by 4 and by 8
+// lanes; the row's last lane to all of it; lane i of 8 to lane 7 - i
+constexpr int kSwap1 = 0xB1, kSwap2 = 0x4E, kTurn4 = 0x124, kTurn8 = 0x128, kLast = 0x15F, kHalfMirror = 0x141;
 
-// sum over the 4 lanes of the group, the same bits on each
-template <class F> __device__ __forceinline__ F group_sum(F x) {
+// Sums over a group's entries, the same bits for 4 lanes and for 16: partial
+// sum j runs over the entries j, j + 4, j + 8, ... in that order.  With 4 lanes
+// it is lane j's own.  With 16, lane j + 4 r has entry j + 4 r of each run of 16,
+// and the partial sums go around the row: added to by the entry of the lane
+// they are on, then turned to the next four lanes.  add() adds this lane's entry
+// (zeros where it has none) to acc; more: there is another run of 16.
+template <int LANES, int N, class F, class Add>
+__device__ __forceinline__ void add_entries(F (&acc)[N], bool more, Add add) {
+    add();
+    if constexpr (LANES == kWideLanes) {
+        auto turn = [&] {
+#pragma unroll
+            for (int i = 0; i < N; ++i) acc[i] = quad_move<kTurn4>(acc[i]);
+        };
+#pragma unroll
+        for (int r = 1; r < 4; ++r) { turn(); add(); }
+        if (more) turn();                       // uniform per group
+    }
+}
+// the four partial sums together, on every lane of the group (of 16: those of
+// the last four lanes, which the last entries were added to)
+template <int LANES, class F> __device__ __forceinline__ F group_sum(F x) {
     x += quad_move<kSwap1>(x);
-    return x + quad_move<kSwap2>(x);
+    x += quad_move<kSwap2>(x);
+    if constexpr (LANES == kWideLanes) x = quad_move<kLast>(x);
+    return x;
 }
 
 // inclusive sums over the lanes below, in each half of the wavefront or all of
@@ -264,17 +301,47 @@ __device__ __forceinline__ unsigned from_lane(unsigned x, int lane) {   // lane:
     return static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(x), lane));
 }
 
-// the list's entries of lane j (the first is the lowest set bit), and the next
-__device__ __forceinline__ unsigned first_entries(unsigned list, int j) {
+// the k-th set bit of word (k below its count)
+__device__ __forceinline__ int nth_bit(unsigned word, int k) {
+    int bit = 0;
 #pragma unroll
-    for (int i = 0; i < kLanes - 1; ++i) list = i < j ? list & (list - 1u) : list;
-    return list;
+    for (int st = 16; st; st >>= 1) {
+        const int low = __popc(word & ((1u << st) - 1u));
+        const bool up = k >= low;
+        k -= up ? low : 0;
+        bit += up ? st : 0;
+        word >>= up ? st : 0;
+    }
+    return bit;
 }
-__device__ __forceinline__ unsigned next_entries(unsigned list) {
+
+// lane j's entries of the list, one after the other: j, j + LANES, ...
+template <int LANES> struct Entries;
+template <> struct Entries<kLanes> {
+    unsigned rest;
+    __device__ __forceinline__ Entries(unsigned list, int j) : rest(list) {
 #pragma unroll
-    for (int i = 0; i < kLanes; ++i) list &= list - 1u;
-    return list;
-}
+        for (int i = 0; i < kLanes - 1; ++i) rest = i < j ? rest & (rest - 1u) : rest;
+    }
+    __device__ __forceinline__ bool any() const { return rest != 0u; }      // this lane has one
+    __device__ __forceinline__ bool has() const { return true; }
+    __device__ __forceinline__ bool more() const { return false; }
+    __device__ __forceinline__ int q() const { return __ffs(static_cast<int>(rest)) - 1; }
+    __device__ __forceinline__ void next() {
+#pragma unroll
+        for (int i = 0; i < kLanes; ++i) rest &= rest - 1u;
+    }
+};
+template <> struct Entries<kWideLanes> {
+    unsigned list;
+    int e, j;
+    __device__ __forceinline__ Entries(unsigned l, int lane) : list(l), e(lane), j(lane) {}
+    __device__ __forceinline__ bool any() const { return e - j < __popc(list); }            // a lane of the group has one
+    __device__ __forceinline__ bool has() const { return e < __popc(list); }
+    __device__ __forceinline__ bool more() const { return e - j + kWideLanes < __popc(list); }
+    __device__ __forceinline__ int q() const { return has() ? nth_bit(list, e) : 13; }
+    __device__ __forceinline__ void next() { e += kWideLanes; }
+};
 
 // neighbour q's point (x, y in the frame, z along n), centre normal
 template <class T, class F>
@@ -327,61 +394,68 @@ __device__ __forceinline__ void cell_point_own(const float4& e, T D, T D0, const
 }
 
 // The fit's 20 sums over the pairs of neighbours (l, l + 16) of the 26 in
-// order, for the few cells that need them so.  Lane j of each four forms up to
-// six, its factor times each of (x^2, y^2, xy, x, y, z): factors x^2, y^2, xy
-// and x; lane 2, whose first two are lanes 0's and 1's, takes y y and y z.
+// order, for the few cells that need them so, on 16 lanes: lane l has the
+// terms of pair l.  They go through LDS, two pairs at a time, and each lane adds up one
+// or two of the 20 sums.
 template <class F, class Point>
-__device__ __forceinline__ void ordered_sums(int j, unsigned mask, unsigned list, Point point, F (&sum)[20]) {
-    F acc[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) acc[k] = F(0);
+__device__ __forceinline__ void ordered_sums(int l, unsigned mask, unsigned list, Point point, F (&terms)[2 * 20],
+                                             F (&sum)[20]) {
+    const int qa = l < 13 ? l : l + 1, qb = min(l + 17, 26);
+    F xa = F(0), ya = F(0), za = F(0), xb = F(0), yb = F(0), zb = F(0);
+    if ((mask >> qa) & 1u) point(qa, __popc(list & ((1u << qa) - 1u)), xa, ya, za);
+    if (l < 10 && ((mask >> qb) & 1u)) point(qb, __popc(list & ((1u << qb) - 1u)), xb, yb, zb);
+    const int i0 = l, i1 = min(16 + l, 19);
+    F acc0 = F(0), acc1 = F(0);
+    __syncwarp();
 #pragma unroll 1
-    for (int l = 0; l < 16; ++l) {
-        const int qa = l < 13 ? l : l + 1, qb = min(l + 17, 26);
-        const bool ia = (mask >> qa) & 1u, ib = l < 10 && ((mask >> qb) & 1u);
-        if (!ia && !ib) continue;
-        F u[2][6], v[2][6];                       // factors of the six sums, of each of the pair
+    for (int b = 0; b < 8; ++b) {
+        if (l / 2 == b) {
+            F* t = terms + (l % 2) * 20;
+            const F Qa[5] = {xa * xa, ya * ya, xa * ya, xa, ya}, Qb[5] = {xb * xb, yb * yb, xb * yb, xb, yb};
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int q = h ? qb : qa;
-            F x = F(0), y = F(0), z = F(0);
-            if (h ? ib : ia) point(q, __popc(list & ((1u << q) - 1u)), x, y, z);
-            const F f = j == 0 ? x * x : (j == 1 ? y * y : (j == 2 ? x * y : x));
-            u[h][0] = j == 2 ? y : f;
-            u[h][1] = u[h][0];
-            u[h][2] = u[h][3] = u[h][4] = u[h][5] = f;
-            v[h][0] = j == 2 ? y : x * x;
-            v[h][1] = j == 2 ? z : y * y;
-            v[h][2] = x * y; v[h][3] = x; v[h][4] = y; v[h][5] = z;
-        }
+            for (int i = 0; i < 5; ++i) {
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const F t = u[0][k] * v[0][k] + u[1][k] * v[1][k];
-            acc[k] += t;
+                for (int k = 0; k <= i; ++k) t[tri(i, k)] = Qa[i] * Qa[k] + Qb[i] * Qb[k];
+                t[15 + i] = za * Qa[i] + zb * Qb[i];
+            }
         }
+        __syncwarp();
+        acc0 += terms[i0]; acc0 += terms[20 + i0];
+        acc1 += terms[i1]; acc1 += terms[20 + i1];
+        __syncwarp();
     }
-    auto from = [&](auto lane, int k) { return quad_move<lane.value * 0x55>(acc[k]); };   // quad_perm: one lane to all
-    const std::integral_constant<int, 0> l0;
-    const std::integral_constant<int, 1> l1;
-    const std::integral_constant<int, 2> l2;
-    const std::integral_constant<int, 3> l3;
+    terms[i0] = acc0;
+    terms[i1] = acc1;
+    __syncwarp();
 #pragma unroll
-    for (int i = 0; i < 5; ++i) sum[tri(i, 0)] = from(l0, i);
+    for (int k = 0; k < 20; ++k) sum[k] = terms[k];
+    __syncwarp();
+}
+
+// The groups that were not done, four of the wavefront at a time on 16 lanes
+// each: again(src) with the first lane of such a group, or -1 where none is
+// left.  Every lane of the wavefront must call it.
+template <int LANES, class Again>
+__device__ __forceinline__ void redo_groups(bool done, int lane, Again again) {
+    constexpr unsigned long long kFirst = LANES == kLanes ? 0x1111111111111111ull : 0x0001000100010001ull;
+    for (unsigned long long left = __ballot(!done) & kFirst; left;) {
+        int src = -1;
 #pragma unroll
-    for (int i = 1; i < 5; ++i) sum[tri(i, 1)] = from(l1, i);
-#pragma unroll
-    for (int i = 2; i < 5; ++i) sum[tri(i, 2)] = from(l2, i);
-    sum[tri(3, 3)] = from(l3, 3);
-    sum[tri(4, 3)] = from(l3, 4);
-    sum[tri(4, 4)] = from(l2, 0);
-    sum[15] = from(l0, 5); sum[16] = from(l1, 5); sum[17] = from(l2, 5); sum[18] = from(l3, 5); sum[19] = from(l2, 1);
+        for (int k = 0; k < 64 / kWideLanes; ++k, left &= left - 1ull)
+            if (lane / kWideLanes == k) src = __ffsll(left) - 1;
+        __syncwarp();
+        again(src);
+        __syncwarp();
+    }
 }
 
 // s: LDS fill levels, c: centre index, sy/sz: LDS strides, lane: lane in the
-// wavefront.  Every lane of the group must call it.  False, with nothing
-// written, when the fit is ill-conditioned and the sums were not ORDERED: the
-// caller then calls it again with ORDERED (from the fill levels, so that nothing
-// is kept in registers for it).  kappa: the same bits on every lane.  With ADJ,
+// wavefront, LANES per cell.  Every lane of the group must call it.  False, with
+// nothing written, when the fit is ill-conditioned and the sums were not
+// ORDERED: the caller then calls it again with ORDERED (from the fill levels:
+// with both kinds of sums in one call, what had to be kept in registers for the
+// second made the first slower, 38.4 -> 42.0 us for a 220 x 218 x 219 forward).
+// kappa: the same bits on every lane.  With ADJ,
 // also writes out[q * ostride] = gk * d kappa / d phi_q (q = 0..26), with the
 // interface mask, the PLIC cases and the active fit parameters held fixed.
 // With NBR (neighbour normals: each interface neighbour's point from its own
@@ -389,35 +463,40 @@ __device__ __forceinline__ void ordered_sums(int j, unsigned mask, unsigned list
 // outh[3t .. 3t+2] = gk * d kappa / d h of neighbour slot t (the 26 offsets
 // other than the centre; zero where the neighbour keeps the centre normal);
 // spreading that over the neighbour's 3^3 is left to the gathers.
-template <bool ORDERED, int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR = false>
+template <int LANES, bool ORDERED, int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR = false>
 __device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, int sy, int sz, int lane,
                                           float gk, float* __restrict__ out, unsigned ostride,
-                                          float* __restrict__ outh, CellLds<T, ADJ>& L, float& kappa,
+                                          float* __restrict__ outh, CellLds<T, F, ADJ>& L, float& kappa,
                                           const Place& where = {}) {
     using mt = M<T>;
-    const int j = lane % kLanes, cell = lane / kLanes;
+    constexpr int kPasses = (27 + LANES - 1) / LANES;
+    const int j = lane % LANES, cell = lane / LANES;
     T gx, gy, gz;
     gradient27<NRM, T>(s, c, sy, sz, gx, gy, gz);
     // (strides 3 and 9, known at compile time: the 27 levels are in a row)
     auto at = [&](int q) { return sy == 3 && sz == 9 ? c - 13 + q : c + q_dz(q) * sz + q_dy(q) * sy + q_dx(q); };
-    // interface mask of the 27 cells, 7 tests per lane
+    // interface mask of the 27 cells, 7 tests per lane (2 with 16 lanes)
     unsigned mask = 0u;
 #pragma unroll
-    for (int k = 0; k < kRounds; ++k) {
-        const int q = j + k * kLanes;
-        if (is_iface(s[at(min(q, 26))]) && q < 27) mask |= 1u << (k * kLanes);
+    for (int k = 0; k < kPasses; ++k) {
+        const int q = j + k * LANES;
+        if (is_iface(s[at(min(q, 26))]) && q < 27) mask |= 1u << (k * LANES);
     }
     mask <<= j;
     mask |= quad_move<kSwap1>(mask);
     mask |= quad_move<kSwap2>(mask);
+    if constexpr (LANES == kWideLanes) {
+        mask |= quad_move<kTurn4>(mask);
+        mask |= quad_move<kTurn8>(mask);
+    }
     mask &= ~kCentre;
     const unsigned list = mask | kCentre;
     const T gn2 = gx * gx + gy * gy + gz * gz;
     if (!(gn2 >= T(1e-24))) {                   // no usable normal: kappa = 0 (uniform per group)
         if constexpr (ADJ) {
-            for (int q = j; q < 27; q += kLanes) out[static_cast<unsigned>(q) * ostride] = 0.0f;
+            for (int q = j; q < 27; q += LANES) out[static_cast<unsigned>(q) * ostride] = 0.0f;
             if constexpr (NBR)
-                for (int t = j; t < 78; t += kLanes) outh[t] = 0.0f;
+                for (int t = j; t < 78; t += LANES) outh[t] = 0.0f;
         }
         kappa = 0.0f;
         return true;
@@ -440,27 +519,27 @@ __device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, in
     // each interface neighbour with its own)
     int k = 0;
 #pragma unroll 1
-    for (unsigned m = first_entries(list, j); m; m = next_entries(m), ++k) {
-        const int q = __ffs(static_cast<int>(m)) - 1;
+    for (Entries<LANES> en(list, j); en.any() && en.has(); en.next(), ++k) {
+        const int q = en.q();
         const T p = T(s[at(q)]);
         if constexpr (NBR) {
             T mq[3] = {n0, n1, n2}, ih;
             bool own = false;
             if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, where, mq, own, ih);
-            L.D[k][lane] = offset<SOLVER, T, U>(mq[0], mq[1], mq[2], p);
+            L.o.D[k][lane] = offset<SOLVER, T, U>(mq[0], mq[1], mq[2], p);
         } else {
-            L.D[k][lane] = offset<SOLVER, T, U>(n0, n1, n2, p);
+            L.o.D[k][lane] = offset<SOLVER, T, U>(n0, n1, n2, p);
         }
     }
     __syncwarp();
     const int c13 = __popc(mask & (kCentre - 1u));          // the centre's place in the list
-    const T D0 = L.D[c13 / kLanes][(lane & ~(kLanes - 1)) + c13 % kLanes];
+    const T D0 = L.o.D[c13 / LANES][(lane & ~(LANES - 1)) + c13 % LANES];
     F sum[20];
 #pragma unroll
     for (int i = 0; i < 20; ++i) sum[i] = F(0);
     // the point of neighbour q, whose offset is entry e of the list
     auto point = [&](int q, int e, F& x, F& y, F& z) {
-        const T D = L.D[e / kLanes][(lane & ~(kLanes - 1)) + e % kLanes];
+        const T D = L.o.D[e / LANES][(lane & ~(LANES - 1)) + e % LANES];
         if constexpr (NBR) {
             T mq[3] = {n0, n1, n2}, ih;
             bool own = false;
@@ -473,23 +552,26 @@ __device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, in
     if constexpr (!ORDERED) {
         int e = j;
 #pragma unroll 1
-        for (unsigned m = first_entries(list, j); m; m = next_entries(m), e += kLanes) {
-            const int q = __ffs(static_cast<int>(m)) - 1;
-            if (q == 13) continue;
-            F x, y, z;
-            point(q, e, x, y, z);
+        for (Entries<LANES> en(list, j); en.any(); en.next(), e += LANES) {
+            const int q = en.q();
+            if (LANES == kLanes && q == 13) continue;
+            F x = F(0), y = F(0), z = F(0);
+            if (LANES == kLanes || q != 13) point(q, e, x, y, z);
             const F Q[5] = {x * x, y * y, x * y, x, y};
+            add_entries<LANES>(sum, en.more(), [&] {
 #pragma unroll
-            for (int i = 0; i < 5; ++i) {
+                for (int i = 0; i < 5; ++i) {
 #pragma unroll
-                for (int l = 0; l <= i; ++l) sum[tri(i, l)] += Q[i] * Q[l];
-                sum[15 + i] += z * Q[i];
-            }
+                    for (int l = 0; l <= i; ++l) sum[tri(i, l)] += Q[i] * Q[l];
+                    sum[15 + i] += z * Q[i];
+                }
+            });
         }
 #pragma unroll
-        for (int i = 0; i < 20; ++i) sum[i] = group_sum(sum[i]);
+        for (int i = 0; i < 20; ++i) sum[i] = group_sum<LANES>(sum[i]);
     } else {
-        ordered_sums<F>(j % 4, mask, list, point, sum);
+        static_assert(LANES == kWideLanes, "lane l has pair l");
+        ordered_sums<F>(j, mask, list, point, L.o.wide.terms[cell], sum);
     }
     const int npts = __popc(mask);
     F m[5][5], b[5];
@@ -530,68 +612,78 @@ __device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, in
         for (int i = 0; i < 10; ++i) arow[i] = F(0);
         k = 0;
 #pragma unroll 1
-        for (unsigned mm = first_entries(list, j); mm; mm = next_entries(mm), ++k) {
-            const int q = __ffs(static_cast<int>(mm)) - 1;
-            const T p = T(s[at(q)]), D = L.D[k][lane];
-            T mq[3] = {n0, n1, n2}, ih = T(0);
-            bool own = false;
-            if constexpr (NBR)
-                if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, where, mq, own, ih);
-            T cq[3];
-            const T dv = offset_grad_from_d0<T>(mq[0], mq[1], mq[2], p, D, cq);   // 1/A, centroid
-            if (q == 13) {
-                L.cen[cell][0] = cq[0]; L.cen[cell][1] = cq[1]; L.cen[cell][2] = cq[2]; L.cen[cell][3] = dv;
-                continue;
-            }
-            F x, y, z;
-            if constexpr (NBR) cell_point_own<T, F>(L.e[q], D, D0, mq, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
-            else cell_point<T, F>(L.e[q], D, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
-            const F Q[5] = {x * x, y * y, x * y, x, y};
-            F zq = F(0), aQ = F(0);
+        for (Entries<LANES> en(list, j); en.any(); en.next(), ++k) {
+            const int q = en.q();
+            T xbar = T(0), ybar = T(0), zt = T(0);              // the point's adjoint and what it multiplies
+            T v0 = T(0), v1 = T(0), v2 = T(0), w0 = T(0), w1 = T(0), w2 = T(0);
+            if (LANES == kLanes || en.has()) {
+                const T p = T(s[at(q)]), D = L.o.D[k][lane];
+                T mq[3] = {n0, n1, n2}, ih = T(0);
+                bool own = false;
+                if constexpr (NBR)
+                    if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, where, mq, own, ih);
+                T cq[3];
+                const T dv = offset_grad_from_d0<T>(mq[0], mq[1], mq[2], p, D, cq);   // 1/A, centroid
+                if (q == 13) {
+                    L.cen[cell][0] = cq[0]; L.cen[cell][1] = cq[1]; L.cen[cell][2] = cq[2]; L.cen[cell][3] = dv;
+                    if constexpr (LANES == kLanes) continue;
+                } else {
+                    F x, y, z;
+                    if constexpr (NBR) cell_point_own<T, F>(L.e[q], D, D0, mq, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
+                    else cell_point<T, F>(L.e[q], D, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
+                    const F Q[5] = {x * x, y * y, x * y, x, y};
+                    F zq = F(0), aQ = F(0);
 #pragma unroll
-            for (int i = 0; i < 5; ++i) { zq += lam[i] * Q[i]; aQ += a[i] * Q[i]; }
-            F Qbar[5];
+                    for (int i = 0; i < 5; ++i) { zq += lam[i] * Q[i]; aQ += a[i] * Q[i]; }
+                    F Qbar[5];
 #pragma unroll
-            for (int i = 0; i < 5; ++i) Qbar[i] = lam[i] * (z - aQ) - a[i] * zq;
-            const T xbar = T(F(2) * x * Qbar[0] + y * Qbar[2] + Qbar[3]);
-            const T ybar = T(F(2) * y * Qbar[1] + x * Qbar[2] + Qbar[4]);
-            const T zt = T(zq);
-            const T ex = T(L.e[q].x), ey = T(L.e[q].y), ez = T(L.e[q].z);
-            if constexpr (NBR) {
-                // x = P.b_x, y = P.b_y, z = P.n with P = e + D m - D0 n, D = d0(phi_q, m)
-                const T P0 = ex + D * mq[0] - D0 * n0, P1 = ey + D * mq[1] - D0 * n1, P2 = ez + D * mq[2] - D0 * n2;
-                const T Pb0 = xbar * bx0 + ybar * by0 + zt * n0;
-                const T Pb1 = xbar * bx1 + ybar * by1 + zt * n1;
-                const T Pb2 = xbar * bx2 + ybar * by2 + zt * n2;
-                const T Dbar = Pb0 * mq[0] + Pb1 * mq[1] + Pb2 * mq[2];
-                const T mb0 = D * Pb0 + Dbar * cq[0], mb1 = D * Pb1 + Dbar * cq[1], mb2 = D * Pb2 + Dbar * cq[2];
-                L.pb[cell][q] = Dbar * dv;
-                arow[0] += F(xbar * P0); arow[1] += F(xbar * P1); arow[2] += F(xbar * P2);
-                arow[3] += F(ybar * P0); arow[4] += F(ybar * P1); arow[5] += F(ybar * P2);
-                // n enters through z = P.n, through -D0 n in P, and as m where the neighbour keeps it
-                arow[6] += F(zt * P0 - D0 * Pb0 + (own ? T(0) : mb0));
-                arow[7] += F(zt * P1 - D0 * Pb1 + (own ? T(0) : mb1));
-                arow[8] += F(zt * P2 - D0 * Pb2 + (own ? T(0) : mb2));
-                arow[9] += F(zt);
-                // m = -h / |h|: the adjoint of h, gathered later at that neighbour
-                // and spread over its 3^3 by the gradient's weights
-                const T md = mq[0] * mb0 + mq[1] * mb1 + mq[2] * mb2;
-                float* o = outh + 3 * (q < 13 ? q : q - 1);
-                o[0] = own ? float(-(mb0 - mq[0] * md) * ih) : 0.0f;
-                o[1] = own ? float(-(mb1 - mq[1] * md) * ih) : 0.0f;
-                o[2] = own ? float(-(mb2 - mq[2] * md) * ih) : 0.0f;
-            } else {
-                L.pb[cell][q] = zt * dv;
-                arow[0] += F(xbar * ex); arow[1] += F(xbar * ey); arow[2] += F(xbar * ez);
-                arow[3] += F(ybar * ex); arow[4] += F(ybar * ey); arow[5] += F(ybar * ez);
-                arow[6] += F(zt * (ex + cq[0])); arow[7] += F(zt * (ey + cq[1])); arow[8] += F(zt * (ez + cq[2]));
-                arow[9] += F(zt);
+                    for (int i = 0; i < 5; ++i) Qbar[i] = lam[i] * (z - aQ) - a[i] * zq;
+                    xbar = T(F(2) * x * Qbar[0] + y * Qbar[2] + Qbar[3]);
+                    ybar = T(F(2) * y * Qbar[1] + x * Qbar[2] + Qbar[4]);
+                    zt = T(zq);
+                    const T ex = T(L.e[q].x), ey = T(L.e[q].y), ez = T(L.e[q].z);
+                    if constexpr (NBR) {
+                        // x = P.b_x, y = P.b_y, z = P.n with P = e + D m - D0 n, D = d0(phi_q, m)
+                        v0 = ex + D * mq[0] - D0 * n0; v1 = ey + D * mq[1] - D0 * n1; v2 = ez + D * mq[2] - D0 * n2;
+                        const T Pb0 = xbar * bx0 + ybar * by0 + zt * n0;
+                        const T Pb1 = xbar * bx1 + ybar * by1 + zt * n1;
+                        const T Pb2 = xbar * bx2 + ybar * by2 + zt * n2;
+                        const T Dbar = Pb0 * mq[0] + Pb1 * mq[1] + Pb2 * mq[2];
+                        const T mb0 = D * Pb0 + Dbar * cq[0], mb1 = D * Pb1 + Dbar * cq[1], mb2 = D * Pb2 + Dbar * cq[2];
+                        L.pb[cell][q] = Dbar * dv;
+                        // n enters through z = P.n, through -D0 n in P, and as m where the neighbour keeps it
+                        w0 = zt * v0 - D0 * Pb0 + (own ? T(0) : mb0);
+                        w1 = zt * v1 - D0 * Pb1 + (own ? T(0) : mb1);
+                        w2 = zt * v2 - D0 * Pb2 + (own ? T(0) : mb2);
+                        // m = -h / |h|: the adjoint of h, gathered later at that neighbour
+                        // and spread over its 3^3 by the gradient's weights
+                        const T md = mq[0] * mb0 + mq[1] * mb1 + mq[2] * mb2;
+                        float* o = outh + 3 * (q < 13 ? q : q - 1);
+                        o[0] = own ? float(-(mb0 - mq[0] * md) * ih) : 0.0f;
+                        o[1] = own ? float(-(mb1 - mq[1] * md) * ih) : 0.0f;
+                        o[2] = own ? float(-(mb2 - mq[2] * md) * ih) : 0.0f;
+                    } else {
+                        L.pb[cell][q] = zt * dv;
+                        v0 = ex; v1 = ey; v2 = ez;
+                        w0 = ex + cq[0]; w1 = ey + cq[1]; w2 = ez + cq[2];
+                    }
+                }
             }
+            add_entries<LANES>(arow, en.more(), [&] {
+                arow[0] += F(xbar * v0); arow[1] += F(xbar * v1); arow[2] += F(xbar * v2);
+                arow[3] += F(ybar * v0); arow[4] += F(ybar * v1); arow[5] += F(ybar * v2);
+                if constexpr (NBR) {
+                    arow[6] += F(w0); arow[7] += F(w1); arow[8] += F(w2);
+                } else {
+                    arow[6] += F(zt * w0); arow[7] += F(zt * w1); arow[8] += F(zt * w2);
+                }
+                arow[9] += F(zt);
+            });
         }
         __syncwarp();
         T asum[10];
 #pragma unroll
-        for (int i = 0; i < 10; ++i) asum[i] = T(group_sum(arow[i]));
+        for (int i = 0; i < 10; ++i) asum[i] = T(group_sum<LANES>(arow[i]));
         const T c00 = L.cen[cell][0], c01 = L.cen[cell][1], c02 = L.cen[cell][2], dvc = L.cen[cell][3];
         const T sbx0 = asum[0], sbx1 = asum[1], sbx2 = asum[2], sz_ = asum[9];
         // the centre offset D0 enters every z with a minus sign
@@ -613,8 +705,8 @@ __device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, in
         const T nd = n0 * nb0 + n1 * nb1 + n2 * nb2;
         const T gb0 = -(nb0 - n0 * nd) * ign, gb1 = -(nb1 - n1 * nd) * ign, gb2 = -(nb2 - n2 * nd) * ign;
 #pragma unroll
-        for (int kk = 0; kk < kRounds; ++kk) {
-            const int q = j + kk * kLanes;
+        for (int kk = 0; kk < kPasses; ++kk) {
+            const int q = j + kk * LANES;
             if (q < 27) {
                 const float4 e = L.e[q];
                 const bool on = (mask >> q) & 1u;
@@ -1000,17 +1092,8 @@ __device__ __forceinline__ int tile_cell(unsigned mw, unsigned pw, unsigned firs
         words = r == k ? half : words;
     }
     const int w = __ffs(static_cast<int>(words)) - 1;
-    unsigned word = __shfl(mw, w, 32);
-    int k = static_cast<int>(first + r - __shfl(pw, w, 32)), bit = 0;
-#pragma unroll
-    for (int st = 16; st; st >>= 1) {                        // the word's k-th set bit
-        const int low = __popc(word & ((1u << st) - 1u));
-        const bool up = k >= low;
-        k -= up ? low : 0;
-        bit += up ? st : 0;
-        word >>= up ? st : 0;
-    }
-    return w * 32 + bit;
+    const unsigned word = __shfl(mw, w, 32);
+    return w * 32 + nth_bit(word, static_cast<int>(first + r - __shfl(pw, w, 32)));
 }
 
 // zero on the whole tile, by one wavefront
@@ -1033,8 +1116,8 @@ __device__ __forceinline__ void zero_tile(float* __restrict__ out, int tile, int
 // their 3x3x3 tiles (their cells can receive a contribution: the gather's
 // tiles), and a zero gradient for the others.  Beside the work items in one
 // launch: those are bound by instruction issue and leave HBM idle.
-__device__ __forceinline__ void zero_away(float* __restrict__ gphi, const Workspace& ws, int seg, int X, int Y, int Z,
-                                          int ntx, int nty, int ntiles) {
+__device__ __forceinline__ void zero_away(float* __restrict__ gphi, const Workspace& ws, int seg, int part, int parts,
+                                          int X, int Y, int Z, int ntx, int nty, int ntiles) {
     const int lane = threadIdx.x, tile = seg * 64 + lane, ntz = ntiles / (ntx * nty);
     bool act = false;
     if (tile < ntiles) {
@@ -1051,41 +1134,160 @@ __device__ __forceinline__ void zero_away(float* __restrict__ gphi, const Worksp
     }
     const unsigned long long bits = __ballot(act);
     if (lane < 2) ws.act[2 * seg + lane] = static_cast<unsigned>(bits >> (32 * lane));
-    const int left = ntiles - seg * 64;
-    unsigned long long away = ~bits & (left >= 64 ? ~0ull : (1ull << left) - 1ull);
-    for (; away; away &= away - 1ull) zero_tile(gphi, seg * 64 + __ffsll(away) - 1, lane, X, Y, Z, ntx, nty);
+    const int end = min(ntiles - seg * 64, 64);
+    for (int t = part; t < end; t += parts)
+        if (!((bits >> t) & 1ull)) zero_tile(gphi, seg * 64 + t, lane, X, Y, Z, ntx, nty);
 }
 
-// Workgroups of one wavefront: each 32-lane half takes a work item (8 cells of
-// a tile, 4 lanes per cell).  A group finds its cell, the i-th interface cell of
-// the tile in cell order, from the tile's bitmask and prefix counts, stages the
-// cell's fill levels and runs curv_cell.  The forward writes kappa, the backward
-// (ADJ) the cell's contribution row when it fits the workspace; its first
-// workgroups are zero_away's, one per CU at most (one per run of tiles, 1152 of
-// them, kept the work items from the SIMDs: 209 against 183 us for the spray).
-__host__ __device__ inline unsigned zero_blocks(const Workspace& ws) { return ws.segs < 256 ? ws.segs : 256; }
+// The backward's first workgroups are zero_away's: one per CU at most (one per
+// run of 64 tiles, 1152 of them, kept the work items from the SIMDs: 209 against
+// 183 us for the spray), and up to 16 to a run where runs are few: with one
+// each, a 64 x 62 x 63 lattice's forward and backward took 42.1 us instead of 33.3.
+__host__ __device__ inline unsigned zero_parts(const Workspace& ws) {
+    return ws.segs >= 256 ? 1u : (ws.segs <= 16 ? 16u : 256u / static_cast<unsigned>(ws.segs));
+}
+__host__ __device__ inline unsigned zero_blocks(const Workspace& ws) {
+    return ws.segs >= 256 ? 256u : static_cast<unsigned>(ws.segs) * zero_parts(ws);
+}
 
-template <class T, bool ADJ>
+// Up to this many work items the cells take 16 lanes each instead of 4: there
+// are then no more wavefronts than the chip holds at once, and the time is that
+// of one cell's chain, which 16 lanes shorten (one round of PLIC problems and
+// points instead of three or four).  Forward and backward with 4 and with 16
+// lanes, mixed precision: 64 x 62 x 63 (600 items) 34.9 and 33.3 us, with neighbour normals
+// 56.8 and 46.1; 100 x 98 x 99 (1400 items) 43.7 and 44.6, with neighbour
+// normals 69.7 and 66.8 (FP64: 77.9 and 78.0); 120 x 118 x 119 (2000 items)
+// 42.4 and 50.9, with neighbour normals 69.7 and 70.5; 150 x 148 x 149 (3100)
+// 57.8 and 72.9, 88.5 and 100.4.  Both give the same bits.
+template <class T, bool NBR> constexpr unsigned kWideItems = NBR && sizeof(T) == 4 ? 2048 : 1024;
+
+// wavefronts per SIMD: what the registers allow without scratch memory (but for
+// 8 bytes in the mixed nested forward)
+template <class T, bool ADJ, bool NBR>
 constexpr int cell_waves() {
-    return sizeof(T) == 4 ? (ADJ ? 3 : 4) : 2;
+    return sizeof(T) == 4 ? (ADJ ? (NBR ? 2 : 3) : 4) : 2;
+}
+
+// This wavefront's share of the work items, LANES lanes per cell: each 32-lane
+// half takes an item, or a quarter of one (2 of its 8 cells) with 16 lanes.  A
+// group finds its cell, the i-th interface cell of the tile in cell order, from the
+// tile's bitmask and prefix counts, stages the cell's fill levels and runs
+// curv_cell.  The forward writes kappa, the backward (ADJ) the cell's
+// contribution row when it fits the workspace.
+template <int LANES, int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR, int NB>
+__device__ __forceinline__ void cell_items(const ItemFinder& finder, unsigned block, unsigned blocks,
+                                           float (&nbh)[kWaveCells][NB], CellLds<T, F, ADJ>& lds,
+                                           const float* __restrict__ phi, const float* __restrict__ gkap,
+                                           float* __restrict__ out_field, const Workspace& ws, int X, int Y, int Z, int ntx,
+                                           int nty) {
+    constexpr int H = NBR ? 2 : 1, W = 2 * H + 1, C = (H * W + H) * W + H;
+    constexpr unsigned kHalfCells = 32 / LANES, kShares = kPartCells / kHalfCells;   // shares of an item
+    const unsigned total = finder.total * kShares;
+    auto contributions = [&](unsigned row) { return ADJ ? ws.contrib + row : nullptr; };
+    auto adjoints = [&](unsigned row) {
+        return ADJ && NBR ? ws.contrib + 27u * ws.rows + static_cast<size_t>(row) * kRowFloatsH : nullptr;
+    };
+    for (unsigned it = 2u * block; it < total; it += 2u * blocks) {
+        const int lane = thread_index_per_iteration(), l32 = lane & 31, cell = lane / LANES, j = lane % LANES;
+        const bool second = it + 1u < total;
+        const unsigned mine = it + (second && lane >= 32 ? 1u : 0u);
+        const unsigned e = finder.item(ws, lane, it / kShares, (it + (second ? 1u : 0u)) / kShares);
+        const int tile = static_cast<int>(e >> 7), part = static_cast<int>(e & 127u);
+        unsigned mw, pw, row;
+        tile_words(ws, tile, l32, mw, pw, row);
+        const unsigned n = __shfl(pw + __popc(mw), kWords - 1, 32);
+        const unsigned i0 = static_cast<unsigned>(part) * kPartCells + mine % kShares * kHalfCells, ic = i0 + cell % kHalfCells;
+        // (n > i0 but for the last item's shares beyond the tile's cells)
+        const unsigned i1 = min(i0, n - 1u);
+        const int cl = tile_cell<kHalfCells>(mw, pw, i1, static_cast<int>(min(ic, n - 1u) - i1), lane);
+        row += ic;
+        // uniform per group; a row that does not fit is recomputed by the gather
+        const bool on = ic < n && (second || lane < 32) && (!ADJ || row < ws.rows);
+        const int gx = (tile % ntx) * TX + cl % TX, gy = ((tile / ntx) % nty) * TY + (cl / TX) % TY,
+                  gz = (tile / (ntx * nty)) * TZ + cl / (TX * TY);
+        const int64_t gi = (static_cast<int64_t>(gz) * Y + gy) * X + gx;
+        float gk = 0.0f, kv = 0.0f;
+        bool done = true;
+        if (on) {
+            if constexpr (ADJ) {
+                gk = gkap[gi];
+                if (j == 0) lds.at[cell] = make_int4(gx, gy, gz, static_cast<int>(row));
+            }
+            if constexpr (NBR) {
+                // 25 rows of 5 levels, those outside the lattice read as 0
+                for (int r = j; r < W * W; r += LANES) {
+                    const int ay = gy + r % W - H, az = gz + r / W - H;
+                    const bool in = ay >= 0 && ay < Y && az >= 0 && az < Z;
+                    const float* p = phi + (static_cast<int64_t>(az) * Y + ay) * X + (gx - H);
+                    float v[W];
+#pragma unroll
+                    for (int t = 0; t < W; ++t) v[t] = in && gx + t - H >= 0 && gx + t - H < X ? p[t] : 0.0f;
+#pragma unroll
+                    for (int t = 0; t < W; ++t) nbh[cell][r * W + t] = v[t];
+                }
+            } else {
+                // 9 rows of 3 consecutive levels, all in the lattice (an interface
+                // cell lies off the outer layer)
+                constexpr int kLoads = (9 + LANES - 1) / LANES;
+                float v[kLoads][3];
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) {
+                    const int r = min(j + u * LANES, 8);
+                    const float* p = phi + (static_cast<int64_t>(gz + r / 3 - 1) * Y + (gy + r % 3 - 1)) * X + (gx - 1);
+                    v[u][0] = p[0]; v[u][1] = p[1]; v[u][2] = p[2];
+                }
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u) {
+                    const int r = j + u * LANES;
+                    if (r < 9) { nbh[cell][3 * r] = v[u][0]; nbh[cell][3 * r + 1] = v[u][1]; nbh[cell][3 * r + 2] = v[u][2]; }
+                }
+            }
+            __syncwarp();
+            done = curv_cell<LANES, false, SOLVER, T, U, F, ADJ, NRM, NBR>(nbh[cell], C, W, W * W, lane, gk, contributions(row), ws.rows,
+                                                                           adjoints(row), lds, kv, Place{gx, gy, gz, X, Y, Z});
+        }
+        if constexpr (!ADJ)
+            if (on && done && j == 0) out_field[gi] = kv;
+        redo_groups<LANES>(done, lane, [&](int src) {
+            const int from = max(src, 0);
+            Place at{0, 0, 0, X, Y, Z};
+            unsigned r = 0u;
+            float g = 0.0f;
+            if constexpr (ADJ) {
+                const int4 p = lds.at[from / LANES];
+                at.x = p.x; at.y = p.y; at.z = p.z;
+                r = static_cast<unsigned>(p.w);
+                if (src >= 0) g = gkap[(static_cast<int64_t>(at.z) * Y + at.y) * X + at.x];
+            } else {
+                at.x = __shfl(gx, from, 64); at.y = __shfl(gy, from, 64); at.z = __shfl(gz, from, 64);
+            }
+            float k = 0.0f;
+            if (src >= 0)
+                curv_cell<kWideLanes, true, SOLVER, T, U, F, ADJ, NRM, NBR>(nbh[src / LANES], C, W, W * W, lane, g, contributions(r),
+                                                                            ws.rows, adjoints(r), lds, k, at);
+            if constexpr (!ADJ)
+                if (src >= 0 && lane % kWideLanes == 0) out_field[(static_cast<int64_t>(at.z) * Y + at.y) * X + at.x] = k;
+        });
+        __syncwarp();                                        // nbh and lds reused by the next pair
+    }
 }
 
 template <int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR>
-__global__ __launch_bounds__(64, (cell_waves<T, ADJ>())) void k_curv_quads(
+__global__ __launch_bounds__(64, (cell_waves<T, ADJ, NBR>())) void k_curv_quads(
     const float* __restrict__ phi, const float* __restrict__ gkap, float* __restrict__ out_field, Workspace ws, int X,
     int Y, int Z, int ntx, int nty, int ntiles) {
     // the cell's 3x3x3 fill levels (5x5x5 with neighbour normals)
-    constexpr int H = NBR ? 2 : 1, W = 2 * H + 1, NB = W * W * W, C = (H * W + H) * W + H;
-    constexpr unsigned kItems = kWaveCells / kPartCells;     // of a wavefront
+    constexpr int NB = NBR ? 125 : 27;
     __shared__ float nbh[kWaveCells][NB];
-    __shared__ CellLds<T, ADJ> lds;
+    __shared__ CellLds<T, F, ADJ> lds;
     unsigned block = blockIdx.x, blocks = gridDim.x;
     if constexpr (ADJ) {
         if (block == 0 && threadIdx.x == 0) ws.counter[kOverflow] = 0u;   // the gather, a later launch, counts there
-        const unsigned nzero = zero_blocks(ws);
+        const unsigned nzero = zero_blocks(ws), parts = zero_parts(ws);
         if (block < nzero) {
-            for (int seg = static_cast<int>(block); seg < ws.segs; seg += static_cast<int>(nzero))
-                zero_away(out_field, ws, seg, X, Y, Z, ntx, nty, ntiles);
+            for (unsigned b = block; b < static_cast<unsigned>(ws.segs) * parts; b += nzero)
+                zero_away(out_field, ws, static_cast<int>(b / parts), static_cast<int>(b % parts), static_cast<int>(parts), X, Y,
+                          Z, ntx, nty, ntiles);
             return;
         }
         block -= nzero;
@@ -1099,69 +1301,12 @@ __global__ __launch_bounds__(64, (cell_waves<T, ADJ>())) void k_curv_quads(
     }
     init_cells<NRM>(lds, static_cast<int>(threadIdx.x));
     const ItemFinder finder(ws);
-    for (unsigned it = kItems * block; it < finder.total; it += kItems * blocks) {
-        const int lane = thread_index_per_iteration(), l32 = lane & 31, cell = lane / kLanes, j = lane % kLanes;
-        const bool second = it + kItems - 1u < finder.total;
-        const unsigned e = finder.item(ws, lane, it, it + (second ? kItems - 1u : 0u));
-        const int tile = static_cast<int>(e >> 7), part = static_cast<int>(e & 127u);
-        unsigned mw, pw, row;
-        tile_words(ws, tile, l32, mw, pw, row);
-        const unsigned n = __shfl(pw + __popc(mw), kWords - 1, 32);
-        const unsigned i0 = static_cast<unsigned>(part * kPartCells), ic = i0 + cell % kPartCells;
-        // n > i0: the tile has the item
-        const int cl = tile_cell<kPartCells>(mw, pw, i0, static_cast<int>(min(ic, n - 1u) - i0), lane);
-        row += ic;
-        // uniform per group; a row that does not fit is recomputed by the gather
-        if (ic >= n || (!second && lane >= 32) || (ADJ && row >= ws.rows)) continue;
-        const int gx = (tile % ntx) * TX + cl % TX, gy = ((tile / ntx) % nty) * TY + (cl / TX) % TY,
-                  gz = (tile / (ntx * nty)) * TZ + cl / (TX * TY);
-        const int64_t gi = (static_cast<int64_t>(gz) * Y + gy) * X + gx;
-        float gk = 0.0f;
-        if constexpr (ADJ) gk = gkap[gi];
-        if constexpr (NBR) {
-            // 25 rows of 5 levels, those outside the lattice read as 0
-            for (int r = j; r < W * W; r += kLanes) {
-                const int ay = gy + r % W - H, az = gz + r / W - H;
-                const bool in = ay >= 0 && ay < Y && az >= 0 && az < Z;
-                const float* p = phi + (static_cast<int64_t>(az) * Y + ay) * X + (gx - H);
-                float v[W];
-#pragma unroll
-                for (int t = 0; t < W; ++t) v[t] = in && gx + t - H >= 0 && gx + t - H < X ? p[t] : 0.0f;
-#pragma unroll
-                for (int t = 0; t < W; ++t) nbh[cell][r * W + t] = v[t];
-            }
-        } else {
-            // 9 rows of 3 consecutive levels, all in the lattice (an interface
-            // cell lies off the outer layer)
-            float v[3][3];
-#pragma unroll
-            for (int u = 0; u < 3; ++u) {
-                const int r = min(j + u * kLanes, 8);
-                const float* p = phi + (static_cast<int64_t>(gz + r / 3 - 1) * Y + (gy + r % 3 - 1)) * X + (gx - 1);
-                v[u][0] = p[0]; v[u][1] = p[1]; v[u][2] = p[2];
-            }
-#pragma unroll
-            for (int u = 0; u < 3; ++u) {
-                const int r = j + u * kLanes;
-                if (r < 9) { nbh[cell][3 * r] = v[u][0]; nbh[cell][3 * r + 1] = v[u][1]; nbh[cell][3 * r + 2] = v[u][2]; }
-            }
-        }
-        __syncwarp();
-        const Place where{gx, gy, gz, X, Y, Z};
-        float kv = 0.0f;
-        float* out = ADJ ? ws.contrib + row : nullptr;
-        float* outh = ADJ && NBR ? ws.contrib + 27u * ws.rows + static_cast<size_t>(row) * kRowFloatsH : nullptr;
-        const bool done = curv_cell<false, SOLVER, T, U, F, ADJ, NRM, NBR>(nbh[cell], C, W, W * W, lane, gk, out,
-                                                                           ws.rows, outh, lds, kv, where);
-        if (__builtin_expect(!done, 0)) {                    // uniform per group
-            __syncwarp();
-            curv_cell<true, SOLVER, T, U, F, ADJ, NRM, NBR>(nbh[cell], C, W, W * W, lane, gk, out, ws.rows, outh, lds,
-                                                            kv, where);
-        }
-        if constexpr (!ADJ)
-            if (j == 0) out_field[gi] = kv;
-        __syncwarp();                                        // nbh and lds reused by the next pair
-    }
+    if (finder.total <= kWideItems<T, NBR>)
+        cell_items<kWideLanes, SOLVER, T, U, F, ADJ, NRM, NBR>(finder, block, blocks, nbh, lds, phi, gkap, out_field, ws, X, Y,
+                                                               Z, ntx, nty);
+    else
+        cell_items<kLanes, SOLVER, T, U, F, ADJ, NRM, NBR>(finder, block, blocks, nbh, lds, phi, gkap, out_field, ws, X, Y, Z,
+                                                           ntx, nty);
 }
 
 // ---------------------------------------------------------------------------
@@ -1205,12 +1350,13 @@ __global__ __launch_bounds__(kThreads) void k_curv_gather_fallback(const float* 
     __shared__ float contrib[kChunk][27];
     __shared__ unsigned crow[kChunk];
     __shared__ int wcount[kThreads / 64];
-    __shared__ CellLds<T, true> cells[kThreads / 64];
+    __shared__ CellLds<T, F, true> cells[kThreads / 64];
     const int tid = threadIdx.x;
-    CellLds<T, true>& lds = cells[tid >> 6];
+    const unsigned ntl = *static_cast<volatile unsigned*>(ws.counter + kOverflow);
+    if (ntl == 0u) return;
+    CellLds<T, F, true>& lds = cells[tid >> 6];
     init_cells<NRM>(lds, tid & 63);
     for (int i = tid; i < C_REGION; i += kThreads) slot[i] = kNoSlot;
-    const unsigned ntl = *static_cast<volatile unsigned*>(ws.counter + kOverflow);
     for (unsigned it = blockIdx.x; it < ntl; it += gridDim.x) {
         const int tile = static_cast<int>(ws.over[it]);
         const int x0 = (tile % ntx) * TX, y0 = ((tile / ntx) % nty) * TY, z0 = (tile / (ntx * nty)) * TZ;
@@ -1254,21 +1400,29 @@ __global__ __launch_bounds__(kThreads) void k_curv_gather_fallback(const float* 
             }
             {
                 // rows that did not fit: recomputed, one group of lanes per cell
-                for (int i = tid / kLanes; i < nc; i += kThreads / kLanes) {
-                    if (crow[i] < ws.rows) continue;                     // uniform per group
-                    const int ci = cand[c0 + i];
-                    const int lx = ci % C_RX, ly = (ci / C_RX) % C_RY, lz = ci / (C_RX * C_RY);
-                    const int gx = x0 - 1 + lx, gy = y0 - 1 + ly, gz = z0 - 1 + lz;
-                    const float gk = gkap[(static_cast<int64_t>(gz) * Y + gy) * X + gx];
-                    const int centre = ((lz + 1) * RY + (ly + 1)) * RX + (lx + 1);
-                    float kv;
-                    const bool done = curv_cell<false, SOLVER, T, U, F, true, NRM>(s, centre, RX, RX * RY, tid & 63, gk,
-                                                                                   contrib[i], 1u, nullptr, lds, kv);
-                    __syncwarp();
-                    if (!done)
-                        curv_cell<true, SOLVER, T, U, F, true, NRM>(s, centre, RX, RX * RY, tid & 63, gk, contrib[i], 1u,
-                                                                    nullptr, lds, kv);
-                    __syncwarp();                                        // lds reused by the next cell
+                const int lane = tid & 63;
+                for (int i0 = 0; i0 < nc; i0 += kThreads / kLanes) {
+                    const int i = i0 + tid / kLanes;
+                    bool done = true;
+                    int centre = 0;
+                    float gk = 0.0f, kv;
+                    if (i < nc && crow[i] >= ws.rows) {                  // uniform per group
+                        const int ci = cand[c0 + i];
+                        const int lx = ci % C_RX, ly = (ci / C_RX) % C_RY, lz = ci / (C_RX * C_RY);
+                        const int gx = x0 - 1 + lx, gy = y0 - 1 + ly, gz = z0 - 1 + lz;
+                        gk = gkap[(static_cast<int64_t>(gz) * Y + gy) * X + gx];
+                        centre = ((lz + 1) * RY + (ly + 1)) * RX + (lx + 1);
+                        done = curv_cell<kLanes, false, SOLVER, T, U, F, true, NRM>(s, centre, RX, RX * RY, lane, gk, contrib[i],
+                                                                                    1u, nullptr, lds, kv);
+                    }
+                    redo_groups<kLanes>(done, lane, [&](int src) {
+                        const int from = max(src, 0), ai = __shfl(i, from, 64), ac = __shfl(centre, from, 64);
+                        const float ag = __shfl(gk, from, 64);
+                        if (src >= 0)
+                            curv_cell<kWideLanes, true, SOLVER, T, U, F, true, NRM>(s, ac, RX, RX * RY, lane, ag, contrib[ai],
+                                                                                    1u, nullptr, lds, kv);
+                    });
+                    __syncwarp();                                        // lds reused by the next cells
                 }
             }
             __syncthreads();
