@@ -3,15 +3,17 @@
 //
 // Layout: V0 and d0 hold one element per problem; the normals are either three
 // such arrays (nx, ny, nz) or, ROWS, one array of rows (x, y, z).  Each thread
-// handles VEC consecutive problems with 16-byte loads and stores per array (4
-// floats or 2 doubles), so a wavefront moves 1 KiB per array per access; VEC =
-// 1 covers unaligned pointers and small batches, and the last block, when it
-// is not whole, goes element by element.  One pass over HBM, no reuse.
+// handles VEC consecutive problems with loads and stores of 16 bytes per array (4
+// floats or 2 doubles; 2 floats where batches are not large); VEC = 1 covers
+// unaligned pointers, and the last block, when it is not whole, goes element by
+// element.  One pass over HBM, no reuse.
 // The inversion kernels settle the closed-form cases in registers and pack the
 // rest (the cubic cases, about 40 % of uniformly random problems) densely in
 // LDS before the iterative / trigonometric stage, so that stage runs on full
 // wavefronts.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "plic_host.hpp"
 #include "plic_math.hpp"
@@ -20,17 +22,21 @@ namespace plic {
 namespace {
 
 constexpr int kBlock = 256;
-// The backward streams 5 input and 4 output arrays; workgroups of 512 keep
-// twice the consecutive bytes of each array in flight per workgroup, which
-// the memory system serves faster for this many streams (measured: a plain
-// 5-read / 4-write copy and this kernel both about 6 % faster than with 256).
+// Large float batches: the backward streams 5 input and 4 output arrays;
+// workgroups of 512 keep twice the consecutive bytes of each array in flight per
+// workgroup, which the memory system serves faster for this many streams
+// (measured: a plain 5-read / 4-write copy and this kernel both about 6 % faster
+// than with 256).  Others: 256, which fill and leave the chip sooner (20,000 float
+// rows 6.9 -> 5.8 us, 10,000 double rows 6.9 -> 5.0 us).
 constexpr int kBwdBlock = 512;
+template <int VEC> constexpr int kBwdThreads = VEC == 4 ? kBwdBlock : kBlock;
 
 // Input streams are read once: the loads carry the non-temporal hint (the
 // "nt" bit), which keeps them from allocating in the caches as reusable data.
 // Measured on a plain 4-read / 1-write stream of 2^26 floats per array:
 // 0.84 of the HBM peak against 0.71 without the hint.
 template <class S, int VEC> struct NVec;
+template <> struct NVec<float, 2> { typedef float type __attribute__((ext_vector_type(2))); };
 template <> struct NVec<float, 4> { typedef float type __attribute__((ext_vector_type(4))); };
 template <> struct NVec<double, 2> { typedef double type __attribute__((ext_vector_type(2))); };
 
@@ -87,10 +93,10 @@ __device__ __forceinline__ void store_part(S* p, int64_t i, int64_t count, bool 
 
 // ---------------------------------------------------------------------------
 // Normals as rows (x, y, z): the 64 VEC rows of a wavefront are 3 KiB of
-// consecutive memory.  They move as three 16-byte accesses per lane over whole
-// cache lines, and change places through LDS to and from the VEC rows of each
-// lane; the 48-byte stride of a lane's rows there meets every bank once per 8
-// lanes.  Rows loaded lane by lane instead would touch each line three times,
+// consecutive memory (1.5 with 2 floats).  They move as three 16-byte (8-byte)
+// accesses per lane over whole cache lines, and change places through LDS to
+// and from the VEC rows of each lane; the 48-byte stride of a lane's rows there
+// meets every bank once per 8 lanes.  Rows loaded lane by lane instead would touch each line three times,
 // and split into component arrays beforehand they cost three strided copies:
 // the volume of 10,000,019 rows took 104.6 us so (75 of them the copies) and
 // takes 32.5 us here (6.2 TB/s).
@@ -378,14 +384,15 @@ __device__ __forceinline__ void bwd_block(const S* __restrict__ nx, const S* __r
 }
 
 template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
-__global__ __launch_bounds__(kBwdBlock) void k_offset_bwd(const S* __restrict__ nx, const S* __restrict__ ny,
+__global__ __launch_bounds__(kBwdThreads<VEC>) void k_offset_bwd(const S* __restrict__ nx, const S* __restrict__ ny,
                                                        const S* __restrict__ nz, const S* __restrict__ V0,
                                                        const S* __restrict__ gd, S* __restrict__ gnx,
                                                        S* __restrict__ gny, S* __restrict__ gnz,
                                                        S* __restrict__ gV0, int64_t count) {
-    __shared__ RowStage<S, VEC> rows[ROWS ? kBwdBlock / 64 : 1];
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kBwdBlock * VEC), i = first + threadIdx.x * VEC;
-    if (first + kBwdBlock * VEC <= count)
+    constexpr int kB = kBwdThreads<VEC>;
+    __shared__ RowStage<S, VEC> rows[ROWS ? kB / 64 : 1];
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kB * VEC), i = first + threadIdx.x * VEC;
+    if (first + kB * VEC <= count)
         bwd_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, gd, gnx, gny, gnz, gV0, i, count, true, rows);
     else
         bwd_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, gd, gnx, gny, gnz, gV0, i, count, false, rows);
@@ -456,23 +463,41 @@ template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
 void launch_bwd_v(const BwdArgs<S>& p, hipStream_t st) {
     for (int64_t base = 0; base < p.count; base += kChunkProblems) {
         const int64_t n = p.count - base < kChunkProblems ? p.count - base : kChunkProblems;
-        hipLaunchKernelGGL((k_offset_bwd<SOLVER, S, T, U, VEC, ROWS>), dim3(grid_for(n, VEC, kBwdBlock)),
-                           dim3(kBwdBlock), 0, st, advance<ROWS>(p.nx, base), advance<ROWS>(p.ny, base),
+        hipLaunchKernelGGL((k_offset_bwd<SOLVER, S, T, U, VEC, ROWS>), dim3(grid_for(n, VEC, kBwdThreads<VEC>)),
+                           dim3(kBwdThreads<VEC>), 0, st, advance<ROWS>(p.nx, base), advance<ROWS>(p.ny, base),
                            advance<ROWS>(p.nz, base), p.V0 + base, p.gd + base, advance<ROWS>(p.gx, base),
                            advance<ROWS>(p.gy, base), advance<ROWS>(p.gz, base), p.gv + base, n);
     }
 }
 
-template <int SOLVER, class S, class T, class U, bool ROWS>
-void launch_t(const OffsetArgs<S>& p, bool vec, hipStream_t st) {
-    if (vec) launch_offset_v<SOLVER, S, T, U, kVec<S>, ROWS>(p, st);
-    else launch_offset_v<SOLVER, S, T, U, 1, ROWS>(p, st);
+// Up to this many problems of a float batch go two to a thread, more four: four
+// take fewer instructions for addresses and stages, two make twice the
+// wavefronts, which fill the chip sooner and leave it more evenly.  SZ, us with
+// four and with two: forward of rows, 100,003 5.0 and 4.7, 300,007 6.2 and 4.9,
+// 1,000,003 9.1 and 8.3, 4,000,037 24.3 and 23.0, 7,900,001 43.2 and 41.9; of three
+// arrays, 1,000,003 7.8 and 6.4, 4,000,037 17.7 and 17.6, 7,900,001 29.2 and 30.4;
+// backward of rows, 100,003 7.1 and 4.7, 1,000,003 11.2 and 10.0, 4,000,037 29.3 and
+// 28.5, 7,900,001 53.3 and 51.0, 12,000,001 75.4 and 77.4; of three arrays, 1,000,003
+// 10.6 and 9.0, 7,900,001 53.7 and 50.9.  (A volume is no faster with two at any
+// size: 4,000,037 rows 14.7 and 15.3.)
+constexpr int64_t kManyProblems = 8000000, kManyArrays = 4000000;
+
+template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
+void launch_v(const OffsetArgs<S>& p, hipStream_t st) {
+    launch_offset_v<SOLVER, S, T, U, VEC, ROWS>(p, st);
+}
+template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
+void launch_v(const BwdArgs<S>& p, hipStream_t st) {
+    launch_bwd_v<SOLVER, S, T, U, VEC, ROWS>(p, st);
 }
 
-template <int SOLVER, class S, class T, class U, bool ROWS>
-void launch_t(const BwdArgs<S>& p, bool vec, hipStream_t st) {
-    if (vec) launch_bwd_v<SOLVER, S, T, U, kVec<S>, ROWS>(p, st);
-    else launch_bwd_v<SOLVER, S, T, U, 1, ROWS>(p, st);
+template <int SOLVER, class S, class T, class U, bool ROWS, class Args>
+void launch_t(const Args& p, bool vec, hipStream_t st) {
+    if (!vec) return launch_v<SOLVER, S, T, U, 1, ROWS>(p, st);
+    constexpr bool kArrays = !ROWS && std::is_same_v<Args, OffsetArgs<S>>;
+    if constexpr (sizeof(S) == 4)
+        if (p.count > (kArrays ? kManyArrays : kManyProblems)) return launch_v<SOLVER, S, T, U, 4, ROWS>(p, st);
+    launch_v<SOLVER, S, T, U, 2, ROWS>(p, st);
 }
 
 // the solver's kernel for a forward (OffsetArgs) or a backward (BwdArgs)
