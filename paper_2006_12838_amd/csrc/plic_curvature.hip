@@ -219,17 +219,30 @@ template <class T, class F> union OffsetLds {
         F terms[64 / kWideLanes][2 * 20];
     } wide;
 };
-template <class T, class F, bool ADJ> struct CellLds {
+template <bool OWN> struct OwnLds {};
+template <> struct OwnLds<true> {
+    float4 own[kRounds][64];                    // each entry's own normal and its factor 1 / |h| (0: the centre's)
+};
+template <class T, class F, bool ADJ, bool OWN = false> struct CellLds : OwnLds<OWN> {
     OffsetLds<T, F> o;
     float4 e[27];
 };
-template <class T, class F> struct CellLds<T, F, true> {
+template <class T, class F, bool OWN> struct CellLds<T, F, true, OWN> : OwnLds<OWN> {
     OffsetLds<T, F> o;
     float4 e[27];
     T pb[kWaveCells][27];
     T cen[kWaveCells][4];
     int4 at[kWaveCells];                        // place and row (kept here, not in registers, for a second call)
 };
+
+// Neighbour normals: an adjoint in FP32 points keeps each entry's own normal from
+// its PLIC problem for its point and its adjoint (they were formed three times,
+// from 26 levels each): 36.2 -> 30.4 us for 5 drops in 150 x 131 x 118, forward
+// and backward of the spray 966 -> 906 us.  Its 7 KiB leave the two wavefronts
+// per SIMD that its registers allow; a forward would drop from four to two (the
+// 5 drops 29.0 -> 25.7 us, but the spray 258 -> 297), an FP64 adjoint from two to
+// one.
+template <class T, bool ADJ, bool NBR> constexpr bool kKeepOwn = NBR && ADJ && sizeof(T) == 4;
 
 template <int NRM, class Lds> __device__ __forceinline__ void init_cells(Lds& L, int lane) {
     if (lane < 27) {
@@ -466,7 +479,8 @@ __device__ __forceinline__ void redo_groups(bool done, int lane, Again again) {
 template <int LANES, bool ORDERED, int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR = false>
 __device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, int sy, int sz, int lane,
                                           float gk, float* __restrict__ out, unsigned ostride,
-                                          float* __restrict__ outh, CellLds<T, F, ADJ>& L, float& kappa,
+                                          float* __restrict__ outh, CellLds<T, F, ADJ, kKeepOwn<T, ADJ, NBR>>& L,
+                                          float& kappa,
                                           const Place& where = {}) {
     using mt = M<T>;
     constexpr int kPasses = (27 + LANES - 1) / LANES;
@@ -526,6 +540,8 @@ __device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, in
             T mq[3] = {n0, n1, n2}, ih;
             bool own = false;
             if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, where, mq, own, ih);
+            if constexpr (kKeepOwn<T, ADJ, NBR>)
+                L.own[k][lane] = make_float4(mq[0], mq[1], mq[2], own ? ih : 0.0f);
             L.o.D[k][lane] = offset<SOLVER, T, U>(mq[0], mq[1], mq[2], p);
         } else {
             L.o.D[k][lane] = offset<SOLVER, T, U>(n0, n1, n2, p);
@@ -541,9 +557,15 @@ __device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, in
     auto point = [&](int q, int e, F& x, F& y, F& z) {
         const T D = L.o.D[e / LANES][(lane & ~(LANES - 1)) + e % LANES];
         if constexpr (NBR) {
-            T mq[3] = {n0, n1, n2}, ih;
-            bool own = false;
-            own_normal<NRM, T>(s, c, sy, sz, q, where, mq, own, ih);
+            T mq[3] = {n0, n1, n2};
+            if constexpr (kKeepOwn<T, ADJ, NBR>) {
+                const float4 m = L.own[e / LANES][(lane & ~(LANES - 1)) + e % LANES];
+                mq[0] = m.x; mq[1] = m.y; mq[2] = m.z;
+            } else {
+                bool own = false;
+                T ih;
+                own_normal<NRM, T>(s, c, sy, sz, q, where, mq, own, ih);
+            }
             cell_point_own<T, F>(L.e[q], D, D0, mq, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
         } else {
             cell_point<T, F>(L.e[q], D, D0, bx0, bx1, bx2, by0, by1, by2, n0, n1, n2, x, y, z);
@@ -620,8 +642,14 @@ __device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, in
                 const T p = T(s[at(q)]), D = L.o.D[k][lane];
                 T mq[3] = {n0, n1, n2}, ih = T(0);
                 bool own = false;
-                if constexpr (NBR)
+                if constexpr (kKeepOwn<T, ADJ, NBR>) {
+                    const float4 m = L.own[k][lane];
+                    mq[0] = m.x; mq[1] = m.y; mq[2] = m.z;
+                    ih = m.w;
+                    own = ih != 0.0f;
+                } else if constexpr (NBR) {
                     if (q != 13) own_normal<NRM, T>(s, c, sy, sz, q, where, mq, own, ih);
+                }
                 T cq[3];
                 const T dv = offset_grad_from_d0<T>(mq[0], mq[1], mq[2], p, D, cq);   // 1/A, centroid
                 if (q == 13) {
@@ -1176,7 +1204,8 @@ constexpr int cell_waves() {
 // contribution row when it fits the workspace.
 template <int LANES, int SOLVER, class T, class U, class F, bool ADJ, int NRM, bool NBR, int NB>
 __device__ __forceinline__ void cell_items(const ItemFinder& finder, unsigned block, unsigned blocks,
-                                           float (&nbh)[kWaveCells][NB], CellLds<T, F, ADJ>& lds,
+                                           float (&nbh)[kWaveCells][NB],
+                                           CellLds<T, F, ADJ, kKeepOwn<T, ADJ, NBR>>& lds,
                                            const float* __restrict__ phi, const float* __restrict__ gkap,
                                            float* __restrict__ out_field, const Workspace& ws, int X, int Y, int Z, int ntx,
                                            int nty) {
@@ -1279,7 +1308,7 @@ __global__ __launch_bounds__(64, (cell_waves<T, ADJ, NBR>())) void k_curv_quads(
     // the cell's 3x3x3 fill levels (5x5x5 with neighbour normals)
     constexpr int NB = NBR ? 125 : 27;
     __shared__ float nbh[kWaveCells][NB];
-    __shared__ CellLds<T, F, ADJ> lds;
+    __shared__ CellLds<T, F, ADJ, kKeepOwn<T, ADJ, NBR>> lds;
     unsigned block = blockIdx.x, blocks = gridDim.x;
     if constexpr (ADJ) {
         if (block == 0 && threadIdx.x == 0) ws.counter[kOverflow] = 0u;   // the gather, a later launch, counts there
