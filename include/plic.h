@@ -148,7 +148,7 @@ int plic_offset_backward_rows_f64(const double *n, const double *V0, const doubl
  * plic_curvature_workspace_bytes — recommended size of the device workspace of
  * plic_curvature_f32 and plic_curvature_backward_f32 for an X*Y*Z lattice.
  * The workspace holds a fixed part of 256 + 784 * tiles bytes (64x4x4 tiles:
- * work-list counters, per-tile interface flags, bitmasks and work lists;
+ * the counts, bitmasks and work items of the interface scan;
  * about 0.8 byte per cell) and, for the backward pass, a store of 108 bytes
  * (27 floats) per interface cell.  The recommended size budgets 16 interface
  * cells per tile (41 MB at 256^3); any size of at least the fixed part is

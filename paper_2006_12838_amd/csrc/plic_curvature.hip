@@ -21,8 +21,8 @@
 // each interface cell's 27 contributions in its row, rows in tile order; a
 // direct gather, one workgroup per tile, sums for every cell next to the
 // interface its sources' rows in a fixed order (tiles away from the interface
-// get their zeros beside the work items); a fallback gather handles the tiles with a source whose row did not fit the
-// workspace, recomputing those rows.
+// get their zeros beside the work items); a fallback gather handles the tiles
+// with a source whose row did not fit the workspace, recomputing those rows.
 // The interface is one cell thick (about 0.2 % of a 256^3 sphere lattice), so
 // the scan carries the HBM traffic and the list kernels the arithmetic.
 //
@@ -190,7 +190,8 @@ __device__ __forceinline__ void gradient27(const float* __restrict__ s, int c, i
 // every call gives the same bits.  Bound by instruction issue and the latency
 // of its chains: with 16 lanes per cell, two slots each, a spray of 24 drops
 // (512 x 384 x 384, mixed precision) took 183 us forward and 308 us adjoint,
-// the 256^3 sphere 16.4 us forward; with 4 lanes 90, 175 and 15 us.
+// the 256^3 sphere 16.4 us forward; with 4 lanes 88, 188 (the gradient's zeros,
+// 14 us, included) and 14 us.
 // An ill-conditioned fit shows the rounding of its sums in its result, many
 // times enlarged.  Where a pivot falls below kSteady of the largest diagonal
 // entry, the sums are formed again over the 16 pairs of neighbours (l, l + 16)
@@ -1091,7 +1092,7 @@ struct ItemFinder {
 
 // ---------------------------------------------------------------------------
 // 2. work items: up to kPartCells interface cells of a tile, each cell on a
-// group of 4 lanes (k_curv_quads; the neighbour-normal variant stages each
+// group of 4 lanes, or of 16 (k_curv_quads; the neighbour-normal variant stages each
 // cell's 5x5x5 neighbourhood, for each neighbour's own 3x3x3).  Forward:
 // kappa.  Backward: the cell's contributions gk * d kappa / d phi_q into its
 // contribution row (when it fits).
