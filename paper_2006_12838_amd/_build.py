@@ -12,6 +12,7 @@ LIB = os.path.join(PKG, "libplic.so")
 NATIVE = os.path.join(PKG, "_native.so")
 BUILD = os.path.join(os.path.dirname(PKG), "_build")
 SOURCES = ["plic_offset.hip", "plic_curvature.hip", "plic_bench.hip", "plic_abi.cpp"]
+PARTS = {"plic_curvature.hip": 5}   # objects of a source, compiled with -DPLIC_PART=0, 1, ...
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 # Packed FP32 (v_pk_*_f32) is disabled for all device code.
@@ -51,12 +52,13 @@ def build_library(verbose: bool = False) -> str:
     procs = [("plic_torch.cpp", subprocess.Popen(native, stdout=subprocess.PIPE, stderr=subprocess.STDOUT))]
     objs = []
     for src in SOURCES:
-        obj = os.path.join(BUILD, src.rsplit(".", 1)[0] + ".o")
-        objs.append(obj)
-        cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
+        for part in range(PARTS.get(src, 1)):
+            obj = os.path.join(BUILD, f"{src.rsplit('.', 1)[0]}_{part}.o")
+            objs.append(obj)
+            cmd = [HIPCC, *FLAGS, *([f"-DPLIC_PART={part}"] if src in PARTS else []), "-c", os.path.join(CSRC, src), "-o", obj]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
     failed = []
     for src, p in procs:
         out, _ = p.communicate()
