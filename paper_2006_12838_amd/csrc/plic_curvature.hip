@@ -49,7 +49,6 @@ constexpr int TX = 64, TY = 4, TZ = 4;       // tile
 constexpr int kTile = TX * TY * TZ;           // 1024 cells
 constexpr int kThreads = 256;                 // 4 wave64
 constexpr int kCellsPerThread = kTile / kThreads;
-constexpr int kGroup = 32;                    // lanes per interface cell of the gradient adjoints' gather
 constexpr int kPersistentBlocks = 2048;
 constexpr int kCellBlocks = 4096;             // wavefronts of the cell kernels: 4 per SIMD
 constexpr int kGatherBlocks = 1792;           // workgroups of the direct gather: 7 per CU, all it holds
@@ -1486,62 +1485,87 @@ __global__ __launch_bounds__(kThreads) void k_curv_gather_fallback(const float* 
     }
 }
 
-// Neighbour-normal backward, between the work items and the gather: over the
-// work items, one 32-lane group per interface cell n, lane j < 26 taking the
-// neighbour q of the adjoint's lane order.  The source c = n - e_q, when an
-// interface cell, stored in slot j of its row the adjoint for its neighbour at
-// +e_q, which is n: the adjoint of n's own fill-level gradient is the sum of
-// these 26 slots (zero where c is no interface cell), formed by a fixed
-// butterfly and written to the 3-vector beside n's row.  A source without a
-// stored row makes it NaN.
-__global__ __launch_bounds__(kThreads) void k_curv_hgather(Workspace ws, int X, int Y, int Z, int ntx, int nty) {
-    const int tid = threadIdx.x, grp = tid / kGroup, j = tid % kGroup;
-    const int half = tid & 32;
-    const int q = j < 13 ? j : j + 1;
-    const ItemFinder finder(ws);
-    for (unsigned item = blockIdx.x; item < finder.total; item += gridDim.x) {
-        const unsigned e = finder.item(ws, tid & 63, item, item);
+// sum over the lanes of each half wavefront, by a butterfly of distances 16, 8,
+// 4, 2, 1 (16 and 4 through LDS, the others by lane permutations)
+__device__ __forceinline__ float half_sum(float x) {
+    x += __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x401F));
+    x += quad_move<kTurn8>(x);
+    x += __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x101F));
+    x += quad_move<kSwap2>(x);
+    return x + quad_move<kSwap1>(x);
+}
+
+// Neighbour-normal backward, between the work items and the gather: PAIRS
+// pairs of a work item's interface cells on a wavefront, one half of it per cell
+// n, lane j < 26 taking the neighbour q of the adjoint's lane order.  The source
+// c = n - e_q, when an interface cell, stored in slot j of its row the adjoint
+// for its neighbour at +e_q, which is n: the adjoint of n's own fill-level
+// gradient is the sum of these 26 slots (zero where c is no interface cell),
+// formed by a fixed butterfly and written to the 3-vector beside n's row.  A
+// source without a stored row makes it NaN.  Bound by the latency of its
+// dependent loads (item, tile, sources, slots).
+template <int PAIRS>
+__device__ __forceinline__ void hgather_items(const ItemFinder& finder, const Workspace& ws, int X, int Y, int Z, int ntx,
+                                              int nty) {
+    constexpr unsigned kShares = kPartCells / 2 / PAIRS;     // of an item
+    const int lane = threadIdx.x & 63, j = lane & 31, half = lane >> 5;
+    const int q = j < 13 ? j : min(j + 1, 26);
+    for (unsigned it = blockIdx.x * (kThreads / 64) + threadIdx.x / 64; it < finder.total * kShares;
+         it += gridDim.x * (kThreads / 64)) {
+        const unsigned e = finder.item(ws, lane, it / kShares, it / kShares), pair0 = it % kShares * PAIRS;
         const int tile = static_cast<int>(e >> 7), part = static_cast<int>(e & 127u);
-        unsigned mw, pw, row;
-        tile_words(ws, tile, j, mw, pw, row);
-        const unsigned n = __shfl(pw + __popc(mw), kWords - 1, kGroup);
-        // both halves of a wavefront look at the same tile, each for its rank
-        const unsigned i0 = static_cast<unsigned>(part * kPartCells + (grp & ~1)), i = i0 + (grp & 1);
-        if (i0 >= n) continue;                               // uniform per wavefront
-        const int cl = tile_cell<2>(mw, pw, i0, static_cast<int>(min(i, n - 1u) - i0), tid & 63);
-        row += i;
-        if (i >= n || row >= ws.rows) continue;              // uniform per group; the gather sees the miss
-        const int gx = (tile % ntx) * TX + cl % TX, gy = ((tile / ntx) % nty) * TY + (cl / TX) % TY,
-                  gz = (tile / (ntx * nty)) * TZ + cl / (TX * TY);
-        const int cx = gx - q_dx(q), cy = gy - q_dy(q), cz = gz - q_dz(q);
-        bool src = j < 26 && cx >= 0 && cx < X && cy >= 0 && cy < Y && cz >= 0 && cz < Z;
-        unsigned r = 0u;
-        if (src) {
+        unsigned mw, pw, first;
+        tile_words(ws, tile, j, mw, pw, first);
+        const unsigned n = __shfl(pw + __popc(mw), kWords - 1, 32);
+        unsigned row[PAIRS], r[PAIRS];
+        bool on[PAIRS], src[PAIRS];
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+            const unsigned i0 = static_cast<unsigned>(part * kPartCells + 2 * p) + 2u * pair0, i = i0 + half, at = min(i0, n - 1u);
+            const int cl = tile_cell<2>(mw, pw, at, static_cast<int>(min(i, n - 1u) - at), lane);
+            row[p] = first + i;
+            on[p] = i < n && row[p] < ws.rows;               // (the gather sees a row that does not fit)
+            // a cell off the outer layer: its 26 neighbours lie in the lattice
+            const int cx = (tile % ntx) * TX + cl % TX - q_dx(q), cy = ((tile / ntx) % nty) * TY + (cl / TX) % TY - q_dy(q),
+                      cz = (tile / (ntx * nty)) * TZ + cl / (TX * TY) - q_dz(q);
             const int ctile = ((cz / TZ) * nty + cy / TY) * ntx + cx / TX;
             const int l = ((cz % TZ) * TY + cy % TY) * TX + cx % TX;
-            src = ws.flags[ctile] != 0u && ((ws.mask[static_cast<size_t>(ctile) * kWords + l / 32] >> (l % 32)) & 1u);
-            if (src) r = contrib_row(ws, cx, cy, cz, ntx, nty);
+            const size_t word = static_cast<size_t>(ctile) * kWords;
+            const unsigned any = ws.flags[ctile], mask = ws.mask[word + l / 32], pre0 = ws.prefix[word],
+                           pre = ws.prefix[word + l / 32], base = ws.grows[ctile / ws.per];
+            src[p] = j < 26 && any != 0u && ((mask >> (l % 32)) & 1u);
+            r[p] = base + pre0 + (l >= 32 ? pre : 0u) + __popc(mask & ((1u << (l % 32)) - 1u));
         }
-        const bool stored = src && r < ws.rows;
-        const bool miss = ((__ballot(src && !stored) >> half) & 0xffffffffull) != 0ull;
-        float h0 = 0.0f, h1 = 0.0f, h2 = 0.0f;
-        if (stored) {
-            const float* p = ws.contrib + 27u * ws.rows + static_cast<size_t>(r) * kRowFloatsH + 3 * j;
-            h0 = p[0];
-            h1 = p[1];
-            h2 = p[2];
+        float h[PAIRS][3];
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+            const bool stored = on[p] && src[p] && r[p] < ws.rows;
+            const float* slot = ws.contrib + 27u * ws.rows + static_cast<size_t>(stored ? r[p] : 0u) * kRowFloatsH + 3 * j;
+            h[p][0] = stored ? slot[0] : 0.0f;
+            h[p][1] = stored ? slot[1] : 0.0f;
+            h[p][2] = stored ? slot[2] : 0.0f;
         }
 #pragma unroll
-        for (int o = kGroup / 2; o > 0; o >>= 1) {
-            h0 += __shfl_xor(h0, o, kGroup);
-            h1 += __shfl_xor(h1, o, kGroup);
-            h2 += __shfl_xor(h2, o, kGroup);
-        }
-        if (j < 3) {
-            const float h = j == 0 ? h0 : (j == 1 ? h1 : h2);
-            ws.hbar[3u * row + static_cast<unsigned>(j)] = miss ? __builtin_nanf("") : h;
+        for (int p = 0; p < PAIRS; ++p) {
+            const bool miss = ((__ballot(src[p] && r[p] >= ws.rows) >> (32 * half)) & 0xffffffffull) != 0ull;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) h[p][c] = half_sum(h[p][c]);
+            if (on[p] && j < 3) {
+                const float v = j == 0 ? h[p][0] : (j == 1 ? h[p][1] : h[p][2]);
+                ws.hbar[3u * row[p] + static_cast<unsigned>(j)] = miss ? __builtin_nanf("") : v;
+            }
         }
     }
+}
+
+// With many items a wavefront takes all 8 cells of one through its loads
+// together, with up to 1024 a pair of them: forward and backward of 5 drops in
+// 150 x 131 x 118 (3400 items) 89.9 us with pairs and 86.8 with items, the spray
+// 905 and 856; 28 x 26 x 27 34.6 and 35.7.
+__global__ __launch_bounds__(kThreads) void k_curv_hgather(Workspace ws, int X, int Y, int Z, int ntx, int nty) {
+    const ItemFinder finder(ws);
+    if (finder.total <= 1024u) hgather_items<1>(finder, ws, X, Y, Z, ntx, nty);
+    else hgather_items<kPartCells / 2>(finder, ws, X, Y, Z, ntx, nty);
 }
 
 // Direct backward gather over the tiles with an interface cell in their 3x3x3
