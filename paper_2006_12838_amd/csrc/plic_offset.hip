@@ -282,14 +282,31 @@ __device__ __forceinline__ void offset_block(const S* __restrict__ nx, const S* 
     store_part<S, VEC>(d0, i, count, full, out);
 }
 
+// FP64 arithmetic on float arrays, four problems a thread, closed forms: the second
+// copy of the block, which checks, took these kernels from 126 registers to 130 and
+// more, from 4 wavefronts per SIMD to 3 (64,000,001 problems in three arrays, SZ: 484 us,
+// and 456 where the last block has a launch of its own).  Their last block goes one
+// problem a thread instead, in fewer registers: 450 us, 4 wavefronts; rows
+// 525 -> 511, analytic 494 -> 468.
+template <int SOLVER, class S, class T, int VEC, bool ROWS>
+constexpr bool kOneByOne = sizeof(S) == 4 && sizeof(T) == 8 && VEC == 4 && (SOLVER == kSZ || (SOLVER == kAnalytic && ROWS));
+
 template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
-__global__ __launch_bounds__(kBlock) void k_offset(const S* __restrict__ nx, const S* __restrict__ ny,
-                                                   const S* __restrict__ nz, const S* V0, S* d0, S* keep,
-                                                   int64_t count) {
+__global__ __launch_bounds__(kBlock, (kOneByOne<SOLVER, S, T, VEC, ROWS> ? 4 : 1)) void k_offset(
+    const S* __restrict__ nx, const S* __restrict__ ny, const S* __restrict__ nz, const S* V0, S* d0, S* keep, int64_t count) {
     __shared__ OffsetLds<S, T, VEC, ROWS> sm;
     const int64_t first = static_cast<int64_t>(blockIdx.x) * (kBlock * VEC), i = first + threadIdx.x * VEC;
-    if (first + kBlock * VEC <= count) offset_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, d0, keep, i, count, true, sm);
-    else offset_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, d0, keep, i, count, false, sm);
+    if (first + kBlock * VEC <= count) {
+        offset_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, d0, keep, i, count, true, sm);
+    } else if constexpr (kOneByOne<SOLVER, S, T, VEC, ROWS>) {
+        auto& one = reinterpret_cast<OffsetLds<S, T, 1, ROWS>&>(sm);   // (8 KiB more would cost a wavefront per SIMD too)
+        static_assert(sizeof(one) <= sizeof(sm));
+#pragma unroll 1
+        for (int64_t base = first; base < count; base += kBlock)
+            offset_block<SOLVER, S, T, U, 1, ROWS>(nx, ny, nz, V0, d0, keep, base + threadIdx.x, count, false, one);
+    } else {
+        offset_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, d0, keep, i, count, false, sm);
+    }
 }
 
 template <class S, class T, int VEC, bool ROWS>

@@ -64,3 +64,15 @@ def test_no_kernel_spills_or_has_scratch(kernels):
 def test_execution_mask_restores_are_kept():
     at = build.FLAGS.index("-mllvm=-amdgpu-remove-redundant-endcf=0")
     assert build.FLAGS[at - 1] == "-Xarch_device"
+
+
+def waves(kernel):
+    """wavefronts per SIMD that a kernel's registers allow (512, by 8)"""
+    return 512 // ((kernel[".vgpr_count"] + 7) // 8 * 8)
+
+
+@pytest.mark.parametrize("solver,rows", [("sz", 0), ("sz", 1), ("analytic", 1)])
+def test_closed_forms_in_fp64_keep_four_wavefronts(kernels, solver, rows):
+    """float arrays, FP64 arithmetic, four problems a thread"""
+    name = f"k_offsetILi{['analytic', 'sz'].index(solver)}EfddLi4ELb{rows}E"
+    assert [waves(k) for n, k in kernels.items() if name in n] == [4]
