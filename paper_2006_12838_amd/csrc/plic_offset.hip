@@ -142,7 +142,7 @@ __device__ __forceinline__ void load_rows(const S* n, S* keep, int64_t i, int64_
     }
 #pragma unroll
     for (int k = 0; k < VEC; ++k) {
-        const bool in = i + k < count;
+        const bool in = full || i + k < count;
         const S* r = n + (i + k) * 3;
         a[k] = in ? r[0] : S(0); b[k] = in ? r[1] : S(0); c[k] = in ? r[2] : S(0);
         if (keep && in) {
@@ -291,12 +291,23 @@ __device__ __forceinline__ void offset_block(const S* __restrict__ nx, const S* 
 template <int SOLVER, class S, class T, int VEC, bool ROWS>
 constexpr bool kOneByOne = sizeof(S) == 4 && sizeof(T) == 8 && VEC == 4 && (SOLVER == kSZ || (SOLVER == kAnalytic && ROWS));
 
+// FP64 arithmetic on unaligned float arrays: the last block's threads past count
+// solve its last problem again (the same bits to the same place; V0, which d0 may
+// be, is read before the packing's barriers and d0 written after them), so there is
+// no second copy of the block: 64,000,001 problems, analytic 657 -> 626 us (at most 88
+// registers, not 92), Kawano's variant 813 -> 713 (5 wavefronts per SIMD, not 4),
+// Newton 563 -> 555, nested 725 -> 716; SZ is no faster (652 and 664).
+template <int SOLVER, class S, class T, int VEC>
+constexpr bool kLastAgain = sizeof(S) == 4 && sizeof(T) == 8 && VEC == 1 && SOLVER != kSZ;
+
 template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
 __global__ __launch_bounds__(kBlock, (kOneByOne<SOLVER, S, T, VEC, ROWS> ? 4 : 1)) void k_offset(
     const S* __restrict__ nx, const S* __restrict__ ny, const S* __restrict__ nz, const S* V0, S* d0, S* keep, int64_t count) {
     __shared__ OffsetLds<S, T, VEC, ROWS> sm;
     const int64_t first = static_cast<int64_t>(blockIdx.x) * (kBlock * VEC), i = first + threadIdx.x * VEC;
-    if (first + kBlock * VEC <= count) {
+    if constexpr (kLastAgain<SOLVER, S, T, VEC>) {
+        offset_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, d0, keep, min(i, count - 1), count, true, sm);
+    } else if (first + kBlock * VEC <= count) {
         offset_block<SOLVER, S, T, U, VEC, ROWS>(nx, ny, nz, V0, d0, keep, i, count, true, sm);
     } else if constexpr (kOneByOne<SOLVER, S, T, VEC, ROWS>) {
         auto& one = reinterpret_cast<OffsetLds<S, T, 1, ROWS>&>(sm);   // (8 KiB more would cost a wavefront per SIMD too)

@@ -52,3 +52,19 @@ def check(P, layout, n, V0, solver):
 def test_four_to_a_thread(layout, rest, solver):
     import paper_2006_12838_amd as P
     check(P, layout, *batch(8_000_512 + rest), solver)
+
+
+@pytest.mark.parametrize("solver", ["sz", "analytic", "newton", "nested", "sz_kawano"])
+@pytest.mark.parametrize("layout", ["rows", "arrays"])
+@pytest.mark.parametrize("count", [1, 63, 255, 256, 257, 70_001])
+def test_unaligned(layout, count, solver):
+    import paper_2006_12838_amd as P
+    n, V0 = batch(count, shift=1)
+    if solver == "sz_kawano":                     # NaN for some fill levels of 0 and 1
+        V0.clamp_(0.01, 0.99)
+    check(P, layout, n, V0, solver)
+    want, _ = offsets(P, layout, n, V0, solver)
+    m = V0.numel()
+    own = torch.cat([V0.new_zeros(1), V0, V0.new_full((8,), 7.0)])[1:]
+    got, _ = offsets(P, layout, n, own[:m], solver, d0=own)          # d0 is V0
+    assert torch.equal(got, want)

@@ -76,3 +76,9 @@ def test_closed_forms_in_fp64_keep_four_wavefronts(kernels, solver, rows):
     """float arrays, FP64 arithmetic, four problems a thread"""
     name = f"k_offsetILi{['analytic', 'sz'].index(solver)}EfddLi4ELb{rows}E"
     assert [waves(k) for n, k in kernels.items() if name in n] == [4]
+
+
+@pytest.mark.parametrize("rows", [0, 1])
+def test_unaligned_kawano_in_fp64_keeps_five_wavefronts(kernels, rows):
+    """float arrays, FP64 arithmetic, one problem a thread"""
+    assert [waves(k) for n, k in kernels.items() if f"k_offsetILi4EfddLi1ELb{rows}E" in n] == [5]
