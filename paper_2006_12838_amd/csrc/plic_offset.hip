@@ -69,10 +69,15 @@ __device__ __forceinline__ void store(S* __restrict__ p, int64_t i, const S (&v)
 }
 
 // Loads VEC consecutive elements at i, or those below count (others 0).
-// full: the block's problems all lie below count (uniform per block).
+// full: the block's problems all lie below count (uniform per block).  VEC = 1
+// goes without the hint: its lines are shared by more lanes, and by blocks, than
+// one access covers (64,000,001 unaligned problems, rows, SZ: 395 us, with it 402; 4,000,037
+// 25.2 and 28.4; volume 224 and 248).
 template <class S, int VEC>
 __device__ __forceinline__ void load_part(const S* p, int64_t i, int64_t count, bool full, S (&v)[VEC]) {
-    if (full) {
+    if (VEC == 1 && full) {
+        v[0] = p[i];
+    } else if (full) {
         load<S, VEC>(p, i, v);
     } else {
 #pragma unroll
@@ -82,7 +87,9 @@ __device__ __forceinline__ void load_part(const S* p, int64_t i, int64_t count, 
 
 template <class S, int VEC>
 __device__ __forceinline__ void store_part(S* p, int64_t i, int64_t count, bool full, const S (&v)[VEC]) {
-    if (full) {
+    if (VEC == 1 && full) {
+        p[i] = v[0];
+    } else if (full) {
         store<S, VEC>(p, i, v);
     } else {
 #pragma unroll
@@ -343,8 +350,20 @@ __global__ __launch_bounds__(kBlock) void k_volume(const S* __restrict__ nx, con
                                                    int64_t count) {
     __shared__ RowStage<S, VEC> rows[ROWS ? kBlock / 64 : 1];
     const int64_t first = static_cast<int64_t>(blockIdx.x) * (kBlock * VEC), i = first + threadIdx.x * VEC;
-    if (first + kBlock * VEC <= count) volume_block<S, T, VEC, ROWS>(nx, ny, nz, d0, V0, i, count, true, rows);
-    else volume_block<S, T, VEC, ROWS>(nx, ny, nz, d0, V0, i, count, false, rows);
+    if constexpr (sizeof(S) == 8 && VEC == 1 && !ROWS) {
+        // unaligned doubles, 8 lanes to a line: each thread checks for itself, one copy of
+        // the block, and the hint pays (64,000,001: 423 us, 444 with two copies without it)
+        if (i < count) {
+            S a[1], b[1], c[1], v[1];
+            load<S, 1>(nx, i, a); load<S, 1>(ny, i, b); load<S, 1>(nz, i, c); load<S, 1>(d0, i, v);
+            const S r[1] = {S(volume<T>(T(a[0]), T(b[0]), T(c[0]), T(v[0])))};
+            store<S, 1>(V0, i, r);
+        }
+    } else if (first + kBlock * VEC <= count) {
+        volume_block<S, T, VEC, ROWS>(nx, ny, nz, d0, V0, i, count, true, rows);
+    } else {
+        volume_block<S, T, VEC, ROWS>(nx, ny, nz, d0, V0, i, count, false, rows);
+    }
 }
 
 // plane-sphere intersection (Sec. 3): one input and one output array;
