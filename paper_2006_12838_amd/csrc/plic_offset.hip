@@ -28,6 +28,9 @@ constexpr int kBlock = 256;
 // (measured: a plain 5-read / 4-write copy and this kernel both about 6 % faster
 // than with 256).  Others: 256, which fill and leave the chip sooner (20,000 float
 // rows 6.9 -> 5.8 us, 10,000 double rows 6.9 -> 5.0 us).
+// Measured since: doubles, 16,000,001 and 32,000,011 rows, 256 and 512 threads, SZ 265.0
+// and 264.2, 512.8 and 512.8; Newton 283.1 and 285.9, 546.9 and 545.4; unaligned floats,
+// 16,000,001 and 64,000,001 in three arrays, SZ 111.0 and 112.4, 452.9 and 455.3.
 constexpr int kBwdBlock = 512;
 template <int VEC> constexpr int kBwdThreads = VEC == 4 ? kBwdBlock : kBlock;
 
@@ -526,8 +529,15 @@ void launch_bwd_v(const BwdArgs<S>& p, hipStream_t st) {
 // backward of rows, 100,003 7.1 and 4.7, 1,000,003 11.2 and 10.0, 4,000,037 29.3 and
 // 28.5, 7,900,001 53.3 and 51.0, 12,000,001 75.4 and 77.4; of three arrays, 1,000,003
 // 10.6 and 9.0, 7,900,001 53.7 and 50.9.  (A volume is no faster with two at any
-// size: 4,000,037 rows 14.7 and 15.3.)
-constexpr int64_t kManyProblems = 8000000, kManyArrays = 4000000;
+// size: 4,000,037 rows 14.7 and 15.3.)  The other solvers behave alike in FP32 and
+// mixed arithmetic (7,900,001 rows forward: Newton 44.3 and 44.0, nested 44.5 and 43.1,
+// analytic 44.7 and 41.9).  In FP64 arithmetic the closed forms fill the chip with
+// fewer problems: SZ forward of rows, 1,500,001 18.1 and 18.0, 2,000,003 21.9 and 22.7,
+// 2,500,001 26.1 and 27.2, 7,900,001 69.7 and 76.6; analytic 1,500,001 17.2 and 17.1, 2,000,003
+// 20.6 and 21.6, 7,900,001 64.4 and 72.6, of three arrays 54.9 and 64.5; the iterative ones do not
+// (Newton 7,900,001 rows 69.0 and 67.0, nested 83.0 and 82.5), nor does a backward (SZ 124.9 and
+// 120.5).
+constexpr int64_t kManyProblems = 8000000, kManyArrays = 4000000, kManyClosed64 = 2000000;
 
 template <int SOLVER, class S, class T, class U, int VEC, bool ROWS>
 void launch_v(const OffsetArgs<S>& p, hipStream_t st) {
@@ -541,9 +551,11 @@ void launch_v(const BwdArgs<S>& p, hipStream_t st) {
 template <int SOLVER, class S, class T, class U, bool ROWS, class Args>
 void launch_t(const Args& p, bool vec, hipStream_t st) {
     if (!vec) return launch_v<SOLVER, S, T, U, 1, ROWS>(p, st);
-    constexpr bool kArrays = !ROWS && std::is_same_v<Args, OffsetArgs<S>>;
+    constexpr bool kForward = std::is_same_v<Args, OffsetArgs<S>>;
+    constexpr bool kClosed64 = kForward && sizeof(T) == 8 && (SOLVER == kSZ || SOLVER == kAnalytic);
+    constexpr int64_t kMany = kClosed64 ? kManyClosed64 : (kForward && !ROWS ? kManyArrays : kManyProblems);
     if constexpr (sizeof(S) == 4)
-        if (p.count > (kArrays ? kManyArrays : kManyProblems)) return launch_v<SOLVER, S, T, U, 4, ROWS>(p, st);
+        if (p.count > kMany) return launch_v<SOLVER, S, T, U, 4, ROWS>(p, st);
     launch_v<SOLVER, S, T, U, 2, ROWS>(p, st);
 }
 
