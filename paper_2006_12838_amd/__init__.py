@@ -15,6 +15,8 @@ plain contiguous tensors (``_native``), ``torch.autograd.Function``s for the res
 """
 from __future__ import annotations
 
+import warnings
+
 import torch
 
 from ._lib import (  # noqa: F401  (re-exported: the C ABI by name)
@@ -59,8 +61,10 @@ from ._lib import (  # noqa: F401  (re-exported: the C ABI by name)
 
 try:  # after _lib: both use the one libplic.so
     from . import _native
-except ImportError as e:
-    raise ImportError(f"{__name__}._native is not built (run __graft_entry__.build()): {e}") from e
+except ImportError as e:  # not built, or against another torch: every call has its Python function
+    warnings.warn(f"{__name__}._native does not load, calls go through the slower Python functions "
+                  f"(run __graft_entry__.build()): {e}", RuntimeWarning, stacklevel=2)
+    _native = None
 
 __all__ = ["offset", "volume", "curvature", "PlicOffset", "PlicCurvature", "SOLVERS", "PAPER_SOLVERS", "PRECISIONS",
            "NORMALS",
@@ -107,10 +111,10 @@ class PlicOffset(torch.autograd.Function):
 
 
 def _native_may():
-    """Whether the native functions may be tried: not under a function
-    transform, a trace or a dispatch mode, which the Python path meets (or
-    refuses) as ever."""
-    return not (torch._C._are_functorch_transforms_active() or torch._C._len_torch_dispatch_stack()
+    """Whether the native functions may be tried: where they are loaded, and not
+    under a function transform, a trace or a dispatch mode, which the Python
+    path meets (or refuses) as ever."""
+    return not (_native is None or torch._C._are_functorch_transforms_active() or torch._C._len_torch_dispatch_stack()
                 or torch._C._get_tracing_state() is not None or torch.compiler.is_compiling())
 
 
