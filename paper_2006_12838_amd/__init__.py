@@ -181,9 +181,9 @@ class PlicCurvature(torch.autograd.Function):
         (phi,) = ctx.saved_tensors
         solver, precision, normal, neighbour_normals = ctx.opts
         grad_phi = torch.empty_like(phi)
+        ws, ctx.ws = ctx.ws, None            # a second backward takes another one and scans
         plic_curvature_backward_ex_f32(phi, grad_kappa.contiguous(), grad_phi, solver, precision, normal,
-                                       neighbour_normals, ctx.ws, reuse=True, grow=True)
-        ctx.ws = None
+                                       neighbour_normals, ws, reuse=ws is not None, grow=True)
         return grad_phi, None, None, None, None
 
 
