@@ -34,10 +34,11 @@
 
 #include <hip/hip_runtime.h>
 
+#include <memory>
 #include <mutex>
+#include <new>
 #include <type_traits>
 #include <unordered_map>
-#include <vector>
 
 #include "plic_host.hpp"
 #include "plic_math.hpp"
@@ -2062,7 +2063,11 @@ void note_scan(const void* ws, const float* phi, int64_t X, int64_t Y, int64_t Z
         return;
     }
     if (g_records.size() >= kMaxRecords && g_records.find(ws) == g_records.end()) g_records.clear();
-    g_records[ws] = ScanRecord{phi, X, Y, Z};
+    try {
+        g_records[ws] = ScanRecord{phi, X, Y, Z};
+    } catch (const std::bad_alloc&) {        // no exception leaves a C entry
+        g_records.clear();
+    }
 }
 
 bool has_scan(const void* ws, const float* phi, int64_t X, int64_t Y, int64_t Z) {
@@ -2253,16 +2258,16 @@ int plic_curvature_status(const void* workspace, size_t workspace_bytes, int64_t
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Workspace ws = carve(const_cast<void*>(workspace), workspace_bytes, g, nbr);
     // the call's interface count is the sum of the tiles' counts the scan wrote
-    std::vector<unsigned> flags(static_cast<size_t>(g.ntiles));
-    hipError_t e = hipStreamSynchronize(st);
-    if (e == hipSuccess)
-        e = hipMemcpy(flags.data(), ws.flags, flags.size() * sizeof(unsigned), hipMemcpyDeviceToHost);
+    const size_t ntiles = static_cast<size_t>(g.ntiles);
+    const std::unique_ptr<unsigned[]> flags(new (std::nothrow) unsigned[ntiles]);
+    hipError_t e = flags ? hipStreamSynchronize(st) : hipErrorOutOfMemory;
+    if (e == hipSuccess) e = hipMemcpy(flags.get(), ws.flags, ntiles * sizeof(unsigned), hipMemcpyDeviceToHost);
     if (e != hipSuccess) {
         set_last_hip_error(static_cast<int>(e));
         return PLIC_EHIP;
     }
     uint64_t cells = 0;
-    for (const unsigned f : flags) cells += f;
+    for (size_t k = 0; k < ntiles; ++k) cells += flags[k];
     const size_t row_bytes = nbr ? kRowBytesNbr : kRowBytes;
     if (interface_cells) *interface_cells = static_cast<int64_t>(cells);
     if (bytes_for_all_rows) *bytes_for_all_rows = fixed_bytes(g) + static_cast<size_t>(cells) * row_bytes;
