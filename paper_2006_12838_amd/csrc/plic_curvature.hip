@@ -196,10 +196,13 @@ __device__ __forceinline__ void gradient27(const float* __restrict__ s, int c, i
 // times enlarged.  Where a pivot falls below kSteady of the largest diagonal
 // entry, the sums are formed again over the 16 pairs of neighbours (l, l + 16)
 // of the 26 in order, so that they do not depend on how the lanes shared out
-// the list (one such cell moved by 5e-5 of the spray's whole gradient).  Those
-// cells are done again four at a time on 16 lanes each: on their own 4 lanes,
+// the list (one such cell moved by 5e-5 of the spray's whole gradient).  Cells on
+// 4 lanes are then done again four at a time on 16 lanes each: on their own 4 lanes,
 // whose wavefront waits for them, a 100 x 98 x 99 lattice's forward and backward
-// took 47.2 us instead of 44.0, a 120 x 118 x 119 one's 44.7 instead of 42.6.
+// took 47.2 us instead of 44.0, a 120 x 118 x 119 one's 44.7 instead of 42.6.  Cells on 16
+// lanes form them at once, from the points that are there: done again from the
+// start, the forward of a 64^3 lattice with specks in 2 % of its cells took 17.8 us
+// instead of 15.2, of a 32^3 one with specks in 20 % 18.6 instead of 15.6.
 // ---------------------------------------------------------------------------
 constexpr int kRowFloatsH = 26 * 3;             // a cell's adjoints of its neighbours' own gradients
 constexpr unsigned kCentre = 1u << 13;
@@ -446,13 +449,13 @@ __device__ __forceinline__ void ordered_sums(int l, unsigned mask, unsigned list
     __syncwarp();
 }
 
-// The groups that were not done, four of the wavefront at a time on 16 lanes
-// each: again(src) with the first lane of such a group, or -1 where none is
+// The groups of 4 lanes that were not done, four of the wavefront at a time on
+// 16 lanes each: again(src) with the first lane of such a group, or -1 where none is
 // left.  Every lane of the wavefront must call it.
-template <int LANES, class Again>
+template <class Again>
 __device__ __forceinline__ void redo_groups(bool done, int lane, Again again) {
-    constexpr unsigned long long kFirst = LANES == kLanes ? 0x1111111111111111ull : 0x0001000100010001ull;
-    for (unsigned long long left = __ballot(!done) & kFirst; left;) {
+    static_assert(kLanes == 4, "every fourth lane is the first of its group");
+    for (unsigned long long left = __ballot(!done) & 0x1111111111111111ull; left;) {
         int src = -1;
 #pragma unroll
         for (int k = 0; k < 64 / kWideLanes; ++k, left &= left - 1ull)
@@ -465,8 +468,8 @@ __device__ __forceinline__ void redo_groups(bool done, int lane, Again again) {
 
 // s: LDS fill levels, c: centre index, sy/sz: LDS strides, lane: lane in the
 // wavefront, LANES per cell.  Every lane of the group must call it.  False, with
-// nothing written, when the fit is ill-conditioned and the sums were not
-// ORDERED: the caller then calls it again with ORDERED (from the fill levels:
+// nothing written, when the fit is ill-conditioned on 4 lanes:
+// the caller then calls it again on 16 with ORDERED (from the fill levels:
 // with both kinds of sums in one call, what had to be kept in registers for the
 // second made the first slower, 38.4 -> 42.0 us for a 220 x 218 x 219 forward).
 // kappa: the same bits on every lane.  With ADJ,
@@ -598,17 +601,25 @@ __device__ __forceinline__ bool curv_cell(const float* __restrict__ s, int c, in
     }
     const int npts = __popc(mask);
     F m[5][5], b[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        b[i] = sum[15 + i];
-#pragma unroll
-        for (int l = 0; l <= i; ++l) m[i][l] = sum[tri(i, l)];
-    }
     bool act[5];
     F a[5], dinv[5];
-    const bool steady = ldlt_factor<F>(m, npts < 5 ? npts : 5, act, dinv);
-    if constexpr (!ORDERED)
-        if (!steady) return false;
+    auto factor = [&] {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            b[i] = sum[15 + i];
+#pragma unroll
+            for (int l = 0; l <= i; ++l) m[i][l] = sum[tri(i, l)];
+        }
+        return ldlt_factor<F>(m, npts < 5 ? npts : 5, act, dinv);
+    };
+    const bool steady = factor();
+    if constexpr (!ORDERED) {
+        if (!steady) {
+            if constexpr (LANES == kLanes) return false;
+            ordered_sums<F>(j, mask, list, point, L.o.wide.terms[cell], sum);
+            factor();
+        }
+    }
     ldlt_solve<F>(m, act, dinv, b, a);
     kappa = float(kappa_of<F>(a));
     if constexpr (ADJ) {
@@ -1241,7 +1252,7 @@ __device__ __forceinline__ void cell_items(const ItemFinder& finder, unsigned bl
         if (on) {
             if constexpr (ADJ) {
                 gk = gkap[gi];
-                if (j == 0) lds.at[cell] = make_int4(gx, gy, gz, static_cast<int>(row));
+                if (LANES == kLanes && j == 0) lds.at[cell] = make_int4(gx, gy, gz, static_cast<int>(row));
             }
             if constexpr (NBR) {
                 // 25 rows of 5 levels, those outside the lattice read as 0
@@ -1278,7 +1289,7 @@ __device__ __forceinline__ void cell_items(const ItemFinder& finder, unsigned bl
         }
         if constexpr (!ADJ)
             if (on && done && j == 0) out_field[gi] = kv;
-        redo_groups<LANES>(done, lane, [&](int src) {
+        if constexpr (LANES == kLanes) redo_groups(done, lane, [&](int src) {
             const int from = max(src, 0);
             Place at{0, 0, 0, X, Y, Z};
             unsigned r = 0u;
@@ -1445,7 +1456,7 @@ __global__ __launch_bounds__(kThreads) void k_curv_gather_fallback(const float* 
                         done = curv_cell<kLanes, false, SOLVER, T, U, F, true, NRM>(s, centre, RX, RX * RY, lane, gk, contrib[i],
                                                                                     1u, nullptr, lds, kv);
                     }
-                    redo_groups<kLanes>(done, lane, [&](int src) {
+                    redo_groups(done, lane, [&](int src) {
                         const int from = max(src, 0), ai = __shfl(i, from, 64), ac = __shfl(centre, from, 64);
                         const float ag = __shfl(gk, from, 64);
                         if (src >= 0)
