@@ -1190,19 +1190,34 @@ __host__ __device__ inline unsigned zero_blocks(const Workspace& ws) {
     return ws.segs >= 256 ? 256u : static_cast<unsigned>(ws.segs) * zero_parts(ws);
 }
 
-// Up to this many work items the cells take 16 lanes each instead of 4: there
-// are then no more wavefronts than the chip holds at once, and the time is that
-// of one cell's chain, which 16 lanes shorten (one round of PLIC problems and
-// points instead of three or four).  Forward and backward with 4 and with 16
-// lanes, mixed precision: 64 x 62 x 63 (600 items) 34.9 and 33.3 us, with neighbour normals
-// 56.8 and 46.1; 100 x 98 x 99 (1400 items) 43.7 and 44.6, with neighbour
-// normals 69.7 and 66.8 (FP64: 77.9 and 78.0); 120 x 118 x 119 (2000 items)
-// 42.4 and 50.9, with neighbour normals 69.7 and 70.5; 150 x 148 x 149 (3100)
-// 57.8 and 72.9, 88.5 and 100.4.  Both give the same bits.
-template <class T, bool NBR> constexpr unsigned kWideItems = NBR && sizeof(T) == 4 ? 2048 : 1024;
+// Up to this many work items the cells take 16 lanes each instead of 4: the chip
+// then holds few more wavefronts than there are, or none, and the time is that of
+// one cell's chain, which 16 lanes shorten (one round of PLIC problems and points
+// instead of three or four).  Both give the same bits.  The line lies where the
+// two meet: later for Newton, whose chain is the longest and varies, and with
+// neighbour normals, later forward than adjoint there (fewer wavefronts fit), and
+// earlier where FP64 points halve the wavefronts that fit.  Graph-timed us with 4 and
+// with 16 lanes, one drop in a box, at items
+//   SZ forward, mixed     837 13.9 13.5, 1078 14.1 14.7   FP32 1359 15.1 14.7, 1650 15.6 16.4
+//                 FP64    837 15.5 15.2, 947 14.8 16.2
+//      adjoint, mixed     947 23.5 23.1, 1078 24.9 25.0   FP32 1359 24.9 24.5, 1514 24.1 25.5
+//   Newton forward, mixed 1514 21.0 19.1, 1650 19.5 20.9  FP32 1972 19.7 17.8, 2659 21.7 22.4
+//                 FP64    2324 33.1 30.7, 2659 35.1 34.9
+//      adjoint, mixed     1514 30.2 30.0, 1650 29.7 33.1  FP64 1972 46.5 39.3, 2324 42.9 45.3
+//   with neighbour normals, SZ forward, mixed 1972 23.2 22.0, 2659 26.6 29.1  FP64 1205 23.8 22.5, 1359 23.9 26.1
+//      adjoint, mixed     1078 42.0 39.6, 1359 43.7 44.7  FP64 1514 52.9 52.5, 1650 52.1 56.0
+//   Newton adjoint, mixed 1514 48.7 46.6, 1650 47.5 48.6  FP64 2324 67.8 64.0, 2659 72.2 75.3
+// (analytic as SZ; nested as SZ or a little later: FP64 forward with neighbour
+// normals 1650 32.7 30.1, 1808 31.6 32.4).
+template <int SOLVER, class T, class F, bool ADJ, bool NBR> constexpr unsigned wide_items() {
+    if (sizeof(T) == 8 && SOLVER == kNewton) return ADJ ? 2048 : 2560;
+    if (sizeof(T) == 8) return NBR ? (ADJ ? 1536 : (SOLVER == kNested ? 1700 : 1300)) : 900;
+    if (NBR) return ADJ ? (SOLVER == kNewton ? 1536 : 1300) : 2048;
+    if (SOLVER == kNewton) return sizeof(F) == 4 && !ADJ ? 2048 : 1536;
+    return sizeof(F) == 4 ? 1400 : 1024;
+}
 
-// wavefronts per SIMD: what the registers allow without scratch memory (but for
-// 8 bytes in the mixed nested forward)
+// wavefronts per SIMD: what the registers allow without scratch memory
 template <class T, bool ADJ, bool NBR>
 constexpr int cell_waves() {
     return sizeof(T) == 4 ? (ADJ ? (NBR ? 2 : 3) : 4) : 2;
@@ -1342,7 +1357,7 @@ __global__ __launch_bounds__(64, (cell_waves<T, ADJ, NBR>())) void k_curv_quads(
     }
     init_cells<NRM>(lds, static_cast<int>(threadIdx.x));
     const ItemFinder finder(ws);
-    if (finder.total <= kWideItems<T, NBR>)
+    if (finder.total <= wide_items<SOLVER, T, F, ADJ, NBR>())
         cell_items<kWideLanes, SOLVER, T, U, F, ADJ, NRM, NBR>(finder, block, blocks, nbh, lds, phi, gkap, out_field, ws, X, Y,
                                                                Z, ntx, nty);
     else
