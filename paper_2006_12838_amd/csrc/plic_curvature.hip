@@ -1077,6 +1077,9 @@ struct ItemFinder {
         const int l1 = __ffsll(__ballot(before <= hi && hi - before < mine)) - 1;
         const int owner = lane & 32 ? l1 : l0, k = lane & 31;
         unsigned rest = lane & 32 ? hi - from_lane(before, l1) : lo - from_lane(before, l0);
+        // up to 64 groups, one a lane: that is the group, without a second look at the
+        // counts (forwards of 48 x 46 x 47 12.2 -> 11.9 us, FP64 13.1 -> 12.8)
+        if (ws.groups <= 64) return ws.items[static_cast<size_t>(owner) * ws.per * kMaxParts + rest];
         // the owner's groups, a run of up to 4 per lane of the half
         const int run = (ws.groups + 64 * 32 - 1) / (64 * 32);
         unsigned c[kMaxGroups / (64 * 32)], sum = 0u;
