@@ -429,7 +429,7 @@ def write_trace_profile(trace_csv, out=None):
         "call counts.",
         "",
         "Template arguments: `k_offset<solver, storage, bulk, cubic, problems per lane, normals as rows>`, "
-        "`k_curv_quads<solver, points, cubic, fit, backward, normal, neighbour normals>` (4 lanes per cell), "
+        "`k_curv_quads<solver, points, cubic, fit, backward, normal, neighbour normals>` (4 lanes per cell, 16 where cells are few), "
         "`k_curv_gather_fallback<solver, points, cubic, fit, normal>`, "
         "`k_curv_scan<writes the zeros, wavefronts>`, `k_curv_gather_direct<neighbour normals, normal>`; solver 0 analytic, 1 optimized SZ, "
         "2 Newton-Raphson, 3 nested intervals, 4 Kawano's SZ; normal 0 Parker-Youngs.",

@@ -160,7 +160,7 @@ int plic_offset_backward_rows_f64(const double *n, const double *V0, const doubl
  * part.  0 for an empty or invalid lattice (2^24 tiles or more, i.e. about
  * 1.7e10 cells, is invalid).
  * The workspace is caller-owned device memory; its contents need no
- * initialisation (each call clears what it uses with a kernel) and are
+ * initialisation (each call writes what it reads) and are
  * scratch after the call.
  */
 size_t plic_curvature_workspace_bytes(int64_t X, int64_t Y, int64_t Z);
@@ -215,7 +215,7 @@ int plic_curvature_f32(const float *phi, int64_t X, int64_t Y, int64_t Z, float 
  * 21,399 tiles of 64x4x4 cells (256^3 has 16,384) fit; a larger lattice
  * returns PLIC_EWORKSPACE before anything is launched.  Every call on a GPU
  * shares that GPU's array, which keeps the last call's contents (each call
- * clears what it uses): calls that overlap in time on one GPU (several
+ * writes what it reads): calls that overlap in time on one GPU (several
  * streams or host threads) race and must be serialised by the caller.
  * Arguments, status codes and results (bit for bit) are otherwise those of
  * plic_curvature_f32.
@@ -324,8 +324,8 @@ int plic_curvature_backward_reuse_f32(const float *phi, int64_t X, int64_t Y, in
 /*
  * plic_curvature_status — what the last curvature call (forward or backward,
  * any variant) found on `workspace`, read after it completed: this call
- * synchronises `stream` (the stream of that call) and copies 24 bytes of the
- * workspace header to the host.  Not for use under graph capture.
+ * synchronises `stream` (the stream of that call) and copies the tiles' counts,
+ * 4 bytes per tile, to the host.  Not for use under graph capture.
  *   X, Y, Z, neighbour_normals, workspace_bytes : as in that call.
  *   interface_cells    : if not NULL, receives its interface-cell count.
  *   bytes_for_all_rows : if not NULL, receives the workspace size that holds
@@ -337,7 +337,8 @@ int plic_curvature_backward_reuse_f32(const float *phi, int64_t X, int64_t Y, in
  * bytes_for_all_rows and call it again), else PLIC_OK (the base backward
  * recomputes missing rows, so its result is complete for any size).
  * PLIC_EINVAL for an invalid lattice, flag or pointer, PLIC_EHIP when the
- * stream or the copy fails.  Row indices are 32-bit: the neighbour-normal
+ * stream or the copy fails or the host has no memory for the counts.  Row
+ * indices are 32-bit: the neighbour-normal
  * variant holds at most 10,226,107 rows, whatever the workspace.
  */
 int plic_curvature_status(const void *workspace, size_t workspace_bytes, int64_t X, int64_t Y, int64_t Z,

@@ -851,11 +851,15 @@ constexpr int kWords = kTile / 32;            // mask words per tile
 constexpr size_t kFixedPerTile = sizeof(unsigned) * (1 + 1 + kWords + kWords + kMaxParts + 1 + 1);
 constexpr size_t kRowBytes = 27 * sizeof(float);
 constexpr size_t kDefaultRowsPerTile = 16;    // contribution rows budgeted per tile by default
-// rows are 32-bit indices: first rows saturate at kRowCap, so that a first
-// row plus a rank (< kTile) never wraps and a saturated tile recomputes; the
+// rows are 32-bit indices: the groups' first rows saturate at kRowCap, so that
+// such a row plus a cell's rank in its group (below 2^21: at most 2048 tiles)
+// never wraps and is past the store, so the cell is recomputed; the
 // capacity is at most kRowLimit rows, so an entry's index q * rows + row stays
 // below 2^30 (a 32-bit byte offset from the store's base)
 constexpr unsigned kRowCap = 0xF0000000u;
+constexpr int64_t kMaxTiles = int64_t(1) << 24;      // see check_lattice
+constexpr int64_t kMaxGroupTiles = kScanWaves * ((kMaxTiles + kScanWaves * kMaxGroups - 1) / (kScanWaves * kMaxGroups));
+static_assert(kRowCap + kMaxGroupTiles * kTile < int64_t(1) << 32);
 constexpr unsigned kRowLimit = (1u << 30) / 27u;
 // The neighbour-normal variant's backward: a row holds the 27 contributions
 // and, per neighbour, the adjoint of that neighbour's own fill-level gradient
@@ -1591,7 +1595,9 @@ __device__ __forceinline__ void hgather_items(const ItemFinder& finder, const Wo
 // With many items a wavefront takes all 8 cells of one through its loads
 // together, with up to 1024 a pair of them: forward and backward of 5 drops in
 // 150 x 131 x 118 (3400 items) 89.9 us with pairs and 86.8 with items, the spray
-// 905 and 856; 28 x 26 x 27 34.6 and 35.7.
+// 905 and 856; 28 x 26 x 27 34.6 and 35.7.  Between, the backward alone, pairs and
+// items (mixed): 678 items 30.7 and 31.1, 837 32.6 and 32.5, 1078 38.9 and 39.3, 1514 44.3
+// and 44.3, 1808 47.2 and 46.2, 2659 51.9 and 49.8.
 __global__ __launch_bounds__(kThreads) void k_curv_hgather(Workspace ws, int X, int Y, int Z, int ntx, int nty) {
     const ItemFinder finder(ws);
     if (finder.total <= 1024u) hgather_items<1>(finder, ws, X, Y, Z, ntx, nty);
@@ -1690,7 +1696,7 @@ struct TileFinder {
     __device__ __forceinline__ int tile(const Workspace& ws, int lane, unsigned i) const {
         const int owner = __ffsll(__ballot(before <= i && i - before < mine)) - 1;
         const unsigned rest = i - from_lane(before, owner);
-        const unsigned long long bits = lane * 64 + owner < 4096 ? of(ws, seg0 + lane * 64 + owner) : 0ull;
+        const unsigned long long bits = of(ws, seg0 + lane * 64 + owner);
         const unsigned n = static_cast<unsigned>(__popcll(bits)), excl = wave_scan(n) - n;
         const int at = __ffsll(__ballot(excl <= rest && rest - excl < n)) - 1;
         const unsigned long long found = from_lane(static_cast<unsigned>(bits), at) |
@@ -1869,9 +1875,9 @@ int check_lattice(int64_t X, int64_t Y, int64_t Z, bool* empty, Grid* g) {
     if (X > (int64_t(1) << 62) / Y / Z) return PLIC_EINVAL;
     const int64_t tx = (X + TX - 1) / TX, ty = (Y + TY - 1) / TY, tz = (Z + TZ - 1) / TZ;
     if (tx > lim / ty || tx * ty > lim / tz) return PLIC_EINVAL;   // grid limit
-    // the scan launches 256 work-items per tile (a dispatch holds < 2^32), and
-    // work items hold a 25-bit tile index
-    if (tx * ty * tz >= (int64_t(1) << 24)) return PLIC_EINVAL;
+    // a work item holds tile << 7 in 32 bits, and the work items of all tiles, up to
+    // 128 each, are counted in 32 bits
+    if (tx * ty * tz >= kMaxTiles) return PLIC_EINVAL;
     g->ntx = static_cast<int>(tx);
     g->nty = static_cast<int>(ty);
     g->ntz = static_cast<int>(tz);
@@ -1969,9 +1975,12 @@ void launch_bwd_t(const float* phi, const float* gk, float* gp, Workspace ws, in
                   const Grid& g, hipStream_t st) {
     launch_cells<SOLVER, T, U, F, true, NRM>(phi, gk, gp, ws, X, Y, Z, g, st);
     launch_gather<false, 0>(gp, ws, X, Y, Z, g, st);
-    // usually empty.  Its registers and LDS allow one workgroup per CU, so a
-    // grid of one per CU (256) runs in a single round, cheap when nothing
-    // overflowed and as concurrent as any larger grid when something did
+    // empty where every row fits: the recommended workspace holds 16 a tile, which a
+    // drop in a box of 40^3 and more does not exceed, one in 28^3 or several in 64^3 do
+    // (their backwards take 53 and 96 us so, 17 and 21 with room for all).  Its registers
+    // (over 256 with the accumulators) allow one workgroup per CU, so a grid of one
+    // per CU (256) runs in a single round, cheap when nothing overflowed and as
+    // concurrent as any larger grid when something did
     hipLaunchKernelGGL((k_curv_gather_fallback<SOLVER, T, U, F, NRM>),
                        dim3(g.ntiles < kFallbackBlocks ? g.ntiles : kFallbackBlocks), dim3(kThreads), 0, st, phi,
                        gk, gp, ws, X, Y, Z, g.ntx, g.nty);
