@@ -335,6 +335,9 @@ __device__ __forceinline__ void volume_block(const S* __restrict__ nx, const S* 
                                              const S* __restrict__ nz, const S* d0, S* V0, int64_t i, int64_t count,
                                              bool full, RowStage<S, VEC>* rows) {
     S a[VEC], b[VEC], c[VEC], v[VEC], r[VEC];
+    // FP64 arithmetic on three float arrays: a thread of the last block whose problems
+    // all lie below count takes the vector accesses too (1,003 problems 4.2 -> 3.7 us)
+    if constexpr (sizeof(S) == 4 && sizeof(T) == 8 && VEC > 1 && !ROWS) full = full || i + VEC <= count;
     if constexpr (ROWS) {
         load_rows<S, VEC>(nx, nullptr, i, count, full, rows[threadIdx.x >> 6], a, b, c);
     } else {

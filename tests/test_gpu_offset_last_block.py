@@ -68,3 +68,22 @@ def test_unaligned(layout, count, solver):
     own = torch.cat([V0.new_zeros(1), V0, V0.new_full((8,), 7.0)])[1:]
     got, _ = offsets(P, layout, n, own[:m], solver, d0=own)          # d0 is V0
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("count", [1, 3, 4, 5, 1021, 1023, 1024, 1025, 1027, 5003])
+def test_volume_of_arrays(count, precision):
+    """aligned arrays (four problems a thread) and the same unaligned (one)"""
+    import paper_2006_12838_amd as P
+
+    g = torch.Generator(device="cuda").manual_seed(count)
+    n = [torch.randn(count, generator=g, device="cuda") for _ in range(3)]
+    d0 = torch.rand(count, generator=g, device="cuda") * 2.0 - 1.0
+    res = []
+    for shift in (0, 1):
+        a = [torch.cat([t.new_zeros(shift), t])[shift:] for t in (*n, d0)]
+        out = torch.full((count + shift + 8,), 7.0, device="cuda")[shift:]
+        P.plic_volume_f32(*a, out[:count], precision)
+        assert (out[count:] == 7.0).all()
+        res.append(out[:count])
+    assert torch.equal(*res) and (res[0] >= 0).all() and (res[0] <= 1).all()
