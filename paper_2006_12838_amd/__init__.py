@@ -111,11 +111,17 @@ class PlicOffset(torch.autograd.Function):
 
 
 def _native_may():
-    """Whether the native functions may be tried: where they are loaded, and not
-    under a function transform, a trace or a dispatch mode, which the Python
-    path meets (or refuses) as ever."""
-    return not (_native is None or torch._C._are_functorch_transforms_active() or torch._C._len_torch_dispatch_stack()
+    """Whether the native functions may be tried: not under a function
+    transform, a trace or a dispatch mode, which the Python path meets (or
+    refuses) as ever."""
+    return not (torch._C._are_functorch_transforms_active() or torch._C._len_torch_dispatch_stack()
                 or torch._C._get_tracing_state() is not None or torch.compiler.is_compiling())
+
+
+if _native is None:
+    def _native_may():  # noqa: F811
+        """Without the native functions: never."""
+        return False
 
 
 def _precision(t, precision):
